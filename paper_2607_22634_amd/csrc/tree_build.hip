@@ -1,26 +1,10 @@
-// Stage 2: prefix-aligned scoring and best-first tree construction.
+// Stage 2: prefix-aligned scoring and draft-tree construction.
 //
-// One wavefront builds one sequence's tree; the batch runs in parallel.
-// LDS holds the candidate table (log q, token ids), the trigram lattice when
-// it fits, and per committed node one 8-byte record (parent, rank, depth, S)
-// plus its children in commit order (ranked once, when the node is
-// committed).  The frontier lives in registers spread over the 64 lanes (SL
-// slots per lane), each slot only (S, packed metadata): a pop is a per-lane
-// max, one DPP wave max and a ballot; the next sibling of a popped node is
-// one LDS read.  Rank-path keys are only derived when several frontier
-// entries share the best S (from the parent records, up to the nearest node
-// whose key an earlier tie stored); token ids, the output rows and the
-// ancestor bitmasks are produced after the search, in parallel over the
-// nodes.
-//
-// Frontier policy.  Committing nodes in pop order yields the B best prefixes
-// under the total order (S desc, rank path asc).  Instead of pushing all of
-// a node's children at once, the frontier holds, for every committed node,
-// only its next not-yet-committed child in that order: committing a node
-// pushes its first child, committing a child pushes its next sibling.  The
-// best uncommitted prefix always has a committed parent and committed
-// better siblings, so it is always in the frontier; the frontier never
-// holds more than (committed + 1) entries.
+// One workgroup builds one sequence's tree; the batch runs in parallel.
+// Three kernels, one per mode:
+//   tree_level_kernel   best-first (the budget best prefixes), level by level
+//   tree_beam_kernel    beam search with global retention
+//   tree_alg2_kernel    Alg. 2 as printed
 #include <math.h>
 
 #include <type_traits>
@@ -32,8 +16,6 @@
 #pragma clang fp contract(off)
 
 namespace presto {
-
-constexpr int kBeamCandSlots = 4;  // beam search: W * k <= 4 * 64 candidates per depth
 
 struct TreeArgs {
     int32_t D, k, branch, budget, N, W, wbits, per_word;
@@ -50,16 +32,17 @@ struct TreeArgs {
     int32_t* rank;
     float* score;
     uint64_t* anc;
-    bool rho_in_lds;
     int32_t beam_width;  // beam search only
-    // LDS byte offsets
-    int o_lp, o_ids, o_kord, o_krank, o_rec, o_pkey, o_ktab, o_beam, o_kbeam, o_rho;
-    // literal Alg. 2 only: T (capacity budget + branch - 1) in LDS
-    int o_tmeta, o_tS, o_tkey, o_tplace;
-    // frontier sweeps only: lambda, the sorted best set, the pending
-    // prefixes and the parent positions
-    int o_lam, o_sw_t, o_sw_p, o_sw_p2, o_sw_par, o_sw_cnt, o_sw_np;
     uint32_t mag_k, mag_k3;  // ceil(2^32 / k), ceil(2^32 / k^3) (k > 1): n / d = umulhi(n, mag) for n < 2^20
+    // LDS byte offsets: the tables of every kernel,
+    int o_lp, o_ids, o_rho;
+    // the level and beam kernels,
+    int o_lam, o_pool, o_key, o_hist, o_fine, o_list, o_place, o_row, o_par, o_misc;
+    int32_t cap;  // entries the pool holds, the root included
+    // one-node-at-a-time search (shares the pool's memory),
+    int o_kord, o_krank, o_rec, o_pkey;
+    // literal Alg. 2: T (capacity budget + branch - 1)
+    int o_tmeta, o_tS, o_tkey, o_tplace;
 };
 
 // Frontier metadata in one word: parent node (10 bits), candidate rank (4),
@@ -102,12 +85,6 @@ __device__ __forceinline__ uint64_t sort8_desc(uint64_t key, int lane) {
     key = bitonic_layer<0x4e, 1>(key, lane);   // i ^ 2
     key = bitonic_layer<0xb1, 0>(key, lane);   // i ^ 1
     return key;
-}
-
-// Same within this lane's quad (quad_perm rotations by 1, 2, 3).
-__device__ __forceinline__ int quad_count_greater(uint64_t key) {
-    return (dpp_u64<0x39>(0ull, key) > key ? 1 : 0) + (dpp_u64<0x4e>(0ull, key) > key ? 1 : 0) +
-           (dpp_u64<0x93>(0ull, key) > key ? 1 : 0);
 }
 
 // Loads up to U words per lane of src[base ..] (batches of 64 words while
@@ -161,252 +138,154 @@ struct SlotCount {
     static constexpr int value = A;
 };
 
-// One entry of a beam (beam search): score, candidate rank, rank of its
-// parent, and its place in rank-path order among the entries of its depth.
-struct BeamEntry {
-    float S;
-    int32_t rank, prank, path;
+// Token scores fl(log q + fl(lambda * log rho)), NaN -> -inf, of candidate r
+// at drafter row `row` in the trigram context (c2, c1) of candidate ranks.
+// RHO: 0 no lattice (s = log q), 1 scores of the whole lattice in LDS, 2
+// lattice read from global memory and scored on the fly.
+template <int RHO>
+struct TokenScores {
+    const float* s_lp;
+    const float* s_lam;
+    const float* s_rho;
+    const float* g_rho;
+    int k;
+    __device__ __forceinline__ TokenScores(const TreeArgs& a, const char* lds)
+        : s_lp(reinterpret_cast<const float*>(lds + a.o_lp)),
+          s_lam(reinterpret_cast<const float*>(lds + a.o_lam)),
+          s_rho(reinterpret_cast<const float*>(lds + a.o_rho)),
+          g_rho(RHO ? a.log_rho + (int64_t)blockIdx.x * a.D * a.k * a.k * a.k : nullptr),
+          k(a.k) {}
+    __device__ __forceinline__ float operator()(int row, int c2, int c1, int r) const {
+        if constexpr (RHO == 0) return s_lp[row * k + r];
+        const int i = ((row * k + c2) * k + c1) * k + r;
+        if constexpr (RHO == 1) return s_rho[i];
+        const float lr = g_rho[i];
+        const float t = s_lam[row] * lr;
+        const float v = s_lp[row * k + r] + t;
+        return (v == v) ? v : -INFINITY;
+    }
 };
 
-// RHO: 0 no lattice (s = log q), 1 lattice staged in LDS, 2 lattice read
-// from global memory.  KQ: k <= 4, children ranked within a quad.  BEAM:
-// beam search with global retention (Alg. 1): a level-by-level beam pass
-// fixes the retained set T, then the best-first pass below, restricted to
-// T, emits TopB(T) in the total order.
-template <int SL, int RHO, bool KQ, bool BEAM>
-__global__ __launch_bounds__(kWave) void tree_build_kernel(TreeArgs a) {
-    extern __shared__ __align__(16) char lds[];
+// Stages the candidate table and lambda of this workgroup's sequence and, with
+// the lattice in LDS, the token scores of every context in its place (so that
+// scoring a child is one read).  Every thread has up to U lattice words in
+// flight, the first batch requested before the barrier that publishes log q
+// and lambda; ends with a barrier.  (With one wave staging and a separate
+// scoring pass, a lattice of 16,000 words took about 45 k cycles; one thread
+// per word with 32 in flight about 23 k.)
+template <int NT, int RHO>
+__device__ __forceinline__ void stage_tables(const TreeArgs& a, char* lds) {
+    const int tid = threadIdx.x, lane = lane_id();
+    const int b = blockIdx.x, D = a.D, k = a.k;
+    float* s_lp = reinterpret_cast<float*>(lds + a.o_lp);
+    float* s_lam = reinterpret_cast<float*>(lds + a.o_lam);
+    float* s_rho = reinterpret_cast<float*>(lds + a.o_rho);
+    int32_t* s_ids = reinterpret_cast<int32_t*>(lds + a.o_ids);
+    const int64_t tb = (int64_t)b * D * k;
+    if (tid < kWave) {
+        uint32_t r_lp[8], r_ids[8];  // D * k <= 512 words
+        load_words(r_lp, reinterpret_cast<const uint32_t*>(a.logprob + tb), D * k, 0, lane);
+        load_words(r_ids, reinterpret_cast<const uint32_t*>(a.ids + tb), D * k, 0, lane);
+        const float lam = lane < D ? a.lambda[(int64_t)b * a.lambda_stride + lane] : 0.f;
+        store_words(reinterpret_cast<uint32_t*>(s_lp), r_lp, D * k, 0, lane);
+        store_words(reinterpret_cast<uint32_t*>(s_ids), r_ids, D * k, 0, lane);
+        if (lane < D) s_lam[lane] = lam;
+    }
+    if constexpr (RHO == 1) {
+        const int rho_n = D * k * k * k;
+        const uint32_t* gr = reinterpret_cast<const uint32_t*>(a.log_rho + (int64_t)b * rho_n);
+        auto stage = [&](auto uc) __attribute__((always_inline)) {
+            constexpr int U = decltype(uc)::value;
+            for (int base = 0; base < rho_n; base += U * NT) {
+                // words of this batch per thread that exist for some thread
+                const int nu = U > 8 ? U : min(U, (rho_n - base + NT - 1) / NT);
+                float x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = base + u * NT + tid;
+                    x[u] = (u < nu && i < rho_n) ? __uint_as_float(gr[i]) : 0.f;
+                }
+                if (base == 0) __syncthreads();
+                // every log q and lambda of the batch read before the first
+                // store (a store between them would order each read after it)
+                float lq[U], lm[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    lq[u] = lm[u] = 0.f;
+                    if (u < nu) {
+                        const int i = min(base + u * NT + tid, rho_n - 1);
+                        const int row = k == 1 ? i : (int)__umulhi((uint32_t)i, a.mag_k3);
+                        const int r = k == 1 ? 0 : i - (int)__umulhi((uint32_t)i, a.mag_k) * k;
+                        lq[u] = s_lp[row * k + r];
+                        lm[u] = s_lam[row];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = base + u * NT + tid;
+                    const float t = lm[u] * x[u];
+                    const float v = lq[u] + t;
+                    if (u < nu && i < rho_n) s_rho[i] = (v == v) ? v : -INFINITY;
+                }
+            }
+        };
+        if (rho_n <= 8 * NT)
+            stage(std::integral_constant<int, 8>{});
+        else
+            stage(std::integral_constant<int, 16>{});
+    } else {
+        __syncthreads();
+        if constexpr (RHO == 0) {
+            for (int i = tid; i < D * k; i += NT) {
+                const float v = s_lp[i];
+                s_lp[i] = (v == v) ? v : -INFINITY;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Best-first search one node at a time, by one wave: the path of inputs that
+// the level search below cannot bound (its pool overflows on very many equal
+// scores, or candidates of probability 0 have to fill the budget).  Per
+// committed node LDS holds one 8-byte record (parent, rank, depth, S) and its
+// children in commit order; the frontier lives in registers spread over the
+// 64 lanes (SL slots per lane), each slot only (S, packed metadata): a pop is
+// a per-lane max, one DPP wave max and a ballot.  The frontier holds, for
+// every committed node, only its next not-yet-committed child in commit
+// order: committing a node pushes its first child, committing a child pushes
+// its next sibling, so it never holds more than (committed + 1) entries.
+// Rank-path keys are only derived when several entries share the best S.
+// About 1300 cycles per pop; the tables were staged by the whole workgroup.
+template <int SL, int RHO>
+__device__ void tree_pop_search(const TreeArgs& a, char* lds) {
     const int lane = lane_id();
     const int b = blockIdx.x;
     const int D = a.D, k = a.k, N = a.N, W = a.W, wbits = a.wbits, per_word = a.per_word;
-    float* s_lp = reinterpret_cast<float*>(lds + a.o_lp);
-    int32_t* s_ids = reinterpret_cast<int32_t*>(lds + a.o_ids);
+    const TokenScores<RHO> scores(a, lds);
+    const int32_t* s_ids = reinterpret_cast<const int32_t*>(lds + a.o_ids);
     // children of every committed node in commit order: ord(S) (0 ends the
     // list) and candidate rank
     uint32_t* s_kord = reinterpret_cast<uint32_t*>(lds + a.o_kord);  // [N][k]
     uint8_t* s_krank = reinterpret_cast<uint8_t*>(lds + a.o_krank);  // [N][k]
     uint2* s_rec = reinterpret_cast<uint2*>(lds + a.o_rec);          // [N] (meta, S bits)
-    float* s_rho = reinterpret_cast<float*>(lds + a.o_rho);
-    const int rho_n = D * k * k * k;
-    const float* g_rho = RHO ? a.log_rho + (int64_t)b * rho_n : nullptr;
-
-    const float lam_lane =
-        lane < D ? a.lambda[(int64_t)b * a.lambda_stride + lane] : 0.f;  // lambda_d held by lane d
-    // stage the candidate table of this sequence (and the lattice when it
-    // fits): the table, lambda and the lattice's first 1024 words are all
-    // requested before the first store, so the common sizes cost one memory
-    // round trip
-    const int64_t tb = (int64_t)b * D * k;
-    {
-        const uint32_t* g_lp = reinterpret_cast<const uint32_t*>(a.logprob + tb);
-        const uint32_t* g_ids = reinterpret_cast<const uint32_t*>(a.ids + tb);
-        constexpr int UT = 8;  // D * k <= 512 words
-        uint32_t r_lp[UT], r_ids[UT], r_rho[16];
-        load_words(r_lp, g_lp, D * k, 0, lane);
-        load_words(r_ids, g_ids, D * k, 0, lane);
-        if constexpr (RHO == 1) load_words(r_rho, reinterpret_cast<const uint32_t*>(g_rho), rho_n, 0, lane);
-        store_words(reinterpret_cast<uint32_t*>(s_lp), r_lp, D * k, 0, lane);
-        store_words(reinterpret_cast<uint32_t*>(s_ids), r_ids, D * k, 0, lane);
-        if constexpr (RHO == 1) {
-            store_words(reinterpret_cast<uint32_t*>(s_rho), r_rho, rho_n, 0, lane);
-            if (rho_n > 16 * kWave)
-                stage_words(reinterpret_cast<uint32_t*>(s_rho) + 16 * kWave,
-                            reinterpret_cast<const uint32_t*>(g_rho) + 16 * kWave, rho_n - 16 * kWave,
-                            lane);
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-
-    // token score of candidate r at drafter row `row` under the trigram
-    // context (ctx2, ctx1): fl(log q + fl(lambda * log rho)), NaN -> -inf
-    auto token_score = [&](int row, int ctx2, int ctx1, int r) {
-        const float lam_d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lam_lane), row));
-        const float lq = s_lp[row * k + r];
-        float s = lq;
-        if constexpr (RHO != 0) {
-            const int ri = ((row * k + ctx2) * k + ctx1) * k + r;
-            float lr;
-            if constexpr (RHO == 1)
-                lr = s_rho[ri];
-            else
-                lr = g_rho[ri];
-            const float t = lam_d * lr;
-            s = lq + t;
-        }
-        return (s == s) ? s : -INFINITY;
-    };
-
-    // ---- beam pass (Alg. 1): per depth, every beam entry's top-`branch`
-    // children join T; the W best (total order) form the next beam.  The
-    // table ktab[d][beam entry of the parent][rank] records, for every node of
-    // depth d, whether it is in T (-1) and if so whether it is in the beam of
-    // its depth (its index there, >= 0); -2: not in T.
-    int8_t* s_ktab = reinterpret_cast<int8_t*>(lds + a.o_ktab);
-    BeamEntry* s_beam = reinterpret_cast<BeamEntry*>(lds + a.o_beam);  // [2][Wb]
-    // [N][k]: the table entry above of every child of a committed node, by
-    // candidate rank (written when the node is expanded)
-    int8_t* s_kbeam = reinterpret_cast<int8_t*>(lds + a.o_kbeam);
-    const int Wb = a.beam_width;
-    if constexpr (BEAM) {
-        const int tab = (D + 1) * Wb * k;
-        for (int i = lane; i < tab; i += kWave) s_ktab[i] = -2;
-        if (lane == 0) s_beam[0] = BeamEntry{0.f, 0, 0, 0};  // the root
-        __builtin_amdgcn_wave_barrier();
-        int nb = 1, cur = 0, nT = 0;
-        constexpr int CS = kBeamCandSlots;
-        // One depth: candidates c = q * 64 + lane of the nb beam entries
-        // (nb * k of them, in ceil(nb * k / 64) <= CS slots per lane: the
-        // per-slot work only covers the slots that hold candidates).
-        auto beam_depth = [&](auto act, int d) {
-            constexpr int A = decltype(act)::value;
-            const int row = d - 1;  // drafter row of depth d
-            const BeamEntry* bc = s_beam + cur * Wb;
-            uint64_t key[CS];
-            int cpb[CS], cr[CS];
-            int count = 0;
-#pragma unroll
-            for (int q = 0; q < A; ++q) {
-                const int ci = q * kWave + lane;
-                const bool valid = ci < nb * k;
-                const int pb = valid ? ci / k : 0, r = valid ? ci % k : 0;
-                const BeamEntry e = bc[pb];
-                const float sv = token_score(row, row >= 2 ? e.prank : 0, row >= 1 ? e.rank : 0, r);
-                bool in = valid;
-                if (a.branch < k) {
-                    // top-`branch` of the parent's k candidates by token score
-                    int sel = 0;
-                    for (int j = 0; j < k; ++j) {
-                        const float sj = token_score(row, row >= 2 ? e.prank : 0, row >= 1 ? e.rank : 0, j);
-                        sel += (sj > sv || (sj == sv && j < r)) ? 1 : 0;
-                    }
-                    in = in && sel < a.branch;
-                }
-                const float S = e.S + sv;
-                key[q] = in ? ((uint64_t)ord32(S) << 32) | (uint64_t)(0xffffffffu - (uint32_t)(e.path * 16 + r))
-                            : 0ull;
-                cpb[q] = pb;
-                cr[q] = r;
-                if (in) s_ktab[(d * Wb + pb) * k + r] = -1;
-                count += __popcll(__ballot(in));
-            }
-            nT += count;
-            // the W best candidates, in the total order (S desc, rank path asc)
-            const int nn = min(Wb, count);
-            BeamEntry mine{0.f, 0, 0, 0};
-            int mine_pb = 0;
-            int okey = 0;
-            if constexpr (A == 1) {
-                // at most 64 candidates: each takes its place among them by
-                // comparing every key once (keys are distinct, 0 = not in T);
-                // the nn best hand themselves to lanes 0 .. nn-1 through the
-                // next beam's LDS buffer (path holds the rank-path key there)
-                int rk = 0;
-                const int ncand = nb * k;
-                for (int c = 0; c < ncand; ++c) rk += readlane_u64(key[0], c) > key[0] ? 1 : 0;
-                if (key[0] != 0ull && rk < nn) {
-                    const BeamEntry pe = bc[cpb[0]];
-                    s_ktab[(d * Wb + cpb[0]) * k + cr[0]] = (int8_t)rk;
-                    s_beam[(cur ^ 1) * Wb + rk] =
-                        BeamEntry{unord32((uint32_t)(key[0] >> 32)), cr[0], pe.rank, pe.path * 16 + cr[0]};
-                }
-                __builtin_amdgcn_wave_barrier();
-                if (lane < nn) {
-                    mine = s_beam[(cur ^ 1) * Wb + lane];
-                    okey = mine.path;
-                }
-            }
-            for (int j = 0; A > 1 && j < nn; ++j) {
-                uint64_t lm = 0ull;
-#pragma unroll
-                for (int q = 0; q < A; ++q) lm = key[q] > lm ? key[q] : lm;
-                const uint64_t m = wave_max_u64_dpp(lm);
-                int wq = 0, wl = 0;
-#pragma unroll
-                for (int q = A - 1; q >= 0; --q) {
-                    const uint64_t hit = __ballot(key[q] == m);
-                    if (hit) {
-                        wq = q;
-                        wl = __ffsll((unsigned long long)hit) - 1;
-                    }
-                }
-                int lpb = 0, lr = 0;
-#pragma unroll
-                for (int q = 0; q < A; ++q) {
-                    lpb = q == wq ? cpb[q] : lpb;
-                    lr = q == wq ? cr[q] : lr;
-                }
-                const int pb = __builtin_amdgcn_readlane(lpb, wl);
-                const int r = __builtin_amdgcn_readlane(lr, wl);
-                if (lane == j) {
-                    mine = BeamEntry{unord32((uint32_t)(m >> 32)), r, bc[pb].rank, 0};
-                    mine_pb = pb;
-                }
-                if (lane == 0) s_ktab[(d * Wb + pb) * k + r] = (int8_t)j;
-#pragma unroll
-                for (int q = 0; q < A; ++q) key[q] = (q == wq && lane == wl) ? 0ull : key[q];
-            }
-            // place of each new entry in rank-path order: (parent's place, rank)
-            if constexpr (A > 1) okey = bc[mine_pb].path * 16 + mine.rank;
-            int place = 0;
-            for (int j = 0; j < nn; ++j) {
-                const int oj = __builtin_amdgcn_readlane(okey, j);
-                place += (oj < okey) ? 1 : 0;
-            }
-            mine.path = place;
-            __builtin_amdgcn_wave_barrier();
-            if (lane < nn) s_beam[(cur ^ 1) * Wb + lane] = mine;
-            __builtin_amdgcn_wave_barrier();
-            cur ^= 1;
-            nb = nn;
-        };
-        for (int d = 1; d <= D && nT < a.budget && nb > 0; ++d) {
-            const int slots = (nb * k + kWave - 1) / kWave;
-            if (slots <= 1) beam_depth(SlotCount<1>{}, d);
-            else if (slots <= 2) beam_depth(SlotCount<2>{}, d);
-            else beam_depth(SlotCount<CS>{}, d);
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
 
     // Children of node n (depth d, own rank rn, parent's rank rp, score Sn):
     // lane r < k scores candidate r, the children are ranked by (S desc,
-    // rank asc) with in-row rotations and stored in that order; returns the
-    // first child as (ord S, rank), ord 0 if none.  A node at the depth limit
-    // (d == D) has no children: nothing is stored and ord 0 is returned.
-    auto expand = [&](int n, int d, int rn, int rp, float Sn, int bidx, uint32_t& c_ord, int& c_rank) {
+    // rank asc) and stored in that order; returns the first child as (ord S,
+    // rank), ord 0 if none.  A node at the depth limit (d == D) has no
+    // children: nothing is stored and ord 0 is returned.
+    auto expand = [&](int n, int d, int rn, int rp, float Sn, uint32_t& c_ord, int& c_rank) {
         const bool live = d < D;
         const int dr = min(d, D - 1);      // drafter row read (clamped at the depth limit)
         const int ctx2 = d >= 2 ? rp : 0;  // grandparent slot of the trigram
         const int ctx1 = d >= 1 ? rn : 0;  // parent slot of the trigram
-        const float lam_d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lam_lane), dr));
         // every lane reads (lanes >= k at a clamped index) so that no branch
         // separates the reads from their use; only lanes < k are kept
-        const int rl = min(lane, k - 1);
-        float s;
-        {
-            const float lq = s_lp[dr * k + rl];
-            if constexpr (RHO != 0) {
-                const int ri = ((dr * k + ctx2) * k + ctx1) * k + rl;
-                float lr;
-                if constexpr (RHO == 1)
-                    lr = s_rho[ri];
-                else
-                    lr = g_rho[ri];
-                const float t = lam_d * lr;
-                s = lq + t;
-            } else {
-                s = lq;
-            }
-            s = (s == s && lane < k) ? s : -INFINITY;
-        }
+        float s = scores(dr, ctx2, ctx1, min(lane, k - 1));
+        s = lane < k ? s : -INFINITY;
         bool in = lane < k && live;
-        if constexpr (BEAM) {
-            // the children in T (the beam pass applied the branch filter);
-            // their table entries are kept for their own pops
-            const int tv = s_ktab[((d + 1) * Wb + bidx) * k + rl];
-            in = in && tv >= -1;
-            if (lane < k && live) s_kbeam[n * k + lane] = (int8_t)tv;
-        } else if (a.branch < k) {
+        if (a.branch < k) {
             // keep the top-`branch` by token score (larger s, then lower rank)
             int sel = 0;
             for (int j = 0; j < k; ++j) {
@@ -418,7 +297,7 @@ __global__ __launch_bounds__(kWave) void tree_build_kernel(TreeArgs a) {
         const float sc = Sn + s;
         const uint32_t o = ord32(sc);  // nonzero for every non-NaN score
         const uint64_t key = in ? (((uint64_t)o << 8) | (uint64_t)(255 - lane)) : 0ull;
-        if (!KQ && k <= 8) {
+        if (k <= 8) {
             // sorted in place: lane p holds the p-th child (key 0 past the
             // last child, which writes the end marker)
             const uint64_t sk = sort8_desc(key, lane);
@@ -430,13 +309,9 @@ __global__ __launch_bounds__(kWave) void tree_build_kernel(TreeArgs a) {
             c_ord = (uint32_t)(top >> 8);
             c_rank = c_ord ? 255 - (int)(top & 255) : 0;
         } else {
-            int pos;
-            if constexpr (KQ)
-                pos = quad_count_greater(key);
-            else
-                pos = row_count_greater<15>(key);
             // the lanes that are not children all land on the first free
             // position and write the end marker there
+            const int pos = row_count_greater<15>(key);
             if (lane < k && live) {
                 s_kord[n * k + pos] = in ? o : 0u;
                 s_krank[n * k + pos] = (uint8_t)lane;
@@ -470,7 +345,7 @@ __global__ __launch_bounds__(kWave) void tree_build_kernel(TreeArgs a) {
     if (lane == 0) s_rec[0] = make_uint2(0xffffffffu, __float_as_uint(0.f));
     uint32_t c_ord;
     int c_rank;
-    expand(0, 0, 0, 0, 0.f, 0, c_ord, c_rank);
+    expand(0, 0, 0, 0, 0.f, c_ord, c_rank);
 
     // frontier slots: slot j of lane l is entry j * 64 + l
     uint32_t fS[SL], fM[SL];
@@ -558,10 +433,6 @@ __global__ __launch_bounds__(kWave) void tree_build_kernel(TreeArgs a) {
         // commit node n: one record; everything else is derived after the search
         const int n = committed++;
         if (lane == 0) s_rec[n] = make_uint2(meta, __float_as_uint(S));
-        int bidx = 0;  // beam search: n's entry in the beam of its depth, or < 0
-        if constexpr (BEAM) {
-            bidx = s_kbeam[p * k + r];  // recorded when p was expanded
-        }
 
         // next sibling of n: the next entry of its parent's ordered children
         // (read unconditionally, at a clamped index, so that its latency
@@ -572,7 +443,7 @@ __global__ __launch_bounds__(kWave) void tree_build_kernel(TreeArgs a) {
         // first child of n
         uint32_t kid_ord = 0u;
         int kid_rank = 0;
-        if (!BEAM || (d < D && bidx >= 0)) expand(n, d, r, rp, S, bidx, kid_ord, kid_rank);
+        expand(n, d, r, rp, S, kid_ord, kid_rank);
         const uint32_t sib_ord = pos + 1 < k ? sib_raw : 0u;
 
         // pushes: the first reuses the popped slot, the second takes a fresh slot
@@ -673,6 +544,484 @@ __global__ __launch_bounds__(kWave) void tree_build_kernel(TreeArgs a) {
     if (lane == 0) a.n_nodes[b] = committed;
 }
 
+// ---------------------------------------------------------------------------
+// Level search and beam search: what the two kernels share.
+//
+// A workgroup collects prefixes level by level (depth by depth) in a pool in
+// LDS: per entry (S, parent entry | rank << 13 | parent's rank << 17 | depth
+// << 21) and the rank-path key.  Entry 0 is the root (S = 0, ranks 0: the
+// slots its children's contexts read), a level's entries are contiguous.
+// Afterwards finish_tree places the entries in the total order (S desc, rank
+// path asc, a prefix before its extensions) and writes the rows.
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kPoolMax = 8191;  // 13 bits of parent entry
+constexpr int kBins = 512;      // histogram of -S, see score_bin
+
+// Monotone bin of a score: 64 bins per octave of 1 - S, so a bin is 1/64 nat
+// wide near S = 0 and 1/8 nat near S = -10; everything below -255 is in the
+// last one.  score_bin(x) < score_bin(y) implies x > y.
+__device__ __forceinline__ uint32_t score_bin(float S) {
+    const uint32_t u = __float_as_uint(fmaxf(1.f - S, 1.f)) >> 17;
+    return min(u - (127u << 6), (uint32_t)(kBins - 1));
+}
+
+// Inclusive prefix sum over the wave (DPP, no LDS traffic).
+__device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t v) {
+    v += dpp_u32<0x111>(0u, v);        // row_shr:1
+    v += dpp_u32<0x112>(0u, v);        // row_shr:2
+    v += dpp_u32<0x114>(0u, v);        // row_shr:4
+    v += dpp_u32<0x118>(0u, v);        // row_shr:8
+    v += dpp_u32<0x142, 0xa>(0u, v);   // row_bcast:15
+    v += dpp_u32<0x143, 0xc>(0u, v);   // row_bcast:31
+    return v;
+}
+
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// The bin holding the `budget`-th best entry counted so far (kBins - 1 if
+// fewer are counted), and the number counted up to it.  Every wave computes
+// it for itself; a histogram that other waves are still adding to gives a
+// bin no better than the true one, since only entries that exist are counted.
+__device__ __forceinline__ uint32_t threshold_bin(const uint32_t* s_hist, uint32_t budget, uint32_t& counted) {
+    const uint4* h = reinterpret_cast<const uint4*>(s_hist) + 2 * lane_id();
+    const uint4 x = h[0], y = h[1];
+    const uint32_t v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    uint32_t sum = 0u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum += v[i];
+    const uint32_t incl = wave_scan_dpp(sum);
+    const uint64_t m = __ballot(incl >= budget);
+    if (m == 0ull) {
+        counted = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+        return kBins - 1;
+    }
+    uint32_t c = incl - sum, j = 0u;
+    uint32_t upto = c + v[0];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) {
+        c += v[i];
+        j += c < budget ? 1u : 0u;
+        upto = c < budget ? c + v[i + 1] : upto;
+    }
+    const int l = __ffsll((unsigned long long)m) - 1;
+    counted = (uint32_t)__builtin_amdgcn_readlane((int)upto, l);
+    return (uint32_t)__builtin_amdgcn_readlane((int)(8 * l + j), l);
+}
+
+template <int KW>
+struct PathKey;
+template <>
+struct PathKey<2> {
+    typedef u32x2 type;
+};
+template <>
+struct PathKey<4> {
+    typedef u32x4 type;
+};
+template <int KW>
+__device__ __forceinline__ bool key_less(typename PathKey<KW>::type x, typename PathKey<KW>::type y) {
+    const uint64_t xa = ((uint64_t)x[0] << 32) | (uint64_t)x[1], ya = ((uint64_t)y[0] << 32) | (uint64_t)y[1];
+    if constexpr (KW == 2) {
+        return xa < ya;
+    } else {
+        const uint64_t xb = ((uint64_t)x[2] << 32) | (uint64_t)x[3], yb = ((uint64_t)y[2] << 32) | (uint64_t)y[3];
+        return (xa < ya) | ((xa == ya) & (xb < yb));
+    }
+}
+
+// The pool and the scratch of finish_tree.  KW: words of a rank-path key
+// (most significant first; digit rank + 1 at the entry's depth).
+template <int KW>
+struct Pool {
+    typedef typename PathKey<KW>::type Key;
+    uint2* rec;       // [cap]
+    Key* key;         // [cap]
+    uint32_t* hist;   // [kBins] entries per score bin
+    uint32_t* fine;   // [fine bins + 1] counts, then offsets
+    uint16_t* list;   // [cap] entries in the order of the fine bins
+    uint16_t* place;  // [cap] place within the bin, then the entry's row
+    uint16_t* row;    // [N] entry of a row
+    uint16_t* par;    // [N] parent row
+    uint32_t* misc;   // [64]: level counts by depth (then wave sums), 63: a flag
+    __device__ __forceinline__ Pool(const TreeArgs& a, char* lds)
+        : rec(reinterpret_cast<uint2*>(lds + a.o_pool)), key(reinterpret_cast<Key*>(lds + a.o_key)),
+          hist(reinterpret_cast<uint32_t*>(lds + a.o_hist)), fine(reinterpret_cast<uint32_t*>(lds + a.o_fine)),
+          list(reinterpret_cast<uint16_t*>(lds + a.o_list)), place(reinterpret_cast<uint16_t*>(lds + a.o_place)),
+          row(reinterpret_cast<uint16_t*>(lds + a.o_row)), par(reinterpret_cast<uint16_t*>(lds + a.o_par)),
+          misc(reinterpret_cast<uint32_t*>(lds + a.o_misc)) {}
+    __device__ __forceinline__ float S(int e) const { return __uint_as_float(rec[e].x); }
+    static __device__ __forceinline__ uint32_t meta(int parent, int rank, int prank, int depth) {
+        return (uint32_t)parent | ((uint32_t)rank << 13) | ((uint32_t)prank << 17) | ((uint32_t)depth << 21);
+    }
+    // the key of a child of rank r, whose digit sits in word wi at shift sh
+    static __device__ __forceinline__ Key child_key(Key x, int wi, int sh, int r) {
+        const uint32_t v = (uint32_t)(r + 1) << sh;
+#pragma unroll
+        for (int w = 0; w < KW; ++w) x[w] |= w == wi ? v : 0u;
+        return x;
+    }
+};
+
+// fine bins of finish_tree's sort (a power of two, at least the workgroup's threads)
+template <int NT>
+constexpr int kFineBins = NT < 512 ? 512 : NT;
+
+template <int NT, int KW>
+__device__ __forceinline__ void init_pool(const TreeArgs& a, const Pool<KW>& P) {
+    const int tid = threadIdx.x;
+    for (int i = tid; i < kBins; i += NT) P.hist[i] = 0u;
+    for (int i = tid; i < kFineBins<NT>; i += NT) P.fine[i] = 0u;
+    if (tid < 64) P.misc[tid] = 0u;
+    if (tid == 0) {
+        P.rec[0] = make_uint2(__float_as_uint(0.f), 0u);
+        typename Pool<KW>::Key z;
+#pragma unroll
+        for (int w = 0; w < KW; ++w) z[w] = 0u;
+        P.key[0] = z;
+    }
+}
+
+// Places the pool's entries 1 .. n - 1 whose bin is at most the budget-th
+// best entry's and writes the tree: the `budget` best in the total order
+// (parents are among them: an entry never precedes its parent).  A counting
+// sort over fine bins of S, then each entry's place within its bin by
+// comparing it with the bin's few others; a handful of barriers, where
+// comparing all pairs of 1000 entries took about as long as the search.
+template <int NT, int KW>
+__device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const Pool<KW>& P, int n) {
+    constexpr int NF = kFineBins<NT>, PER = NF / NT > 0 ? NF / NT : 1;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int b = blockIdx.x, k = a.k, N = a.N, W = a.W;
+    const int budget = a.budget;
+    const int32_t* s_ids = reinterpret_cast<const int32_t*>(lds + a.o_ids);
+    uint32_t M;
+    const uint32_t J = threshold_bin(P.hist, budget, M);
+    // lower edge (in S) of the last bin that holds entries, below the
+    // catch-all bin: the fine bins cover 0 .. edge, quadratically spaced
+    // (scores crowd towards the threshold)
+    float inv;
+    {
+        const uint4* h = reinterpret_cast<const uint4*>(P.hist) + 2 * lane;
+        const uint4 x = h[0], y = h[1];
+        const uint32_t v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+        int last = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) last = (v[i] != 0u && 8 * lane + i <= (int)min(J, (uint32_t)kBins - 2)) ? 8 * lane + i : last;
+        last = (int)wave_max_u32_dpp((uint32_t)last);
+        inv = 1.f / (__uint_as_float((uint32_t)(last + 1 + (127 << 6)) << 17) - 1.f);
+    }
+    auto fine_bin = [&](float S) {
+        const float u = fminf(fmaxf(-S * inv, 0.f), 1.f);
+        return (int)fminf(u * u * (float)NF, (float)(NF - 1));
+    };
+    for (int e = 1 + tid; e < n; e += NT) {
+        const float S = P.S(e);
+        if (score_bin(S) <= J) P.place[e] = (uint16_t)atomicAdd(&P.fine[fine_bin(S)], 1u);
+    }
+    __syncthreads();
+    // counts -> offsets, PER consecutive bins per thread
+    {
+        uint32_t c[PER], sum = 0u;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            c[i] = P.fine[tid * PER + i];
+            sum += c[i];
+        }
+        const uint32_t incl = wave_scan_dpp(sum);
+        if (lane == kWave - 1) P.misc[wv] = incl;
+        __syncthreads();
+        uint32_t off = incl - sum;
+        for (int w = 0; w < wv; ++w) off += P.misc[w];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            P.fine[tid * PER + i] = off;
+            off += c[i];
+        }
+        if (tid == NT - 1) P.fine[NF] = off;
+    }
+    __syncthreads();
+    for (int e = 1 + tid; e < n; e += NT) {
+        const float S = P.S(e);
+        if (score_bin(S) <= J) P.list[P.fine[fine_bin(S)] + P.place[e]] = (uint16_t)e;
+    }
+    __syncthreads();
+    const int nt = min((int)M, budget);  // non-root rows
+    for (int t = tid; t < (int)M; t += NT) {
+        const int e = P.list[t];
+        const float S = P.S(e);
+        const int f = fine_bin(S);
+        const int q0 = (int)P.fine[f], q1 = (int)P.fine[f + 1];
+        int at = q0;
+        for (int q = q0; q < q1; ++q) {
+            const int o = P.list[q];
+            const float So = P.S(o);
+            bool before = So > S;
+            if (So == S && o != e) before = key_less<KW>(P.key[o], P.key[e]);
+            at += before ? 1 : 0;
+        }
+        P.place[e] = (uint16_t)(at + 1);
+        if (at < nt) P.row[at + 1] = (uint16_t)e;
+    }
+    if (tid == 0) P.place[0] = 0;
+    __syncthreads();
+    // rows
+    const int64_t ob = (int64_t)b * N;
+    const int root_tok = __builtin_amdgcn_readfirstlane(a.root_token[b]);
+    for (int i = tid; i < N; i += NT) {
+        int par = -1, tok = -1, dep = -1, rank = -1;
+        float S = -INFINITY;
+        if (i == 0) {
+            tok = root_tok;
+            dep = 0;
+            S = 0.f;
+        } else if (i <= nt) {
+            const uint2 r = P.rec[P.row[i]];
+            rank = (int)(r.y >> 13) & 15;
+            dep = (int)(r.y >> 21);
+            tok = s_ids[(dep - 1) * k + rank];
+            par = min((int)P.place[r.y & 8191u], i - 1);
+            S = __uint_as_float(r.x);
+            P.par[i] = (uint16_t)par;
+        }
+        a.parent[ob + i] = par;
+        a.token[ob + i] = tok;
+        a.depth[ob + i] = dep;
+        a.rank[ob + i] = rank;
+        a.score[ob + i] = S;
+    }
+    __syncthreads();
+    // ancestor masks: the parent chain downwards in row index, one 64-bit
+    // word at a time
+    for (int i = tid; i < N; i += NT) {
+        int y = i <= nt ? i : -1;
+        for (int q = W - 1; q >= 0; --q) {
+            uint64_t w = 0ull;
+            while (y >= q * 64) {
+                w |= 1ull << (y & 63);
+                y = y == 0 ? -1 : (int)P.par[y];
+            }
+            a.anc[(ob + i) * W + q] = w;
+        }
+    }
+    if (tid == 0) a.n_nodes[b] = nt + 1;
+}
+
+// Best-first tree, level by level.
+//
+// Every token score is <= 0, so S never increases along a path and an
+// ancestor precedes its descendants in the total order: the nodes that
+// best-first search commits, in pop order, are the `budget` best non-root
+// prefixes in that order (the closed form of Sec. 4.2), sorted.  The kernel
+// collects that set: level d's candidates are the children of level d - 1's
+// entries, one thread per candidate, and a candidate enters the pool unless
+// `budget` better entries are known, which a histogram of the scores tells
+// (threshold_bin: entries in bins past the one holding the budget-th best
+// cannot be in the tree, nor can their descendants).  A level with more
+// candidates than threads is counted first and entered afterwards, so that
+// its own scores already bound it.  The search ends when a level enters
+// nothing: the trees are wide and shallow (6 to 15 levels at depths 16 to 32,
+// 1.2 to 4 entries per budgeted node on peaked, flat and Gaussian drafters),
+// and finish_tree sorts what remains at or above the threshold.  One barrier
+// per level, two where it is counted first.
+//
+// Latency bounds it: a level is a chain of LDS round trips (count, record,
+// score, place, record) of about 1000 cycles, on one workgroup per sequence.
+// Measured per call, against merging a sorted set of the best prefixes sweep
+// by sweep (budgets 33 - 512) or popping one node at a time (others): budget
+// 64, k = 4: 29.8 -> 11.1 us; 32 sequences of budget 128, depth 32: 33.2 ->
+// 14.8; budget 256, k = 8: 89.4 -> 16.4.
+// Two kinds of input go to the one-node-at-a-time search instead: more equal
+// scores at the threshold than the pool holds, and trees that only candidates
+// of S = -inf can fill (the level search leaves those out, since all their
+// descendants tie with them).
+template <int NT, int SL, int RHO, int KW>
+__global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
+    extern __shared__ __align__(16) char lds[];
+    const int tid = threadIdx.x, lane = lane_id();
+    const int D = a.D, k = a.k;
+    const Pool<KW> P(a, lds);
+    typedef typename Pool<KW>::Key Key;
+    init_pool<NT, KW>(a, P);
+    stage_tables<NT, RHO>(a, lds);
+    const TokenScores<RHO> scores(a, lds);
+
+    int lo = 0, hi = 1;         // entries of the level above
+    uint32_t J = kBins - 1;     // candidates in later bins are dropped
+    bool below = false;         // a candidate of S = -inf was left out
+    for (int d = 1; d <= D; ++d) {
+        const int total = (hi - lo) * k;
+        const int wi = (d - 1) / a.per_word, sh = 32 - ((d - 1) % a.per_word + 1) * a.wbits;
+        // candidate i of the level: entry p's child of rank r
+        auto score = [&](int i, int& p, int& r, uint2& rec, uint32_t& bin) __attribute__((always_inline)) {
+            const int q = k == 1 ? i : (int)__umulhi((uint32_t)i, a.mag_k);
+            r = i - q * k;
+            p = lo + q;
+            rec = P.rec[p];
+            const int rank = (int)(rec.y >> 13) & 15, prank = (int)(rec.y >> 17) & 15;
+            const float s = scores(d - 1, prank, rank, r);
+            bool in = true;
+            if (a.branch < k) {
+                // the top-`branch` by token score (larger s, then lower rank)
+                int sel = 0;
+                for (int j = 0; j < k; ++j) {
+                    const float sj = scores(d - 1, prank, rank, j);
+                    sel += ((sj > s) | ((sj == s) & (j < r))) ? 1 : 0;
+                }
+                in = sel < a.branch;
+            }
+            const float S = __uint_as_float(rec.x) + s;
+            below |= in & (S == -INFINITY);
+            rec.x = __float_as_uint(S);
+            bin = score_bin(S);
+            return in & (S > -INFINITY) & (bin <= J);
+        };
+        const bool counted = total > NT;
+        uint32_t known;
+        if (counted) {
+            for (int i = tid; i < total; i += NT) {
+                int p, r;
+                uint2 rec;
+                uint32_t bin;
+                if (score(i, p, r, rec, bin)) atomicAdd(&P.hist[bin], 1u);
+            }
+            __syncthreads();
+            J = threshold_bin(P.hist, a.budget, known);
+        }
+        for (int i0 = 0; i0 < total; i0 += NT) {
+            int p = 0, r = 0;
+            uint2 rec = make_uint2(0u, 0u);
+            uint32_t bin = 0u;
+            bool in = false;
+            if (i0 + tid < total) in = score(i0 + tid, p, r, rec, bin);
+            const uint64_t m = __ballot(in);
+            if (m != 0ull) {
+                uint32_t at = 0u;
+                if (lane == 0) at = atomicAdd(&P.misc[d], (uint32_t)__popcll(m));
+                at = hi + (uint32_t)__builtin_amdgcn_readlane((int)at, 0) + lanes_below(m);
+                if (in & (at < (uint32_t)a.cap)) {
+                    const Key pk = P.key[p];
+                    P.rec[at] = make_uint2(rec.x, Pool<KW>::meta(p, r, (int)(rec.y >> 13) & 15, d));
+                    P.key[at] = Pool<KW>::child_key(pk, wi, sh, r);
+                    if (!counted) atomicAdd(&P.hist[bin], 1u);
+                }
+            }
+        }
+        __syncthreads();
+        const int entered = (int)P.misc[d];
+        lo = hi;
+        hi += entered;
+        if ((entered == 0) | (hi > a.cap)) break;
+        if (!counted && hi > a.budget) J = threshold_bin(P.hist, a.budget, known);
+    }
+    // the whole workgroup agrees on the search's outcome (the counts are
+    // shared; a wave's J may differ, finish_tree takes it anew)
+    bool redo = hi > a.cap;
+    if (!redo && hi - 1 < a.budget) {
+        if (below) P.misc[63] = 1u;
+        __syncthreads();
+        redo = P.misc[63] != 0u;
+    }
+    if (redo) {
+        if (tid < kWave) tree_pop_search<SL, RHO>(a, lds);
+        return;
+    }
+    finish_tree<NT, KW>(a, lds, P, hi);
+}
+
+// Beam search with global retention (Alg. 1): per depth, every beam entry's
+// top-`branch` children join T, and the `beam_width` best of them (S desc,
+// rank path asc) form the next beam; depths are taken while T holds fewer
+// than `budget` nodes.  T never exceeds budget - 1 + beam_width * k entries, so it
+// is kept whole, and the tree is its `budget` best (finish_tree).
+//
+// One thread per candidate (beam_width * k <= 256).  The beam is kept in
+// rank-path order, so a candidate's index orders it by path among its depth:
+// its place comes from comparing (ord S, index) keys with every candidate's,
+// and the chosen ones keep their order by a prefix count.  Three barriers per
+// depth.  k = 10, width 10, budget 512: 27.8 us per call, where a best-first
+// search restricted to T, one node at a time (about 1300 cycles each), took
+// 367.
+constexpr int kBeamThreads = 256;
+template <int RHO, int KW>
+__global__ __launch_bounds__(kBeamThreads) void tree_beam_kernel(TreeArgs a) {
+    constexpr int NT = kBeamThreads;
+    extern __shared__ __align__(16) char lds[];
+    __shared__ __align__(16) uint64_t s_keys[NT];
+    __shared__ uint16_t s_beam[2][64];  // pool entries of the beam, in rank-path order
+    __shared__ uint32_t s_wave[NT / kWave];
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int D = a.D, k = a.k, width = a.beam_width;
+    const Pool<KW> P(a, lds);
+    init_pool<NT, KW>(a, P);
+    if (tid == 0) s_beam[0][0] = 0;
+    stage_tables<NT, RHO>(a, lds);
+    const TokenScores<RHO> scores(a, lds);
+
+    int nb = 1, n = 1, cur = 0;
+    for (int d = 1; d <= D && n - 1 < a.budget && nb > 0; ++d) {
+        const int total = nb * k;
+        const int wi = (d - 1) / a.per_word, sh = 32 - ((d - 1) % a.per_word + 1) * a.wbits;
+        bool in = tid < total;
+        const int pb = k == 1 ? tid : (int)__umulhi((uint32_t)tid, a.mag_k), r = tid - pb * k;
+        int p = 0, rank = 0;
+        float S = 0.f;
+        if (in) {
+            p = s_beam[cur][pb];
+            const uint2 rec = P.rec[p];
+            rank = (int)(rec.y >> 13) & 15;
+            const int prank = (int)(rec.y >> 17) & 15;
+            const float s = scores(d - 1, prank, rank, r);
+            if (a.branch < k) {
+                int sel = 0;
+                for (int j = 0; j < k; ++j) {
+                    const float sj = scores(d - 1, prank, rank, j);
+                    sel += ((sj > s) | ((sj == s) & (j < r))) ? 1 : 0;
+                }
+                in = sel < a.branch;
+            }
+            S = __uint_as_float(rec.x) + s;
+        }
+        // larger S first, then the lower index; 0: no candidate
+        const uint64_t key = in ? ((uint64_t)ord32(S) << 32) | (uint64_t)(0xffffffffu - (uint32_t)tid) : 0ull;
+        s_keys[tid] = key;
+        __syncthreads();
+        int before = 0;
+        const ulonglong2* kv = reinterpret_cast<const ulonglong2*>(s_keys);
+        for (int j = 0; j < (total + 1) / 2; ++j) {
+            const ulonglong2 x = kv[j];
+            before += (x.x > key ? 1 : 0) + (x.y > key ? 1 : 0);
+        }
+        const bool sel = in & (before < width);
+        const uint64_t mi = __ballot(in), ms = __ballot(sel);
+        if (lane == 0) s_wave[wv] = (uint32_t)__popcll(mi) | ((uint32_t)__popcll(ms) << 16);
+        __syncthreads();
+        uint32_t off = 0u, all = 0u;
+#pragma unroll
+        for (int w = 0; w < NT / kWave; ++w) {
+            const uint32_t c = s_wave[w];
+            off += w < wv ? c : 0u;
+            all += c;
+        }
+        const int at = n + (int)(off & 0xffffu) + lanes_below(mi);
+        if (in & (at < a.cap)) {
+            P.rec[at] = make_uint2(__float_as_uint(S), Pool<KW>::meta(p, r, rank, d));
+            P.key[at] = Pool<KW>::child_key(P.key[p], wi, sh, r);
+            atomicAdd(&P.hist[score_bin(S)], 1u);
+            if (sel) s_beam[cur ^ 1][(int)(off >> 16) + lanes_below(ms)] = (uint16_t)at;
+        }
+        n += (int)(all & 0xffffu);
+        nb = (int)(all >> 16);
+        cur ^= 1;
+        __syncthreads();
+    }
+    finish_tree<NT, KW>(a, lds, P, min(n, a.cap));
+}
 
 // Literal Alg. 2 (Sec. 4.2): T grows by whole expansions.  The root is
 // expanded first; every later pop takes the best node of T not yet expanded
@@ -921,672 +1270,6 @@ __global__ __launch_bounds__(kWave) void tree_alg2_kernel(TreeArgs a) {
     }
     if (lane == 0) a.n_nodes[b] = keep + 1;
 }
-
-// ---------------------------------------------------------------------------
-// Best-first tree by frontier sweeps.
-//
-// Every token score is <= 0, so S never increases along a path and an
-// ancestor precedes its descendants in the total order (S desc, rank path
-// asc): the nodes that best-first search commits, in pop order, are the
-// `budget` best non-root prefixes in that order (the closed form of Sec.
-// 4.2), sorted.  This kernel finds that set without popping one node at a
-// time.  One workgroup per sequence keeps in LDS
-//   T: the best (at most budget) prefixes materialised so far, sorted;
-//   P: pending prefixes, each the next sibling (in child order: S desc,
-//      rank asc, among the top-`branch` candidates) or a member of the
-//      first-child chain (below) of a prefix that entered T, not
-//      materialised yet.
-// A sweep merges all of P into T (every entry's new place from counting
-// comparisons; entries pushed past the budget are dropped for good, since
-// T's last entry only ever improves) and then, for every prefix of P that
-// entered T, pushes its next sibling and, if it ends a chain, the chain of
-// its first child, that child's first child, ... (CL levels; only a chain's
-// last member pushes the next chain), keeping a push while T is not full or
-// when it precedes T's last entry.  A prefix of the optimal tree is always
-// pushed (its parent, or its previous sibling, or the head of its chain
-// precedes it and so enters T when materialised) and never dropped (it
-// precedes every last entry T ever has), so T is the optimal tree once
-// nothing is pending.  A prefix is pushed at most once, and a sweep pushes
-// at most CL + 1 prefixes per entry that entered T, so P never holds more
-// than (CL + 1) budget.  The number of sweeps follows the depth of the tree
-// and the chain length, not the budget (at depth 16 and budget 64: about 15
-// with CL = 1, 6 with CL = 3).
-//
-// Every record carries its full rank-path key, its parent's S and the ranks
-// of its trigram context, so that a push reads no other record; a node's
-// parent is found after the search by a binary search of T for the
-// parent's (S, key).
-
-// A record: ord(S), rank-path key (k0 most significant), ord(S) of the
-// parent, and rank | depth << 4 | parent's rank << 10 | grandparent's rank
-// << 14 | chain end << 18.  In LDS two 16-byte words: (o, k0, k1, k2),
-// (k3, po, meta, 0).
-struct SwRec {
-    uint32_t o, k0, k1, k2, k3, po, meta;
-};
-
-__device__ __forceinline__ SwRec sw_load(const uint4* base, int i) {
-    const uint4 x = base[2 * i], y = base[2 * i + 1];
-    return SwRec{x.x, x.y, x.z, x.w, y.x, y.y, y.z};
-}
-__device__ __forceinline__ void sw_store(uint4* base, int i, const SwRec& r) {
-    base[2 * i] = make_uint4(r.o, r.k0, r.k1, r.k2);
-    base[2 * i + 1] = make_uint4(r.k3, r.po, r.meta, 0u);
-}
-// The rank-path key of x is smaller than that of y.  Written with bitwise
-// operators throughout: short-circuit forms compile to divergent branches.
-__device__ __forceinline__ bool sw_key_less(const SwRec& x, const SwRec& y) {
-    const uint64_t xa = ((uint64_t)x.k0 << 32) | (uint64_t)x.k1;
-    const uint64_t ya = ((uint64_t)y.k0 << 32) | (uint64_t)y.k1;
-    const uint64_t xb = ((uint64_t)x.k2 << 32) | (uint64_t)x.k3;
-    const uint64_t yb = ((uint64_t)y.k2 << 32) | (uint64_t)y.k3;
-    return (xa < ya) | ((xa == ya) & (xb < yb));
-}
-// x precedes y in the total order (keys of distinct prefixes differ)
-__device__ __forceinline__ bool sw_before(const SwRec& x, const SwRec& y) {
-    return (x.o > y.o) | ((x.o == y.o) & sw_key_less(x, y));
-}
-__device__ __forceinline__ SwRec sw_readlane(const SwRec& r, int l) {
-    SwRec y;
-    y.o = (uint32_t)__builtin_amdgcn_readlane((int)r.o, l);
-    y.k0 = (uint32_t)__builtin_amdgcn_readlane((int)r.k0, l);
-    y.k1 = (uint32_t)__builtin_amdgcn_readlane((int)r.k1, l);
-    y.k2 = (uint32_t)__builtin_amdgcn_readlane((int)r.k2, l);
-    y.k3 = (uint32_t)__builtin_amdgcn_readlane((int)r.k3, l);
-    y.po = 0u;
-    y.meta = 0u;
-    return y;
-}
-__device__ __forceinline__ int lanes_below(uint64_t m) {
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-constexpr int kSweepWaves = 4;  // one wave per SIMD
-// An entry that enters T pushes its next sibling and, when it ends a chain,
-// the chain of its first child, that child's first child, ... CL levels
-// deep; only the last of a chain pushes the next chain (every prefix is
-// still pushed once: a first child by its parent's chain).  A chain advances
-// a path of first children CL levels per sweep: at budget 64 and depth 16
-// the sweeps drop from about 15 to 8 with CL = 2 and to 6 with CL = 3.
-constexpr uint32_t kChainEnd = 1u << 18;  // record meta: this entry pushes the next chain
-
-// MT: slots per lane of T (budget <= 64 MT), MP: slots per lane of P
-// ((CL + 1) budget <= 64 MP), KM: k <= KM, RHO as in tree_build_kernel, CL:
-// chain length.
-//
-// One workgroup of four waves per sequence.  Every wave holds all of T and
-// P in registers (from 8 slots of T on, only P's ord S: its records stay in
-// LDS, in two buffers, one read and one written by a sweep); the merge's comparisons are split over the waves (each
-// takes every fourth P entry in turn and its partial counts are summed
-// through LDS); the push candidates are scored before the merge, split into
-// tasks (first children, next siblings) per slot of P, and each task
-// reserves its places in the next P with one LDS atomic.  A sweep has two
-// barriers: after the partial counts, and after the stores and pushes.
-template <int MT, int MP, int KM, int RHO, int CL>
-__global__ __launch_bounds__(kSweepWaves * kWave) void tree_sweep_kernel(TreeArgs a) {
-    constexpr int NWV = kSweepWaves, NT = NWV * kWave;
-    extern __shared__ __align__(16) char lds[];
-    const int tid = threadIdx.x, lane = lane_id();
-    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int b = blockIdx.x;
-    const int D = a.D, k = a.k, N = a.N, W = a.W, wbits = a.wbits, per_word = a.per_word;
-    const int NB = N - 1;             // non-root nodes of a full tree
-    const int cap_p = (CL + 1) * NB;  // P's capacity
-    float* s_lp = reinterpret_cast<float*>(lds + a.o_lp);
-    int32_t* s_ids = reinterpret_cast<int32_t*>(lds + a.o_ids);
-    float* s_lam = reinterpret_cast<float*>(lds + a.o_lam);
-    uint4* s_t = reinterpret_cast<uint4*>(lds + a.o_sw_t);          // [NB] records, sorted
-    constexpr bool PL = MT >= 8;  // P's records in LDS only
-    uint4* s_pc = reinterpret_cast<uint4*>(lds + a.o_sw_p);         // [cap_p] records: P of this sweep
-    uint4* s_pn = PL ? reinterpret_cast<uint4*>(lds + a.o_sw_p2) : s_pc;  // the pushes
-    int32_t* s_par = reinterpret_cast<int32_t*>(lds + a.o_sw_par);  // [N] parent of node i
-    int32_t* s_cnt = reinterpret_cast<int32_t*>(lds + a.o_sw_cnt);  // [NWV][MT + MP][64] partial counts
-    int32_t* s_np = reinterpret_cast<int32_t*>(lds + a.o_sw_np);    // [2] pending counts, alternating
-    float* s_rho = reinterpret_cast<float*>(lds + a.o_rho);
-    const int rho_n = D * k * k * k;
-    const float* g_rho = RHO ? a.log_rho + (int64_t)b * rho_n : nullptr;
-
-    const int64_t tb = (int64_t)b * D * k;
-    if (wv == 0) {
-        uint32_t r_lp[8], r_ids[8];  // D * k <= 512 words
-        load_words(r_lp, reinterpret_cast<const uint32_t*>(a.logprob + tb), D * k, 0, lane);
-        load_words(r_ids, reinterpret_cast<const uint32_t*>(a.ids + tb), D * k, 0, lane);
-        const float lam = lane < D ? a.lambda[(int64_t)b * a.lambda_stride + lane] : 0.f;
-        store_words(reinterpret_cast<uint32_t*>(s_lp), r_lp, D * k, 0, lane);
-        store_words(reinterpret_cast<uint32_t*>(s_ids), r_ids, D * k, 0, lane);
-        if (lane < D) s_lam[lane] = lam;
-    }
-    // Token scores fl(log q + fl(lambda * log rho)), NaN -> -inf, computed
-    // once per trigram context in place of the lattice (or of the log q
-    // table without one), so that scoring a node's children reads k values.
-    // Every thread stages the lattice with up to 32 words in flight, the
-    // first batch requested before the barrier that publishes log q and
-    // lambda.  A lattice of at most 8 words per thread takes a copy of the
-    // loop unrolled 8 times (its cold instruction fetch is part of every
-    // launch).  A lattice read from global memory is scored on the fly.
-    if constexpr (RHO == 1) {
-        const uint32_t* gr = reinterpret_cast<const uint32_t*>(g_rho);
-        auto stage = [&](auto uc) __attribute__((always_inline)) {
-            constexpr int U = decltype(uc)::value;
-            for (int base = 0; base < rho_n; base += U * NT) {
-                // words of this batch per thread that exist for some thread
-                // (bounded in the small copy only: in the large one the
-                // bound's branches would split the batch's requests)
-                const int nu = U > 8 ? U : min(U, (rho_n - base + NT - 1) / NT);
-                float x[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = base + u * NT + tid;
-                    x[u] = (u < nu && i < rho_n) ? __uint_as_float(gr[i]) : 0.f;
-                }
-                if (base == 0) __syncthreads();
-                // every log q and lambda of the batch read before the first
-                // store (a store between them would order each read after it)
-                float lq[U], lm[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    lq[u] = lm[u] = 0.f;
-                    if (u < nu) {
-                        const int i = min(base + u * NT + tid, rho_n - 1);
-                        const int row = k == 1 ? i : (int)__umulhi((uint32_t)i, a.mag_k3);
-                        const int r = k == 1 ? 0 : i - (int)__umulhi((uint32_t)i, a.mag_k) * k;
-                        lq[u] = s_lp[row * k + r];
-                        lm[u] = s_lam[row];
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = base + u * NT + tid;
-                    const float t = lm[u] * x[u];
-                    const float v = lq[u] + t;
-                    if (u < nu && i < rho_n) s_rho[i] = (v == v) ? v : -INFINITY;
-                }
-            }
-        };
-        if (rho_n <= 8 * NT)
-            stage(std::integral_constant<int, 8>{});
-        else
-            stage(std::integral_constant<int, 32>{});
-    } else {
-        __syncthreads();
-        if constexpr (RHO == 0) {
-            for (int i = tid; i < D * k; i += NT) {
-                const float v = s_lp[i];
-                s_lp[i] = (v == v) ? v : -INFINITY;
-            }
-        }
-    }
-    __syncthreads();
-
-    const uint32_t pw_magic = (65536u + per_word - 1) / per_word;  // t / per_word = t * magic >> 16 (t < 128)
-    // the key with the digit of depth d set to rank r + 1 (cleared first)
-    auto with_digit = [&](SwRec x, int d, int r) {
-        const uint32_t t = (uint32_t)(d - 1);
-        const uint32_t wi = (t * pw_magic) >> 16;
-        const uint32_t sh = 32u - (t - wi * (uint32_t)per_word + 1u) * (uint32_t)wbits;
-        const uint32_t m = ((1u << wbits) - 1u) << sh;
-        const uint32_t v = (uint32_t)(r + 1) << sh;
-        x.k0 = wi == 0 ? (x.k0 & ~m) | v : x.k0;
-        x.k1 = wi == 1 ? (x.k1 & ~m) | v : x.k1;
-        x.k2 = wi == 2 ? (x.k2 & ~m) | v : x.k2;
-        x.k3 = wi == 3 ? (x.k3 & ~m) | v : x.k3;
-        return x;
-    };
-
-    // The best child, in child order, of a node with score Sn whose children
-    // sit at drafter row `row` in trigram context (c2, c1): with `first`,
-    // the first child; otherwise the first one after the child (ao, ar) (its
-    // ord S and rank).  The top-`branch` by (token score desc, rank asc) are
-    // children.  Returns ord S of the child, 0 if there is none.
-    auto child = [&](int row, int c2, int c1, float Sn, bool first, uint32_t ao, int ar, int& r_out,
-                     float& S_out) -> uint32_t {
-        float s[KM];
-        if constexpr (RHO == 2) {
-            const float lam = s_lam[row];
-#pragma unroll
-            for (int r = 0; r < KM; ++r) {
-                const int rr = r < k ? r : k - 1;
-                const float lq = s_lp[row * k + rr];
-                const float lr = g_rho[((row * k + c2) * k + c1) * k + rr];
-                const float t = lam * lr;
-                const float v = lq + t;
-                s[r] = (v == v) ? v : -INFINITY;
-            }
-        } else {
-            const float* sc = RHO == 1 ? s_rho + ((row * k + c2) * k + c1) * k : s_lp + row * k;
-            if (KM == 4 && k == 4) {
-                const float4 v = *reinterpret_cast<const float4*>(sc);  // 16-byte aligned: offsets are multiples of 4 words
-                s[0] = v.x;
-                s[1] = v.y;
-                s[2] = v.z;
-                s[3] = v.w;
-            } else {
-#pragma unroll
-                for (int r = 0; r < KM; ++r) s[r] = sc[r < k ? r : k - 1];
-            }
-        }
-        // candidates kept by the branch filter (a mask), then one key per
-        // candidate, (ord S, 255 - rank), and a maximum over them as a tree
-        uint32_t selm = k >= 32 ? ~0u : (1u << k) - 1u;
-        if (a.branch < k) {
-            selm = 0u;
-#pragma unroll
-            for (int r = 0; r < KM; ++r) {
-                int c = 0;
-#pragma unroll
-                for (int j = 0; j < KM; ++j)
-                    c += ((j < k) & ((s[j] > s[r]) | ((s[j] == s[r]) & (j < r)))) ? 1 : 0;
-                selm |= ((r < k) & (c < a.branch)) ? 1u << r : 0u;
-            }
-        }
-        uint64_t key[KM];
-#pragma unroll
-        for (int r = 0; r < KM; ++r) {
-            const float Sc = Sn + s[r];
-            const uint32_t oc = ord32(Sc);
-            const bool after = first | (oc < ao) | ((oc == ao) & (r > ar));
-            key[r] = (((selm >> r) & 1u) & after) ? ((uint64_t)oc << 8) | (uint64_t)(255 - r) : 0ull;
-        }
-#pragma unroll
-        for (int w = 1; w < KM; w *= 2)
-#pragma unroll
-            for (int r = 0; r + w < KM; r += 2 * w) key[r] = key[r + w] > key[r] ? key[r + w] : key[r];
-        const uint32_t bo = (uint32_t)(key[0] >> 8);
-        r_out = 255 - (int)(key[0] & 255u);
-        S_out = unord32(bo);  // S is never -0.0 or NaN here, so this is the sum itself
-        return bo;
-    };
-
-    // the first child of a record w (chain end flag `end`), or of the root
-    auto first_child = [&](const SwRec& w, bool root, bool end, SwRec& c) -> bool {
-        const int d = root ? 0 : (int)(w.meta >> 4) & 63, r = (int)(w.meta & 15);
-        const int rp = (int)(w.meta >> 10) & 15;
-        const int drow = min(max(d, 0), D - 1);  // clamped for lanes without a valid entry
-        int cr;
-        float cS;
-        const uint32_t co = child(drow, d >= 2 ? rp : 0, d >= 1 ? r : 0, root ? 0.f : unord32(w.o), true, 0u,
-                                  0, cr, cS);
-        c = SwRec{co, root ? 0u : w.k0, root ? 0u : w.k1, root ? 0u : w.k2, root ? 0u : w.k3,
-                  root ? ord32(0.f) : w.o,
-                  (uint32_t)cr | ((uint32_t)(d + 1) << 4) | ((uint32_t)r << 10) | ((uint32_t)rp << 14) |
-                      (end ? kChainEnd : 0u)};
-        c = with_digit(c, min(d + 1, D), cr);
-        return (d < D) & (co != 0u);
-    };
-
-    // P starts as the root's first chain
-    if (tid == 0) {
-        SwRec par{0u, 0u, 0u, 0u, 0u, 0u, 0u};
-        int n = 0;
-        for (int i = 0; i < CL; ++i) {
-            SwRec c;
-            if (!first_child(par, i == 0, i == CL - 1, c)) break;
-            sw_store(s_pc, n++, c);
-            par = c;
-        }
-        s_np[0] = n;
-        s_np[1] = 0;
-    }
-    __syncthreads();
-
-    int nt = 0, cur = 0;
-    int np = min(s_np[0], cap_p);
-    while (np > 0) {
-        // P in slots (entry u * 64 + lane), T likewise (position v * 64 + lane)
-        SwRec pr[PL ? 1 : MP], tr[MT];  // P's records (register mode)
-        uint32_t pS[MP];                // P's ord S
-        bool pv[MP], tv[MT];
-#pragma unroll
-        for (int u = 0; u < MP; ++u) {
-            pv[u] = u * kWave + lane < np;
-            pS[u] = 0u;
-            if constexpr (PL) {
-                if (u * kWave < np) pS[u] = reinterpret_cast<const uint32_t*>(s_pc)[8 * min(u * kWave + lane, np - 1)];
-            } else {
-                pr[u] = SwRec{0u, 0u, 0u, 0u, 0u, 0u, 0u};
-                if (u * kWave < np) pr[u] = sw_load(s_pc, min(u * kWave + lane, np - 1));
-                pS[u] = pr[u].o;
-            }
-        }
-        // P entry u * 64 + lane as a whole record (from LDS when only its
-        // ord S is held)
-        auto prec = [&](int u) __attribute__((always_inline)) {
-            if constexpr (PL) return sw_load(s_pc, min(u * kWave + lane, np - 1));
-            else return pr[u];
-        };
-        auto prec_at = [&](int u, int l) __attribute__((always_inline)) {
-            if constexpr (PL) return sw_load(s_pc, u * kWave + l);
-            else return sw_readlane(pr[u], l);
-        };
-#pragma unroll
-        for (int v = 0; v < MT; ++v) {
-            tv[v] = v * kWave + lane < nt;
-            tr[v] = SwRec{0u, 0u, 0u, 0u, 0u, 0u, 0u};
-            if (v * kWave < nt) tr[v] = sw_load(s_t, min(v * kWave + lane, nt - 1));
-        }
-        // ord S of lanes without an entry: 0, below every score (ord32 of
-        // -inf is 0x007fffff), so that comparisons of S need no masks
-#pragma unroll
-        for (int u = 0; u < MP; ++u) pS[u] = pv[u] ? pS[u] : 0u;
-#pragma unroll
-        for (int v = 0; v < MT; ++v) tr[v].o = tv[v] ? tr[v].o : 0u;
-        if (tid == 0) s_np[cur ^ 1] = 0;  // last read a sweep ago, before two barriers
-
-        // Push candidates: task 2u scores the first-child chains of slot u
-        // (of the entries that end a chain), task 2u + 1 the next siblings, on
-        // wave 3 - task mod 4.  With at most four slots per lane, slot 0's two
-        // tasks are scored before the merge (whether an entry enters T is only
-        // known after it), so that with one slot in use they overlap the
-        // counting of waves 0 and 1; every other task is scored after it.
-        constexpr bool EARLY = MP <= 4;
-        auto owner = [&](int t) { return NWV - 1 - t % NWV; };
-        auto score_chain = [&](const SwRec& w, bool valid, SwRec (&c)[CL], bool (&ok)[CL])
-                               __attribute__((always_inline)) {
-            SwRec par = w;
-            bool okp = valid & ((par.meta & kChainEnd) != 0u);
-#pragma unroll
-            for (int i = 0; i < CL; ++i) {
-                ok[i] = okp & first_child(par, false, i == CL - 1, c[i]);
-                par = c[i];
-                okp = ok[i];
-            }
-        };
-        auto score_sibling = [&](const SwRec& w, bool valid, SwRec& c, bool& ok) __attribute__((always_inline)) {
-            // next sibling (depth d, drafter row d - 1, the parent's context)
-            const int d = (int)(w.meta >> 4) & 63, r = (int)(w.meta & 15);
-            const int rp = (int)(w.meta >> 10) & 15, rg = (int)(w.meta >> 14) & 15;
-            const int srow = min(max(d - 1, 0), D - 1);
-            int sr;
-            float sS;
-            const uint32_t so =
-                child(srow, d - 1 >= 2 ? rg : 0, d - 1 >= 1 ? rp : 0, unord32(w.po), false, w.o, r, sr, sS);
-            c = SwRec{so, w.k0, w.k1, w.k2, w.k3, w.po,
-                      (uint32_t)sr | ((uint32_t)d << 4) | ((uint32_t)rp << 10) | ((uint32_t)rg << 14) | kChainEnd};
-            c = with_digit(c, max(d, 1), sr);
-            ok = valid & (so != 0u);
-        };
-        SwRec ea[CL], eb = SwRec{0u, 0u, 0u, 0u, 0u, 0u, 0u};
-        bool oea[CL], oeb = false;
-#pragma unroll
-        for (int i = 0; i < CL; ++i) {
-            oea[i] = false;
-            ea[i] = SwRec{0u, 0u, 0u, 0u, 0u, 0u, 0u};
-        }
-        if (EARLY) {
-            if (owner(0) == wv) score_chain(prec(0), pv[0], ea, oea);
-            if (owner(1) == wv) score_sibling(prec(0), pv[0], eb, oeb);
-        }
-
-        // merged places: a T entry moves down by the P entries before it; a P
-        // entry lands after the T and P entries before it.  Each P entry in
-        // turn is read from its lane and compared with all entries at once,
-        // on S alone unless some S equals its S (then the keys decide); wave
-        // w takes the entries l = w (mod 4) of every slot.  AT, AP: the slots
-        // that hold entries this sweep.
-        int tc[MT], pc[MP];
-#pragma unroll
-        for (int v = 0; v < MT; ++v) tc[v] = 0;
-#pragma unroll
-        for (int u = 0; u < MP; ++u) pc[u] = 0;
-        // Counts for the P entries at lanes l0 and l1 (l1 < 0: none) of slot
-        // u, written so that the two entries' instructions interleave.  Lane
-        // masks straight from the compares: T entries before y, T entries y
-        // precedes, P entries y precedes; equal S (rare) falls back to keys.
-        auto count = [&](auto at, auto ap) __attribute__((always_inline)) {
-            constexpr int AT = decltype(at)::value, AP = decltype(ap)::value;
-            auto tie_fix = [&](const SwRec& y, int u, int l, int& before) __attribute__((always_inline)) {
-                const uint32_t yo = y.o;
-#pragma unroll
-                for (int v = 0; v < AT; ++v) {
-                    const bool e = tr[v].o == yo;
-                    const bool g = sw_key_less(tr[v], y);
-                    before += __popcll(__ballot(e & g));
-                    tc[v] += (e & !g) ? 1 : 0;
-                }
-#pragma unroll
-                for (int q = 0; q < AP; ++q) {
-                    const bool e = (pS[q] == yo) & !((q == u) & (lane == l));
-                    if (__ballot(e) != 0ull) pc[q] += (e & sw_key_less(y, prec(q))) ? 1 : 0;
-                }
-            };
-#pragma unroll
-            for (int u = 0; u < AP; ++u) {
-                const int cnt = min(kWave, np - u * kWave);
-                for (int l0 = wv; l0 < cnt; l0 += 2 * NWV) {
-                    const int l1 = l0 + NWV < cnt ? l0 + NWV : l0;
-                    const bool two = l1 != l0;
-                    const uint32_t y0 = (uint32_t)__builtin_amdgcn_readlane((int)pS[u], l0);
-                    const uint32_t y1 = (uint32_t)__builtin_amdgcn_readlane((int)pS[u], l1);
-                    int b0 = 0, b1 = 0;
-                    uint64_t e0 = 0ull, e1 = 0ull;
-#pragma unroll
-                    for (int v = 0; v < AT; ++v) {
-                        b0 += __popcll(__builtin_amdgcn_uicmp(tr[v].o, y0, 34));  // T before y: greater ord S
-                        b1 += __popcll(__builtin_amdgcn_uicmp(tr[v].o, y1, 34));
-                        tc[v] += (tr[v].o < y0 ? 1 : 0) + ((two & (tr[v].o < y1)) ? 1 : 0);
-                        e0 |= __builtin_amdgcn_uicmp(tr[v].o, y0, 32);
-                        e1 |= __builtin_amdgcn_uicmp(tr[v].o, y1, 32);
-                    }
-#pragma unroll
-                    for (int q = 0; q < AP; ++q) {
-                        pc[q] += (pS[q] < y0 ? 1 : 0) + ((two & (pS[q] < y1)) ? 1 : 0);
-                        const uint64_t self0 = q == u ? 1ull << l0 : 0ull, self1 = q == u ? 1ull << l1 : 0ull;
-                        e0 |= __builtin_amdgcn_uicmp(pS[q], y0, 32) & ~self0;
-                        e1 |= __builtin_amdgcn_uicmp(pS[q], y1, 32) & ~self1;
-                    }
-                    if (e0 != 0ull) tie_fix(prec_at(u, l0), u, l0, b0);
-                    if (two && e1 != 0ull) tie_fix(prec_at(u, l1), u, l1, b1);
-                    pc[u] += (lane == l0 ? b0 : 0) + ((two & (lane == l1)) ? b1 : 0);
-                }
-            }
-        };
-        auto count_p = [&](auto at) __attribute__((always_inline)) {
-            if (np <= kWave) count(at, SlotCount<1>{});
-            else if (MP <= 2 || np <= 2 * kWave) count(at, SlotCount<(MP < 2 ? MP : 2)>{});
-            else if (MP <= 4 || np <= 4 * kWave) count(at, SlotCount<(MP < 4 ? MP : 4)>{});
-            else count(at, SlotCount<MP>{});
-        };
-        if (nt <= kWave) count_p(SlotCount<1>{});
-        else if (MT <= 2 || nt <= 2 * kWave) count_p(SlotCount<(MT < 2 ? MT : 2)>{});
-        else count_p(SlotCount<MT>{});
-
-        // sum of the four waves' counts
-        int32_t* my_cnt = s_cnt + wv * (MT + MP) * kWave;
-#pragma unroll
-        for (int v = 0; v < MT; ++v)
-            if (v * kWave < nt) my_cnt[v * kWave + lane] = tc[v];
-#pragma unroll
-        for (int u = 0; u < MP; ++u)
-            if (u * kWave < np) my_cnt[(MT + u) * kWave + lane] = pc[u];
-        __syncthreads();
-#pragma unroll
-        for (int v = 0; v < MT; ++v) {
-            if (v * kWave < nt) {
-                int c = 0;
-#pragma unroll
-                for (int w = 0; w < NWV; ++w) c += s_cnt[(w * (MT + MP) + v) * kWave + lane];
-                tc[v] = c;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < MP; ++u) {
-            if (u * kWave < np) {
-                int c = 0;
-#pragma unroll
-                for (int w = 0; w < NWV; ++w) c += s_cnt[(w * (MT + MP) + MT + u) * kWave + lane];
-                pc[u] = c;
-            }
-        }
-
-        // moved T entries and the P entries that made it go to their places
-        // (every wave read every record before the barrier); slot j of the
-        // two lists is stored by wave j mod 4
-#pragma unroll
-        for (int v = 0; v < MT; ++v) {
-            const int to = v * kWave + lane + tc[v];
-            if (v % NWV == wv && v * kWave < nt && (tv[v] & (tc[v] != 0) & (to < NB))) sw_store(s_t, to, tr[v]);
-        }
-#pragma unroll
-        for (int u = 0; u < MP; ++u)
-            if ((MT + u) % NWV == wv && u * kWave < np && (pv[u] & (pc[u] < NB))) sw_store(s_t, pc[u], prec(u));
-        const int nt_new = min(NB, nt + np);
-        const bool full = nt_new == NB;
-        // T's last entry, from the registers
-        SwRec last = SwRec{0u, 0u, 0u, 0u, 0u, 0u, 0u};
-        if (full) {
-#pragma unroll
-            for (int v = 0; v < MT; ++v) {
-                if (v * kWave < nt) {
-                    const uint64_t m = __ballot(tv[v] & (v * kWave + lane + tc[v] == NB - 1));
-                    if (m) last = sw_readlane(tr[v], __ffsll((unsigned long long)m) - 1);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < MP; ++u) {
-                if (u * kWave < np) {
-                    const uint64_t m = __ballot(pv[u] & (pc[u] == NB - 1));
-                    if (m) last = prec_at(u, __ffsll((unsigned long long)m) - 1);
-                }
-            }
-        }
-
-        // pushes of the P entries that entered T, while T is not full or when
-        // they precede its last entry; a task takes its places in the next P
-        // with one atomic
-        auto push = [&](auto& h, auto& c) __attribute__((always_inline)) {
-            constexpr int n = sizeof(h) / sizeof(h[0]);
-            uint64_t m[n];
-            int total = 0;
-#pragma unroll
-            for (int i = 0; i < n; ++i) {
-                m[i] = __ballot(h[i]);
-                total += __popcll(m[i]);
-            }
-            if (total == 0) return;
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&s_np[cur ^ 1], total);
-            base = __builtin_amdgcn_readlane(base, 0);
-#pragma unroll
-            for (int i = 0; i < n; ++i) {
-                const int at = base + lanes_below(m[i]);
-                if (h[i] & (at < cap_p)) sw_store(s_pn, at, c[i]);
-                base += __popcll(m[i]);
-            }
-        };
-#pragma unroll
-        for (int u = 0; u < MP; ++u) {
-            if (u * kWave >= np) break;
-            const bool in = pv[u] & (pc[u] < NB);
-            if (owner(2 * u) == wv) {
-                SwRec c[CL];
-                bool ok[CL];
-                if (EARLY && u == 0) {
-#pragma unroll
-                    for (int i = 0; i < CL; ++i) {
-                        c[i] = ea[i];
-                        ok[i] = oea[i];
-                    }
-                } else {
-                    score_chain(prec(u), pv[u], c, ok);
-                }
-                bool h[CL];
-#pragma unroll
-                for (int i = 0; i < CL; ++i) h[i] = ok[i] & in & (!full | sw_before(c[i], last));
-                push(h, c);
-            }
-            if (owner(2 * u + 1) == wv) {
-                SwRec c[1] = {eb};
-                bool ok = oeb;
-                if (!(EARLY && u == 0)) score_sibling(prec(u), pv[u], c[0], ok);
-                bool h[1] = {(bool)(ok & in & (!full | sw_before(c[0], last)))};
-                push(h, c);
-            }
-        }
-        nt = nt_new;
-        __syncthreads();
-        cur ^= 1;
-        np = min(s_np[cur], cap_p);
-        if (PL) {
-            uint4* t = s_pc;
-            s_pc = s_pn;
-            s_pn = t;
-        }
-    }
-
-    // parents: node i >= 1 is T's position i - 1; the parent of a node of
-    // depth d > 1 is the T entry with the parent's (S, key), found by binary
-    // search (it precedes the node, so its position is smaller)
-    if (tid == 0) s_par[0] = -1;
-    const int top = nt > 0 ? 1 << (31 - __clz(nt)) : 0;
-    for (int p = tid; p < nt; p += NT) {
-        const SwRec x = sw_load(s_t, p);
-        const int d = (int)(x.meta >> 4) & 63;
-        int par = 0;
-        if (d > 1) {
-            SwRec tg = x;
-            tg.o = x.po;
-            const uint32_t t = (uint32_t)(d - 1);
-            const uint32_t wi = (t * pw_magic) >> 16;
-            const uint32_t sh = 32u - (t - wi * (uint32_t)per_word + 1u) * (uint32_t)wbits;
-            const uint32_t m = ~(((1u << wbits) - 1u) << sh);
-            tg.k0 &= wi == 0 ? m : ~0u;
-            tg.k1 &= wi == 1 ? m : ~0u;
-            tg.k2 &= wi == 2 ? m : ~0u;
-            tg.k3 &= wi == 3 ? m : ~0u;
-            int q = 0;
-            for (int step = top; step > 0; step >>= 1) {
-                const int c = q + step;
-                if (c <= nt && sw_before(sw_load(s_t, c - 1), tg)) q = c;
-            }
-            par = min(q + 1, p);
-        }
-        s_par[p + 1] = par;
-    }
-    __syncthreads();
-
-    // output rows and ancestor masks (the parent chain, at most D steps)
-    constexpr int SLW = MT + 1;  // W = ceil((budget + 1) / 64) <= MT + 1
-    const int64_t ob = (int64_t)b * N;
-    const int root_tok = __builtin_amdgcn_readfirstlane(a.root_token[b]);
-    for (int i = tid; i < N; i += NT) {
-        uint64_t words[SLW];
-#pragma unroll
-        for (int q = 0; q < SLW; ++q) words[q] = 0ull;
-        if (i == 0) {
-            a.parent[ob] = -1;
-            a.token[ob] = root_tok;
-            a.depth[ob] = 0;
-            a.rank[ob] = -1;
-            a.score[ob] = 0.f;
-            words[0] = 1ull;
-        } else if (i <= nt) {
-            const SwRec x = sw_load(s_t, i - 1);
-            const int d = (int)(x.meta >> 4) & 63, r = (int)(x.meta & 15);
-            a.parent[ob + i] = s_par[i];
-            a.token[ob + i] = s_ids[(d - 1) * k + r];
-            a.depth[ob + i] = d;
-            a.rank[ob + i] = r;
-            a.score[ob + i] = unord32(x.o);
-            int y = i;
-            for (int step = 0; step <= D && y > 0; ++step) {
-#pragma unroll
-                for (int q = 0; q < SLW; ++q) words[q] |= q == (y >> 6) ? 1ull << (y & 63) : 0ull;
-                y = s_par[y];
-            }
-            words[0] |= 1ull;
-        } else {
-            a.parent[ob + i] = -1;
-            a.token[ob + i] = -1;
-            a.depth[ob + i] = -1;
-            a.rank[ob + i] = -1;
-            a.score[ob + i] = -INFINITY;
-        }
-#pragma unroll
-        for (int q = 0; q < SLW; ++q)
-            if (q < W) a.anc[(ob + i) * W + q] = words[q];
-    }
-    if (tid == 0) a.n_nodes[b] = nt + 1;
-}
 }  // namespace presto
 
 namespace presto_host {
@@ -1595,31 +1278,8 @@ using namespace presto;
 
 static int align16(int x) { return (x + 15) & ~15; }
 
-struct TreeLayout {
-    int total_no_rho, total_with_rho;
-    int o_lp, o_ids, o_kord, o_krank, o_rec, o_pkey, o_ktab, o_beam, o_kbeam, o_rho;
-};
-
-static TreeLayout tree_layout(int D, int k, int N, int Wb) {
-    TreeLayout L;
-    int off = 0;
-    L.o_lp = off; off = align16(off + D * k * 4);
-    L.o_ids = off; off = align16(off + D * k * 4);
-    L.o_kord = off; off = align16(off + N * k * 4);
-    L.o_krank = off; off = align16(off + N * k);
-    L.o_ktab = off; off = align16(off + (D + 1) * Wb * k);
-    L.o_beam = off; off = align16(off + 2 * Wb * (int)sizeof(BeamEntry));
-    L.o_kbeam = off; off = align16(off + (Wb > 0 ? N * k : 0));  // beam search only
-    L.o_rec = off; off = align16(off + N * 8);
-    L.o_pkey = off; off = align16(off + N * 16);
-    L.total_no_rho = off;
-    L.o_rho = off;
-    L.total_with_rho = align16(off + D * k * k * k * 4);
-    return L;
-}
-
-// gfx950 gives one workgroup up to 160 KiB of LDS; the search runs one wave
-// per CU anyway, so the lattice stays in LDS whenever the total fits.
+// gfx950 gives one workgroup up to 160 KiB of LDS; one sequence's search runs
+// alone on its CU anyway.
 static constexpr int kTreeLdsBudget = 160 * 1024;
 static constexpr int kDefaultLds = 64 * 1024;
 
@@ -1669,50 +1329,80 @@ static Alg2Layout alg2_layout(int D, int k, int branch, int budget) {
     return L;
 }
 
-// Frontier sweeps: candidate table, lambda, T, P (capacity 2 budget), the
-// parent positions, then the lattice.
-struct SweepLayout {
-    int total_no_rho, total_with_rho;
-    int o_lp, o_ids, o_lam, o_t, o_p, o_p2, o_par, o_cnt, o_np, o_rho;
+// Threads of the level kernel: enough that a level's candidates (up to about
+// budget * k / 2, usually budget) take few rounds, few enough that the
+// barriers stay cheap.
+static int level_threads(int budget) { return budget <= 128 ? 256 : (budget <= 256 ? 512 : 1024); }
+
+// Level and beam kernels: candidate table, lambda, the pool with its sort
+// scratch (the one-node-at-a-time search of the level kernel reuses that
+// memory), then the lattice.
+struct PoolLayout {
+    int kw, cap, total;
+    bool rho_in_lds;
+    int o_lp, o_ids, o_lam, o_pool, o_key, o_hist, o_fine, o_list, o_place, o_row, o_par, o_misc, o_rho;
+    int o_kord, o_krank, o_rec, o_pkey;
 };
 
-// slots per lane of T and P for a budget (the kernel's MT and MP)
-static int sweep_mt(int budget) { return budget <= 64 ? 1 : (budget <= 128 ? 2 : (budget <= 256 ? 4 : 8)); }
-// chains of three first children at budgets <= 64 (8 -> 6 sweeps at depth 16 against chains of
-// two, 15 with none); at larger budgets the trees are wider and chains added entries without
-// removing sweeps
-static int sweep_chain(int budget) { return sweep_mt(budget) == 1 ? 3 : 1; }
-static int sweep_mp(int budget) { return (sweep_chain(budget) + 1) * sweep_mt(budget); }
-
-static SweepLayout sweep_layout(int D, int k, int N) {
-    SweepLayout L;
-    const int nb = N - 1;
+static PoolLayout pool_layout_cap(int D, int k, int N, int threads, bool pops, bool lattice, int cap) {
+    PoolLayout L;
+    L.kw = D <= 2 * (32 / tree_key_bits(k)) ? 2 : 4;
+    L.cap = cap;
     int off = 0;
     L.o_lp = off; off = align16(off + D * k * 4);
     L.o_ids = off; off = align16(off + D * k * 4);
     L.o_lam = off; off = align16(off + D * 4);
-    L.o_t = off; off = align16(off + nb * 32);
-    L.o_p = off; off = align16(off + (sweep_chain(nb) + 1) * nb * 32);
-    L.o_p2 = off; off = align16(off + (sweep_mt(nb) >= 8 ? (sweep_chain(nb) + 1) * nb * 32 : 0));  // P's second buffer
-    L.o_par = off; off = align16(off + N * 4);
-    L.o_cnt = off; off = align16(off + kSweepWaves * (sweep_mt(nb) + sweep_mp(nb)) * kWave * 4);
-    L.o_np = off; off = align16(off + 2 * 4);
-    L.total_no_rho = off;
-    L.o_rho = off;
-    L.total_with_rho = align16(off + D * k * k * k * 4);
+    const int base = off;
+    L.o_pool = off; off = align16(off + cap * 8);
+    L.o_key = off; off = align16(off + cap * 4 * L.kw);
+    L.o_hist = off; off = align16(off + kBins * 4);
+    L.o_fine = off; off = align16(off + ((threads < 512 ? 512 : threads) + 1) * 4);
+    L.o_list = off; off = align16(off + cap * 2);
+    L.o_place = off; off = align16(off + cap * 2);
+    L.o_row = off; off = align16(off + N * 2);
+    L.o_par = off; off = align16(off + N * 2);
+    L.o_misc = off; off = align16(off + 64 * 4);
+    int end = off;
+    off = base;
+    L.o_kord = off; off = align16(off + N * k * 4);
+    L.o_krank = off; off = align16(off + N * k);
+    L.o_rec = off; off = align16(off + N * 8);
+    L.o_pkey = off; off = align16(off + N * 16);
+    if (pops && off > end) end = off;
+    L.o_rho = end;
+    L.rho_in_lds = lattice;
+    L.total = lattice ? align16(end + D * k * k * k * 4) : end;
     return L;
 }
 
-// Budgets the sweep kernel takes: above 512 the slots per lane would not
-// fit (T's records stay in registers); at 32 and below popping one node at
-// a time is faster (a sweep costs about three pops, and a tree of depth 16
-// needs about 14 sweeps).
-static constexpr int kSweepMinBudget = 33;
-static constexpr int kSweepMaxBudget = 512;
+// The pool holds four entries per budgeted node (three to four is what the
+// searches enter) and 256 more, or what fits; the lattice is in LDS whenever
+// that leaves room for two per node and 256.
+static PoolLayout level_layout(int D, int k, int budget, bool lattice) {
+    const int threads = level_threads(budget), N = budget + 1;
+    const int want = 4 * budget + 257 < kPoolMax ? 4 * budget + 257 : kPoolMax;
+    for (int in_lds = lattice ? 1 : 0; in_lds >= 0; --in_lds)
+        for (int cap = want; cap >= 2 * budget + 257; cap -= 64) {
+            const PoolLayout L = pool_layout_cap(D, k, N, threads, true, in_lds != 0, cap);
+            if (L.total <= kTreeLdsBudget) return L;
+        }
+    return pool_layout_cap(D, k, N, threads, true, false, 2 * budget + 257);
+}
+
+// static LDS of the beam kernel, taken off the dynamic budget
+static constexpr int kBeamStatic = 4096;
+
+static PoolLayout beam_layout(int D, int k, int budget, int width, bool lattice) {
+    const int cap = budget + width * k + 1;  // root, T below the budget, one more depth
+    const PoolLayout L = pool_layout_cap(D, k, budget + 1, kBeamThreads, false, lattice, cap);
+    if (!lattice || L.total <= kTreeLdsBudget - kBeamStatic) return L;
+    return pool_layout_cap(D, k, budget + 1, kBeamThreads, false, false, cap);
+}
 
 bool tree_build_fits(int D, int k, int branch, int N, int beam_width, bool alg2) {
     if (alg2) return alg2_layout(D, k, branch, N - 1).total_no_rho <= kTreeLdsBudget;
-    return tree_layout(D, k, N, beam_width).total_no_rho <= kTreeLdsBudget;
+    if (beam_width > 0) return beam_layout(D, k, N - 1, beam_width, false).total <= kTreeLdsBudget - kBeamStatic;
+    return level_layout(D, k, N - 1, false).total <= kTreeLdsBudget;
 }
 
 presto_status launch_build_tree(const presto_tree_desc* desc, const int32_t* ids,
@@ -1742,16 +1432,16 @@ presto_status launch_build_tree(const presto_tree_desc* desc, const int32_t* ids
     a.rank = rank;
     a.score = score;
     a.anc = anc;
+    presto_status st = PRESTO_OK;
     if (desc->mode == PRESTO_TREE_BEST_FIRST_ALG2) {
         const Alg2Layout L = alg2_layout(a.D, a.k, a.branch, a.budget);
         a.beam_width = 0;
         a.o_lp = L.o_lp; a.o_ids = L.o_ids; a.o_rho = L.o_rho;
         a.o_tmeta = L.o_tmeta; a.o_tS = L.o_tS; a.o_tkey = L.o_tkey; a.o_tplace = L.o_tplace;
-        a.rho_in_lds = log_rho != nullptr && L.total_with_rho <= kTreeLdsBudget;
-        const int lds = a.rho_in_lds ? L.total_with_rho : L.total_no_rho;
+        const bool rho_in_lds = log_rho != nullptr && L.total_with_rho <= kTreeLdsBudget;
+        const int lds = rho_in_lds ? L.total_with_rho : L.total_no_rho;
         const int slt = (L.cap + kWave - 1) / kWave;
-        const int rho_mode = log_rho == nullptr ? 0 : (a.rho_in_lds ? 1 : 2);
-        presto_status st = PRESTO_OK;
+        const int rho_mode = log_rho == nullptr ? 0 : (rho_in_lds ? 1 : 2);
         auto go = [&](auto kernel) {
             st = allow_lds(kernel, lds);
             if (st == PRESTO_OK) kernel<<<desc->batch, kWave, lds, stream>>>(a);
@@ -1770,77 +1460,51 @@ presto_status launch_build_tree(const presto_tree_desc* desc, const int32_t* ids
         return check_launch("tree_alg2_kernel");
     }
     const bool beam = desc->mode == PRESTO_TREE_BEAM;
-    if (!beam && a.budget >= kSweepMinBudget && a.budget <= kSweepMaxBudget) {
-        const SweepLayout L = sweep_layout(a.D, a.k, a.N);
-        a.beam_width = 0;
-        a.o_lp = L.o_lp; a.o_ids = L.o_ids; a.o_lam = L.o_lam; a.o_rho = L.o_rho;
-        a.o_sw_t = L.o_t; a.o_sw_p = L.o_p; a.o_sw_p2 = L.o_p2; a.o_sw_par = L.o_par; a.o_sw_cnt = L.o_cnt;
-        a.o_sw_np = L.o_np;
-        a.rho_in_lds = log_rho != nullptr && L.total_with_rho <= kTreeLdsBudget;
-        const uint64_t k3 = (uint64_t)a.k * a.k * a.k;
-        a.mag_k = (uint32_t)(((1ull << 32) + a.k - 1) / a.k);        // k > 1 only
-        a.mag_k3 = (uint32_t)(((1ull << 32) + k3 - 1) / k3);
-        const int lds = a.rho_in_lds ? L.total_with_rho : L.total_no_rho;
-        const int rho_mode = log_rho == nullptr ? 0 : (a.rho_in_lds ? 1 : 2);
-        presto_status st = PRESTO_OK;
-        auto go = [&](auto kernel) {
-            st = allow_lds(kernel, lds);
-            if (st == PRESTO_OK) kernel<<<desc->batch, kSweepWaves * kWave, lds, stream>>>(a);
-        };
-#define PRESTO_SWEEP3(T, P, K, C)                                    \
-    if (rho_mode == 0) go(tree_sweep_kernel<T, P, K, 0, C>);        \
-    else if (rho_mode == 1) go(tree_sweep_kernel<T, P, K, 1, C>);   \
-    else go(tree_sweep_kernel<T, P, K, 2, C>)
-#define PRESTO_SWEEP(T, P, C)                                        \
-    if (a.k <= 4) { PRESTO_SWEEP3(T, P, 4, C); }                     \
-    else if (a.k <= 8) { PRESTO_SWEEP3(T, P, 8, C); }                \
-    else { PRESTO_SWEEP3(T, P, 16, C); }
-        const int mt = sweep_mt(a.budget);
-        if (mt == 1) { PRESTO_SWEEP(1, 4, 3) }
-        else if (mt == 2) { PRESTO_SWEEP(2, 4, 1) }
-        else if (mt == 4) { PRESTO_SWEEP(4, 8, 1) }
-        else { PRESTO_SWEEP(8, 16, 1) }
-#undef PRESTO_SWEEP
-#undef PRESTO_SWEEP3
-        if (st != PRESTO_OK) return st;
-        return check_launch("tree_sweep_kernel");
-    }
+    const bool lattice = log_rho != nullptr;
     a.beam_width = beam ? desc->beam_width : 0;
-    const TreeLayout L = tree_layout(a.D, a.k, a.N, a.beam_width);
-    a.o_lp = L.o_lp; a.o_ids = L.o_ids; a.o_kord = L.o_kord; a.o_krank = L.o_krank; a.o_rec = L.o_rec;
-    a.o_pkey = L.o_pkey;
-    a.o_ktab = L.o_ktab; a.o_beam = L.o_beam; a.o_kbeam = L.o_kbeam;
-    a.o_rho = L.o_rho;
-    a.rho_in_lds = log_rho != nullptr && L.total_with_rho <= kTreeLdsBudget;
-    const int lds = a.rho_in_lds ? L.total_with_rho : L.total_no_rho;
-    const int SL = (a.N + kWave - 1) / kWave;
-    const int rho_mode = log_rho == nullptr ? 0 : (a.rho_in_lds ? 1 : 2);
-    presto_status st = PRESTO_OK;
+    const PoolLayout L = beam ? beam_layout(a.D, a.k, a.budget, a.beam_width, lattice)
+                              : level_layout(a.D, a.k, a.budget, lattice);
+    a.o_lp = L.o_lp; a.o_ids = L.o_ids; a.o_lam = L.o_lam; a.o_rho = L.o_rho;
+    a.o_pool = L.o_pool; a.o_key = L.o_key; a.o_hist = L.o_hist; a.o_fine = L.o_fine; a.o_list = L.o_list;
+    a.o_place = L.o_place; a.o_row = L.o_row; a.o_par = L.o_par; a.o_misc = L.o_misc;
+    a.o_kord = L.o_kord; a.o_krank = L.o_krank; a.o_rec = L.o_rec; a.o_pkey = L.o_pkey;
+    a.cap = L.cap;
+    const uint64_t k3 = (uint64_t)a.k * a.k * a.k;
+    a.mag_k = (uint32_t)(((1ull << 32) + a.k - 1) / a.k);  // k > 1 only
+    a.mag_k3 = (uint32_t)(((1ull << 32) + k3 - 1) / k3);
+    const int rho_mode = !lattice ? 0 : (L.rho_in_lds ? 1 : 2);
+    const int threads = beam ? kBeamThreads : level_threads(a.budget);
     auto go = [&](auto kernel) {
-        st = allow_lds(kernel, lds);
-        if (st == PRESTO_OK) kernel<<<desc->batch, kWave, lds, stream>>>(a);
+        st = allow_lds(kernel, L.total);
+        if (st == PRESTO_OK) kernel<<<desc->batch, threads, L.total, stream>>>(a);
     };
-#define PRESTO_TREE4(S, R, Q)                         \
-    if (beam) go(tree_build_kernel<S, R, Q, true>);   \
-    else go(tree_build_kernel<S, R, Q, false>)
-#define PRESTO_TREE2(S, R) \
-    if (a.k <= 4) { PRESTO_TREE4(S, R, true); } else { PRESTO_TREE4(S, R, false); }
-#define PRESTO_TREE(S)                      \
-    if (rho_mode == 0) { PRESTO_TREE2(S, 0); } \
-    else if (rho_mode == 1) { PRESTO_TREE2(S, 1); } \
-    else { PRESTO_TREE2(S, 2); }
-    if (SL <= 1) { PRESTO_TREE(1) }
-    else if (SL <= 2) { PRESTO_TREE(2) }
-    else if (SL <= 3) { PRESTO_TREE(3) }
-    else if (SL <= 4) { PRESTO_TREE(4) }
-    else if (SL <= 5) { PRESTO_TREE(5) }
-    else if (SL <= 8) { PRESTO_TREE(8) }
-    else { PRESTO_TREE(16) }
-#undef PRESTO_TREE
-#undef PRESTO_TREE2
-#undef PRESTO_TREE4
+    if (beam) {
+#define PRESTO_BEAM(K)                                    \
+    if (rho_mode == 0) go(tree_beam_kernel<0, K>);        \
+    else if (rho_mode == 1) go(tree_beam_kernel<1, K>);   \
+    else go(tree_beam_kernel<2, K>)
+        if (L.kw == 2) { PRESTO_BEAM(2); } else { PRESTO_BEAM(4); }
+#undef PRESTO_BEAM
+        if (st != PRESTO_OK) return st;
+        return check_launch("tree_beam_kernel");
+    }
+#define PRESTO_LEVEL3(T, S, K)                                   \
+    if (rho_mode == 0) go(tree_level_kernel<T, S, 0, K>);        \
+    else if (rho_mode == 1) go(tree_level_kernel<T, S, 1, K>);   \
+    else go(tree_level_kernel<T, S, 2, K>)
+#define PRESTO_LEVEL(T, S) \
+    if (L.kw == 2) { PRESTO_LEVEL3(T, S, 2); } else { PRESTO_LEVEL3(T, S, 4); }
+    // the second parameter: frontier slots per lane of the one-node-at-a-time
+    // search, ceil(N / 64)
+    if (a.budget <= 64) { PRESTO_LEVEL(256, 2) }
+    else if (a.budget <= 128) { PRESTO_LEVEL(256, 3) }
+    else if (a.budget <= 256) { PRESTO_LEVEL(512, 5) }
+    else if (a.budget <= 512) { PRESTO_LEVEL(1024, 9) }
+    else { PRESTO_LEVEL(1024, 16) }
+#undef PRESTO_LEVEL
+#undef PRESTO_LEVEL3
     if (st != PRESTO_OK) return st;
-    return check_launch("tree_build_kernel");
+    return check_launch("tree_level_kernel");
 }
 
 }  // namespace presto_host

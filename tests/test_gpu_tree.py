@@ -222,3 +222,45 @@ def test_tree_deep_ties(D, k, B, mode):
     _assert_same(g, o)
     ties = sum(int((np.diff(np.sort(row[np.isfinite(row)])) == 0).sum()) for row in o["score"][:, 1:])
     assert ties > b * 10  # ties really occur
+
+
+def _shape_table(kind, rng, b, D, k):
+    """Candidate tables that decide the level search's route: `flat` (whole
+    levels tie), `zero` (candidates of probability 1: every prefix ties with
+    its ancestors), `masked` (most rows hold fewer than k finite logits),
+    `steep` (scores far below the histogram's range) and `mixed`."""
+    lp = -np.sort(rng.exponential(1.5, size=(b, D, k)), axis=2)
+    if kind == "flat":
+        lp[:] = -1.5
+    elif kind == "zero":
+        lp[:, :, : min(2, k)] = 0.0
+    elif kind == "masked":
+        for s, d in np.ndindex(b, D):
+            lp[s, d, rng.integers(1, k + 1):] = -np.inf
+    elif kind == "steep":
+        lp *= 300.0
+    return lp.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["flat", "zero", "masked", "steep", "mixed"])
+@pytest.mark.parametrize("D,k,branch,B", [(16, 4, 4, 63), (16, 4, 4, 64), (16, 4, 4, 65), (32, 4, 3, 128),
+                                          (20, 4, 4, 129), (12, 8, 8, 256), (13, 8, 8, 257), (16, 10, 10, 512),
+                                          (17, 10, 7, 513), (5, 16, 16, 1023), (24, 1, 1, 30)])
+def test_tree_level_search_routes(kind, D, k, branch, B):
+    """Budgets at the edges of the level kernel's sizes, two- and four-word
+    rank-path keys (D = 16 | 17 at k = 10), levels that are counted before
+    they are entered, and both ways into the one-node-at-a-time search (a pool
+    that overflows with ties; candidates of S = -inf filling the budget);
+    beam search on the same tables.  Bit-exact."""
+    rng = np.random.default_rng([D, k, B, len(kind)])
+    b = 3
+    lp = _shape_table(kind, rng, b, D, k)
+    R = np.log(rng.uniform(1e-3, 1, (b, D, k, k, k))).astype(np.float32)
+    ids = np.stack([[rng.choice(5000, k, replace=False) for _ in range(D)] for _ in range(b)]).astype(np.int32)
+    root = rng.integers(0, 5000, size=b).astype(np.int32)
+    for lam_v, rho in ((0.0, None), (0.3, R)):
+        lam = np.full(D, lam_v, np.float32)
+        for width in (0, 10):
+            print(f"routes {kind} D={D} k={k} branch={branch} B={B} lam={lam_v} W={width}", flush=True)
+            g, o = _gpu_and_oracle(ids, lp, rho, lam, root, D, k, B, branch=branch, beam_width=width)
+            _assert_same(g, o)
