@@ -291,6 +291,8 @@ presto_status presto_build_tree(const presto_tree_desc *desc, const int32_t *ids
  * out      [batch, n_max, hq, head_dim], dtype dt
  * Arithmetic: bf16 inputs use bf16 matrix cores with fp32 accumulation and
  * fp32 softmax; fp32 inputs use fp32 throughout.
+ * fp32 inputs may be given a smaller workspace, or none: the context is then
+ * not split over workgroups (slower for small batches).
  * Limits: head_dim in {64, 128}; hq % hkv == 0; n_max <= 1024.
  */
 typedef enum { PRESTO_CTX_PACKED = 0, PRESTO_CTX_SLOTS = 1 } presto_ctx_layout;

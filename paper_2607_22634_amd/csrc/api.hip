@@ -321,8 +321,14 @@ presto_status presto_tree_attention(const presto_attn_desc* desc, const void* q,
                              (uintptr_t)(v_cache ? v_cache : q);
         REQUIRE(al % 16 == 0, "presto_tree_attention: bf16 tensors must be 16-byte aligned");
     }
-    presto_status st = check_ws(ws, ws_bytes, presto_tree_attention_workspace(&d));
-    if (st != PRESTO_OK) return st;
+    if (d.dt == PRESTO_DT_F32) {
+        // fp32 runs without a workspace too, one workgroup per row block
+        // taking the whole context
+        if (ws_bytes < presto_tree_attention_workspace(&d)) ws = nullptr;
+    } else {
+        presto_status st = check_ws(ws, ws_bytes, presto_tree_attention_workspace(&d));
+        if (st != PRESTO_OK) return st;
+    }
     return launch_tree_attention(&d, q, k_cache, v_cache, ctx_offsets, k_tree, v_tree, anc, n_nodes,
                                  out, ws, stream);
 }

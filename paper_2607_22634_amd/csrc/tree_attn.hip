@@ -753,77 +753,306 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
     }
 }
 
-// fp32 path: one wave per (b, n, h) row, plain fp32 arithmetic.  Each lane
-// runs an online softmax over a strided subset of keys; lanes are merged
-// through LDS at the end.
+// fp32 path, on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: exact fp32
+// products, fp32 accumulation), fp32 throughout.  A workgroup serves 32 query
+// rows of one KV head (packed as in the bf16 kernel) over one range of keys;
+// its four waves take every fourth 32-key block and combine their (m, l, O)
+// through LDS.  Scores are computed transposed, S^T = K Q^T, so a lane holds
+// one row and 16 of a block's keys, and the probabilities are the B operand of
+// O^T = V^T P^T as they are: an MFMA contracts two keys (or two head
+// dimensions), one from each half of the wave, and since the order of a
+// contraction and of the output rows is free, each lane reads 16 contiguous
+// bytes of a K row per four MFMAs (dimensions 8 j + 4 h + 0 .. 3) and D / 32
+// contiguous floats of a V row per key.  A block of 32 x 32 takes 2 x 64
+// MFMAs of 64 cycles, 8192 in all, for 32 KB of K/V: the matrix cores bound
+// it, so K and V come straight from global memory (16 B per clock and CU out
+// of the L2), K of the next block under the current P V, V under the scores.
+// Q sits in LDS to leave the registers to the loads in flight.
+// 2 sequences x 2048 keys, 33 nodes, 32/8 heads of 128: 701 us with one wave
+// per query row and a key per lane (uncoalesced reads, each row reading all
+// of K and V), 46 now (43% of the cycles with the matrix cores busy; the rest is
+// the first blocks' arrival, which all workgroups wait for at once, the
+// exponentials of two waves per SIMD and the combination).  8 x 16384 keys, 32
+// nodes: 102 TFLOP/s (a large fp32 matrix product reaches 148 on this card).
+struct AttnF32Args {
+    const float* q;
+    const float* kc;
+    const float* vc;
+    const int32_t* ctx_off;
+    int32_t ctx_slots;
+    const float* kt;
+    const float* vt;
+    const uint64_t* anc;
+    const int32_t* n_nodes;
+    float* out;
+    float* part_o;    // splits > 1: [b, g, split, row, D], normalised
+    float2* part_ml;  // [b, g, row, split]
+    int32_t n_max, hq, hkv, G, W;
+    int32_t row_blocks, splits, split_len;  // split_len: keys, a multiple of 32
+    int32_t n_tasks, n_blocks;
+    float scale;
+};
+
+constexpr int kF32Waves = 4;
+
+template <int N>
+struct FloatVec {
+    // rows are only 4-byte aligned in general
+    typedef float type __attribute__((ext_vector_type(N), aligned(4)));
+};
+
 template <int D>
-__global__ __launch_bounds__(kWave) void tree_attn_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ kc, const float* __restrict__ vc,
-    const int32_t* __restrict__ ctx_off, int32_t ctx_slots, const float* __restrict__ kt,
-    const float* __restrict__ vt, const uint64_t* __restrict__ anc,
-    const int32_t* __restrict__ n_nodes, float* __restrict__ out, int32_t n_max, int32_t hq,
-    int32_t hkv, float scale) {
-    __shared__ float s_acc[kWave][D + 1];
-    __shared__ float s_m[kWave], s_l[kWave];
-    const int lane = lane_id();
-    const int h = blockIdx.x % hq;
-    const int n = (blockIdx.x / hq) % n_max;
-    const int b = blockIdx.x / hq / n_max;
-    const int G = hq / hkv, g = h / G, W = (n_max + 63) / 64;
-    const int nn = clamp_nodes(n_nodes[b], n_max);
-    float* op = out + (((int64_t)b * n_max + n) * hq + h) * D;
-    if (n >= nn) {
-        for (int e = lane; e < D; e += kWave) op[e] = 0.f;
+__global__ __launch_bounds__(kF32Waves * kWave, 2) void tree_attn_f32_kernel(AttnF32Args a) {
+    constexpr int NW = kF32Waves, NT = NW * kWave;
+    constexpr int KJ = D / 8;   // 16-byte chunks of a K row per lane
+    constexpr int DB = D / 32;  // 32-row blocks of O^T
+    constexpr int QC = D / 4;   // 16-byte chunks of a Q row
+    constexpr int SLOT = kWave * (16 * DB + 2);  // floats of a wave's state
+    typedef typename FloatVec<4>::type f4;
+    typedef typename FloatVec<DB>::type fdb;
+    typedef float f4a __attribute__((ext_vector_type(4)));
+    // Q rows, chunk c of row r at c ^ r (sixteen rows read one chunk each:
+    // different banks); after the key loop the waves' states
+    __shared__ __align__(16) float s_mem[NW / 2 * SLOT > 32 * D ? NW / 2 * SLOT : 32 * D];
+
+    const int task = xcd_task(blockIdx.x, a.n_blocks);
+    if (task >= a.n_tasks) return;
+    // task = ((b * hkv + g) * splits + split) * row_blocks + rb: the row
+    // blocks that read the same keys share an XCD and its L2
+    const int rb = task % a.row_blocks;
+    const int split = task / a.row_blocks % a.splits;
+    const int bg = task / a.row_blocks / a.splits;
+    const int b = bg / a.hkv, g = bg - b * a.hkv;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int l32 = lane & 31, h = lane >> 5;
+
+    const CtxSpan cs = ctx_span(a.ctx_off, b, a.ctx_slots);
+    const int c0 = cs.c0, ctx = cs.ctx;
+    const int nn = clamp_nodes(a.n_nodes[b], a.n_max);
+    const int keys = ctx + nn;
+    const int live = a.G * nn, all_rows = a.G * a.n_max;
+    const int k_begin = split * a.split_len;
+    if (k_begin >= keys) return;  // the merge does not read this split of b
+    const int k_end = min(keys, k_begin + a.split_len);
+    const int nblk = (k_end - k_begin + 31) / 32;
+
+    const int row0 = rb * 32, rho = row0 + l32;
+    const int qn = rho / a.G, qh = rho - qn * a.G;
+    const bool is_live = rho < live;
+    if (row0 >= live) {
+        // padding nodes only: zeros (the merge writes them when there is one)
+        if (a.splits == 1)
+            for (int i = tid; i < 32 * D; i += NT) {
+                const int r = row0 + i / D;
+                if (r < all_rows)
+                    a.out[(((int64_t)b * a.n_max + r / a.G) * a.hq + g * a.G + r % a.G) * D + i % D] = 0.f;
+            }
         return;
     }
-    const CtxSpan cs = ctx_span(ctx_off, b, ctx_slots);
-    const int c0 = cs.c0, ctx = cs.ctx;
-    const float* qp = q + (((int64_t)b * n_max + n) * hq + h) * D;
-    const uint64_t* arow = anc + ((int64_t)b * n_max + n) * W;
-    float qv[D];
+    const uint64_t* arow = a.anc + ((int64_t)b * a.n_max + min(qn, a.n_max - 1)) * a.W;
+    const int64_t tree_row0 = (int64_t)b * a.n_max;
+    // row `key` of this KV head (keys past the end repeat the last one, masked)
+    auto row_of = [&](const float* cache, const float* tree, int key) __attribute__((always_inline)) {
+        const int kk = min(key, k_end - 1);
+        const bool in_ctx = kk < ctx;
+        const int64_t r = in_ctx ? (int64_t)(c0 + kk) : tree_row0 + (kk - ctx);
+        return (in_ctx ? cache : tree) + (r * a.hkv + g) * D;
+    };
+    const int64_t stride = (int64_t)a.hkv * D;  // from one key's row to the next
+    auto load_k = [&](int j0, f4 (&kr)[KJ]) __attribute__((always_inline)) {
+        const float* kp = row_of(a.kc, a.kt, j0 + l32) + 4 * h;
 #pragma unroll
-    for (int e = 0; e < D; ++e) qv[e] = qp[e];
-    float acc[D];
+        for (int j = 0; j < KJ; ++j) kr[j] = *reinterpret_cast<const f4*>(kp + 8 * j);
+    };
+    // V of keys 8 (i / 4) + 4 h + i % 4, i = 8 part .. 8 part + 7
+    auto load_v = [&](int j0, int part, fdb (&vr)[8]) __attribute__((always_inline)) {
+        if (j0 + 32 <= min(ctx, k_end)) {
+            const float* vp = a.vc + ((int64_t)(c0 + j0 + 16 * part + 4 * h) * a.hkv + g) * D + DB * l32;
 #pragma unroll
-    for (int e = 0; e < D; ++e) acc[e] = 0.f;
-    float m = -INFINITY, l = 0.f;
-    for (int j = lane; j < ctx + nn; j += kWave) {
-        const float *kp, *vp;
-        if (j < ctx) {
-            kp = kc + ((int64_t)(c0 + j) * hkv + g) * D;
-            vp = vc + ((int64_t)(c0 + j) * hkv + g) * D;
+            for (int i = 0; i < 8; ++i) vr[i] = *reinterpret_cast<const fdb*>(vp + (8 * (i / 4) + i % 4) * stride);
         } else {
-            const int t = j - ctx;
-            if (!((arow[t >> 6] >> (t & 63)) & 1ull)) continue;
-            kp = kt + (((int64_t)b * n_max + t) * hkv + g) * D;
-            vp = vt + (((int64_t)b * n_max + t) * hkv + g) * D;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int e = 8 * part + i;
+                vr[i] = *reinterpret_cast<const fdb*>(row_of(a.vc, a.vt, j0 + 8 * (e / 4) + 4 * h + e % 4) + DB * l32);
+            }
         }
-        float dot = 0.f;
+    };
+    auto swap_half = [&](float v) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        return __uint_as_float(h == 0 ? sw[1] : sw[0]);
+    };
+
+    floatx16 o[DB];
 #pragma unroll
-        for (int e = 0; e < D; ++e) dot += qv[e] * kp[e];
-        const float sc = dot * scale;
-        const float mn = fmaxf(m, sc);
-        const float al = expf(m - mn), p = expf(sc - mn);
-        l = l * al + p;
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int e = 0; e < D; ++e) acc[e] = acc[e] * al + p * vp[e];
-        m = mn;
+        for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
+    float m = -INFINITY, l = 0.f;
+    f4 kr[KJ];
+    if (wave < nblk) load_k(k_begin + 32 * wave, kr);  // in flight under the staging of Q
+    for (int i = tid; i < 32 * QC; i += NT) {
+        const int r = i / QC, c = i % QC;
+        const int rr = min(row0 + r, all_rows - 1);
+        const float* qp = a.q + (((int64_t)b * a.n_max + rr / a.G) * a.hq + g * a.G + rr % a.G) * D;
+        const f4 v = *reinterpret_cast<const f4*>(qp + 4 * c);
+        *reinterpret_cast<f4a*>(&s_mem[r * D + 4 * (c ^ (r & (QC - 1)))]) = v;
     }
-    s_m[lane] = m;
-    s_l[lane] = l;
-#pragma unroll
-    for (int e = 0; e < D; ++e) s_acc[lane][e] = acc[e];
     __syncthreads();
-    float M = -INFINITY;
-    for (int i = 0; i < kWave; ++i) M = fmaxf(M, s_m[i]);
-    float L = 0.f;
-    for (int i = 0; i < kWave; ++i) L += s_m[i] == -INFINITY ? 0.f : s_l[i] * expf(s_m[i] - M);
-    for (int e = lane; e < D; e += kWave) {
-        float v = 0.f;
-        for (int i = 0; i < kWave; ++i)
-            v += s_m[i] == -INFINITY ? 0.f : s_acc[i][e] * expf(s_m[i] - M);
-        op[e] = v / L;
+
+    for (int i = wave; i < nblk; i += NW) {
+        const int j0 = k_begin + 32 * i;
+        asm volatile("" ::: "memory");  // Q is read anew per block, not kept in (spilled) registers
+        fdb va[8], vb[8];
+        load_v(j0, 0, va);
+        floatx16 S;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) S[e] = 0.f;
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) {
+            const f4a qv = *reinterpret_cast<const f4a*>(&s_mem[l32 * D + 4 * ((2 * j + h) ^ (l32 & (QC - 1)))]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) S = __builtin_amdgcn_mfma_f32_32x32x2f32(kr[j][c], qv[c], S, 0, 0, 0);
+        }
+        load_v(j0, 1, vb);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) S[e] *= a.scale;
+        if (j0 + 32 > min(ctx, k_end)) {
+            // visible keys of this lane's row: the context, then its ancestors
+            uint32_t anc = 0u;
+            const int s0 = j0 - ctx;  // tree index of the block's first key
+            if (j0 + 32 > ctx) {
+                if (s0 >= 0) {
+                    const int w = s0 >> 6, sh = s0 & 63;
+                    const uint64_t lo = w < a.W ? arow[w] : 0ull, hi = w + 1 < a.W ? arow[w + 1] : 0ull;
+                    anc = (uint32_t)(sh == 0 ? lo : (lo >> sh) | (hi << (64 - sh)));
+                } else {
+                    anc = (uint32_t)(arow[0] << (-s0));
+                }
+            }
+            const int nctx = ctx - j0, nend = k_end - j0;
+            const uint32_t ctx_mask = nctx >= 32 ? ~0u : (nctx <= 0 ? 0u : (1u << nctx) - 1u);
+            const uint32_t end_mask = nend >= 32 ? ~0u : (1u << nend) - 1u;
+            const uint32_t vis = ((ctx_mask | anc) & end_mask) >> (4 * h);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) S[e] = ((vis >> (8 * (e >> 2) + (e & 3))) & 1u) ? S[e] : -INFINITY;
+        }
+        float mx = S[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, S[e]);
+        mx = fmaxf(mx, swap_half(mx));
+        if (__ballot(mx > m)) {
+            const float mn = fmaxf(m, mx);
+            const float al = m == -INFINITY ? 0.f : expf(m - mn);
+            l *= al;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) o[db] *= al;
+            m = mn;
+        }
+        const float mr = m == -INFINITY ? 0.f : m;  // no key visible yet: every term is 0
+        float ls = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            S[e] = expf(S[e] - mr);
+            ls += S[e];
+        }
+        l += ls + swap_half(ls);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[e][db], S[e], o[db], 0, 0, 0);
+        if (i + NW < nblk) load_k(j0 + 32 * NW, kr);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[e][db], S[8 + e], o[db], 0, 0, 0);
     }
+
+    // the waves' states, combined pairwise: odd multiples of `step` write,
+    // their partners fold them in
+#pragma unroll
+    for (int step = 1; step < NW; step *= 2) {
+        __syncthreads();
+        float* st = s_mem + wave / (2 * step) * SLOT + lane;
+        if (wave % (2 * step) == step) {
+            st[0] = m;
+            st[kWave] = l;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) st[(2 + db * 16 + e) * kWave] = o[db][e];
+        }
+        __syncthreads();
+        if (wave % (2 * step) == 0) {
+            const float m2 = st[0], l2 = st[kWave];
+            const float M = fmaxf(m, m2);
+            const float a1 = m == -INFINITY ? 0.f : expf(m - M), a2 = m2 == -INFINITY ? 0.f : expf(m2 - M);
+            l = a1 * l + a2 * l2;
+            m = M;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o[db][e] = a1 * o[db][e] + a2 * st[(2 + db * 16 + e) * kWave];
+        }
+    }
+    if (wave != 0 || rho >= all_rows) return;
+    // lane: row l32, dimensions DB (8 (e / 4) + 4 h + e % 4) + db
+    const float inv = is_live && l > 0.f ? 1.f / l : 0.f;
+    float* op;
+    if (a.splits == 1) {
+        op = a.out + (((int64_t)b * a.n_max + qn) * a.hq + g * a.G + qh) * D;
+    } else {
+        op = a.part_o + (((int64_t)bg * a.splits + split) * all_rows + rho) * D;
+        if (h == 0) a.part_ml[((int64_t)bg * all_rows + rho) * a.splits + split] = make_float2(m, l);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        fdb v;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) v[db] = o[db][e] * inv;
+        *reinterpret_cast<fdb*>(op + DB * (8 * (e >> 2) + 4 * h + (e & 3))) = v;
+    }
+}
+
+// Merge of the fp32 split partials: one wave per query row, lane s weighs
+// split s by l exp(m - M); dead rows are written as zeros.
+template <int D>
+__global__ __launch_bounds__(256) void tree_attn_f32_merge_kernel(AttnF32Args a) {
+    constexpr int PER = D / kWave;
+    const int lane = lane_id();
+    const int rows = a.G * a.n_max;
+    const int rho = (int)blockIdx.x * (blockDim.x / kWave) + (int)threadIdx.x / kWave;
+    if (rho >= rows) return;
+    const int bg = (int)blockIdx.y;
+    const int b = bg / a.hkv, g = bg - b * a.hkv;
+    const int n = rho / a.G, hh = rho - n * a.G;
+    const int nn = clamp_nodes(a.n_nodes[b], a.n_max);
+    const int keys = ctx_span(a.ctx_off, b, a.ctx_slots).ctx + nn;
+    const int nsplit = min(a.splits, (keys + a.split_len - 1) / a.split_len);
+    float acc[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] = 0.f;
+    if (n < nn) {
+        float2 ml = make_float2(-INFINITY, 0.f);
+        if (lane < nsplit) ml = a.part_ml[((int64_t)bg * rows + rho) * a.splits + lane];
+        const float M = wave_max_f32_dpp(ml.x);
+        const float wl = ml.x == -INFINITY ? 0.f : expf(ml.x - M) * ml.y;
+        const float L = wave_sum_f32_dpp(wl);
+        const float* po = a.part_o + ((int64_t)bg * a.splits * rows + rho) * D + lane * PER;
+        for (int s = 0; s < nsplit; ++s) {
+            const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wl), s));
+#pragma unroll
+            for (int e = 0; e < PER; ++e) acc[e] += w * po[(int64_t)s * rows * D + e];
+        }
+#pragma unroll
+        for (int e = 0; e < PER; ++e) acc[e] /= L;
+    }
+    float* op = a.out + (((int64_t)b * a.n_max + n) * a.hq + g * a.G + hh) * D + lane * PER;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) op[e] = acc[e];
 }
 
 }  // namespace presto
@@ -893,12 +1122,111 @@ static AttnPlan attn_plan(const presto_attn_desc* d) {
     return p;
 }
 
+// fp32: row blocks of 32, and the context split until the grid gives every
+// SIMD about two waves (512 workgroups of four); time in key blocks per wave:
+// rounds of workgroups x (blocks per wave + about 1 for the prologue and the
+// combination), and about 1 for a merge.  2 x 2048 keys, 33 nodes (80 row
+// blocks): 6 splits 48 us, against 59 at 2, 47 at 3, 60 at 4, 64 at 8, 71 at
+// 16; 1 x 2048 keys, 8 nodes (8 row blocks): 17 splits 22 us, against 54 at 2,
+// 28 at 6, 24 at 9, 31 at 33.
+struct AttnF32Plan {
+    int G, rows, row_blocks, splits, split_len;
+    int64_t tasks, blocks;
+};
+
+static AttnF32Plan attn_f32_plan(const presto_attn_desc* d, bool may_split) {
+    AttnF32Plan p;
+    p.G = d->hq / d->hkv;
+    p.rows = p.G * d->n_max;
+    p.row_blocks = (p.rows + 31) / 32;
+    const int64_t per_split = (int64_t)d->batch * d->hkv * p.row_blocks;
+    const int blocks = (d->max_ctx + d->n_max + 31) / 32;  // key blocks of the longest sequence
+    // the merge's grid.y and its lane per split bound the splits
+    const int most = may_split && (int64_t)d->batch * d->hkv <= 65535 ? kWave : 1;
+    double best = 1e30;
+    p.splits = 1;
+    p.split_len = blocks * 32;
+    for (int s = 1; s <= most && s * kF32Waves < blocks + kF32Waves; ++s) {
+        const int len = (blocks + s - 1) / s;
+        const int se = (blocks + len - 1) / len;
+        const double cost = ceil((double)per_split * se / 512.0) * ((len + kF32Waves - 1) / kF32Waves + 1.0) +
+                            (se > 1 ? 1.0 : 0.0);
+        if (cost < best - 1e-9) {
+            best = cost;
+            p.splits = se;
+            p.split_len = len * 32;
+        }
+    }
+    p.tasks = per_split * p.splits;
+    p.blocks = (p.tasks + 7) / 8 * 8;
+    return p;
+}
+
+// part_o bytes (rounded up), then part_ml
+static size_t attn_f32_partial_rows(const presto_attn_desc* d, const AttnF32Plan& p) {
+    return (size_t)d->batch * d->hkv * p.rows * p.splits;
+}
+
 size_t attn_workspace_bytes(const presto_attn_desc* d) {
-    if (d->dt != PRESTO_DT_BF16) return 0;
+    if (d->dt != PRESTO_DT_BF16) {
+        const AttnF32Plan p = attn_f32_plan(d, true);
+        if (p.splits <= 1) return 0;
+        const size_t prs = attn_f32_partial_rows(d, p);
+        return ((prs * d->head_dim * sizeof(float) + 255) & ~(size_t)255) + prs * sizeof(float2) + 256;
+    }
     const AttnPlan p = attn_plan(d);
     if (p.splits <= 1) return 0;
     const size_t prs = (size_t)d->batch * d->hkv * p.G * d->n_max * p.splits;
     return ((prs * d->head_dim * sizeof(uint16_t) + 255) & ~(size_t)255) + prs * sizeof(float2) + 256;
+}
+
+static presto_status launch_tree_attention_f32(const presto_attn_desc* d, const void* q, const void* k_cache,
+                                               const void* v_cache, const int32_t* ctx_offsets,
+                                               const void* k_tree, const void* v_tree, const uint64_t* anc,
+                                               const int32_t* n_nodes, void* out, void* ws, hipStream_t stream) {
+    const AttnF32Plan p = attn_f32_plan(d, ws != nullptr);
+    if (p.blocks >= (int64_t)1 << 31)
+        return set_error(PRESTO_ERR_UNSUPPORTED, "tree attention: %lld workgroups", (long long)p.blocks);
+    AttnF32Args a;
+    a.q = (const float*)q;
+    a.kc = (const float*)k_cache;
+    a.vc = (const float*)v_cache;
+    a.ctx_off = ctx_offsets;
+    a.ctx_slots = d->ctx_layout == PRESTO_CTX_SLOTS;
+    a.kt = (const float*)k_tree;
+    a.vt = (const float*)v_tree;
+    a.anc = anc;
+    a.n_nodes = n_nodes;
+    a.out = (float*)out;
+    a.part_o = (float*)ws;
+    a.part_ml = nullptr;
+    if (p.splits > 1)
+        a.part_ml = (float2*)((char*)ws +
+                              ((attn_f32_partial_rows(d, p) * d->head_dim * sizeof(float) + 255) & ~(size_t)255));
+    a.n_max = d->n_max;
+    a.hq = d->hq;
+    a.hkv = d->hkv;
+    a.G = p.G;
+    a.W = (d->n_max + 63) / 64;
+    a.row_blocks = p.row_blocks;
+    a.splits = p.splits;
+    a.split_len = p.split_len;
+    a.n_tasks = (int32_t)p.tasks;
+    a.n_blocks = (int32_t)p.blocks;
+    a.scale = d->scale;
+    const dim3 grid((unsigned)p.blocks), block(kF32Waves * kWave);
+    if (d->head_dim == 64)
+        tree_attn_f32_kernel<64><<<grid, block, 0, stream>>>(a);
+    else
+        tree_attn_f32_kernel<128><<<grid, block, 0, stream>>>(a);
+    presto_status st = check_launch("tree_attn_f32_kernel");
+    if (st != PRESTO_OK || p.splits == 1) return st;
+    const dim3 mgrid((unsigned)((p.rows + 3) / 4), (unsigned)(d->batch * d->hkv));
+    if (d->head_dim == 64)
+        tree_attn_f32_merge_kernel<64><<<mgrid, 256, 0, stream>>>(a);
+    else
+        tree_attn_f32_merge_kernel<128><<<mgrid, 256, 0, stream>>>(a);
+    return check_launch("tree_attn_f32_merge_kernel");
 }
 
 presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, const void* k_cache,
@@ -906,18 +1234,9 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
                                     const void* k_tree, const void* v_tree, const uint64_t* anc,
                                     const int32_t* n_nodes, void* out, void* ws,
                                     hipStream_t stream) {
-    if (d->dt == PRESTO_DT_F32) {
-        const unsigned grid = (unsigned)((int64_t)d->batch * d->n_max * d->hq);
-#define PRESTO_F32(DD)                                                                           \
-    tree_attn_f32_kernel<DD><<<grid, kWave, 0, stream>>>(                                        \
-        (const float*)q, (const float*)k_cache, (const float*)v_cache, ctx_offsets,              \
-        d->ctx_layout == PRESTO_CTX_SLOTS,                                                       \
-        (const float*)k_tree, (const float*)v_tree, anc, n_nodes, (float*)out, d->n_max, d->hq, \
-        d->hkv, d->scale)
-        if (d->head_dim == 64) PRESTO_F32(64); else PRESTO_F32(128);
-#undef PRESTO_F32
-        return check_launch("tree_attn_f32_kernel");
-    }
+    if (d->dt == PRESTO_DT_F32)
+        return launch_tree_attention_f32(d, q, k_cache, v_cache, ctx_offsets, k_tree, v_tree, anc, n_nodes, out,
+                                         ws, stream);
     const AttnPlan p = attn_plan(d);
     if (p.splits > 1 && (int64_t)d->batch * d->hkv > 65535)  // the merge's grid.y
         return set_error(PRESTO_ERR_UNSUPPORTED, "tree attention: batch x KV heads %lld above 65535",

@@ -210,3 +210,44 @@ def test_attention_many_ragged_sequences_compact(layout):
         nn = int(n_nodes[s])
         assert _row_errors(got[s, :nn], reff[s, :nn]).max() <= 2e-2, s
         assert not got[s, nn:].any()
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 2, 128), (6, 2, 64), (32, 8, 128), (5, 5, 64)])
+@pytest.mark.parametrize("how", ["split", "no_workspace", "unaligned"])
+def test_attention_f32_blocks(hq, hkv, d, how):
+    """fp32: query rows around a 32-row block, contexts around a 32-key block
+    and around the four waves' share of a split, dead row blocks, no room for
+    split partials, and tensors that are only 4-byte aligned."""
+    rng = np.random.default_rng([hq, hkv, d, len(how)])
+    N, dtype = 65, "f32"
+    ctx = np.array([0, 1, 31, 32, 33, 127, 128, 129, 1500], np.int32)
+    n_nodes = np.array([1, 65, 8, 32, 31, 33, 64, 3, 65], np.int32)
+    b = len(ctx)
+    parent = np.full((b, N), -1, np.int32)
+    for s in range(b):
+        for n in range(1, int(n_nodes[s])):
+            parent[s, n] = rng.integers(max(0, n - 5), n)
+    att, anc = _edge_inputs(rng, b, N, hq, hkv, d, ctx, dtype, parent, n_nodes)
+
+    def dev(a):
+        if how != "unaligned":
+            return to_dev(a, dtype)
+        flat = torch.zeros(a.size + 1, dtype=torch.float32, device="cuda")
+        flat[1:] = to_dev(a, dtype).reshape(-1)
+        return flat[1:].view(a.shape)
+
+    kw = {"workspace": torch.empty(4, dtype=torch.uint8, device="cuda")} if how == "no_workspace" else {}
+    print(f"attn f32 hq={hq} hkv={hkv} d={d} {how}", flush=True)
+    out = P.presto_tree_attention(dev(att["q"]), dev(att["k_cache"]), dev(att["v_cache"]),
+                                  to_dev(att["ctx_offsets"]), dev(att["k_tree"]), dev(att["v_tree"]),
+                                  to_dev(anc), to_dev(n_nodes), int(ctx.max()), d ** -0.5, **kw)
+    torch.cuda.synchronize()
+    ref = oracle.tree_attention(dtype, att["q"], att["k_cache"], att["v_cache"], att["ctx_offsets"],
+                                att["k_tree"], att["v_tree"], anc, n_nodes, d ** -0.5)
+    got, reff = to_host(out).astype(np.float64), ref.astype(np.float64)
+    for s in range(b):
+        nn = int(n_nodes[s])
+        # sums of up to 1565 fp32 terms and dot products of d terms, each
+        # within about sqrt(d) 2^-24 of its magnitude: a few 1e-6
+        assert _row_errors(got[s, :nn], reff[s, :nn]).max() <= 1e-5, s
+        assert not got[s, nn:].any()
