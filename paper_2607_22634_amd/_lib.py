@@ -142,8 +142,12 @@ def _ptr(t) -> int | None:
 
 
 def _stream(stream) -> int | None:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    # the current device's current stream as its handle, without the Stream
+    # object that torch.cuda.current_stream() builds: 0.3 us instead of 2.6,
+    # of about 9 a call of one kernel took on the host
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _dt(t: torch.Tensor) -> int:
