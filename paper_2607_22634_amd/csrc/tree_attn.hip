@@ -75,7 +75,10 @@ struct AttnArgs {
     int32_t batch, n_max, hq, hkv, G, W;
     int32_t row_tiles, rows_per_tile, splits, split_len;  // rows_per_tile: a multiple of 32, <= 256
     int32_t n_tasks, n_blocks;
-    int32_t compact;  // tasks dealt over the (sequence, split) pairs that hold keys
+    // shares > 0: the key tiles of all sequences together are cut into that
+    // many equal shares (see TileShares); the partials are then [slot, g, row,
+    // D] and [g, row, slot], slot = share + sequence < n_slots
+    int32_t shares, n_slots;
     float scale_log2;  // scale * log2(e)
 };
 
@@ -91,6 +94,47 @@ __device__ __forceinline__ CtxSpan ctx_span(const int32_t* off, int b, int slots
 
 __device__ __forceinline__ int clamp_nodes(int nn, int n_max) {
     return nn < 1 ? 1 : (nn > n_max ? n_max : nn);
+}
+
+// Ragged batches: the key tiles of all sequences in a row (each sequence led by
+// kLeadTiles of them that stand for a workgroup's start on it: query
+// fragments, the first tiles' arrival, the partial's store) cut into equal
+// shares, the first V % shares one tile longer.  A share holds part of one
+// sequence, or the end of one, whole ones and the start of another; it and the
+// next sequence never advance together past a boundary, so share + sequence
+// numbers the parts.
+constexpr int kLeadTiles = 3;
+struct TileShares {
+    int q, r;
+    __device__ __forceinline__ TileShares(int total, int shares) : q(total / shares), r(total % shares) {}
+    __device__ __forceinline__ int begin(int c) const { return c * q + min(c, r); }
+    __device__ __forceinline__ int of(int tile) const {
+        const int longer = r * (q + 1);
+        return tile < longer ? tile / (q + 1) : r + (tile - longer) / max(q, 1);
+    }
+};
+// (lead and key) tiles of sequence bb, 0 past the batch
+__device__ __forceinline__ int share_tiles(const AttnArgs& a, int bb) {
+    if (bb >= a.batch) return 0;
+    const int keys = ctx_span(a.ctx_off, bb, a.ctx_slots).ctx + clamp_nodes(a.n_nodes[bb], a.n_max);
+    return (keys + kKeyTile - 1) / kKeyTile + kLeadTiles;
+}
+__device__ __forceinline__ int wave_prefix_dpp(int v) {
+    uint32_t x = (uint32_t)v;
+    x += dpp_u32<0x111>(0u, x);        // row_shr:1
+    x += dpp_u32<0x112>(0u, x);        // row_shr:2
+    x += dpp_u32<0x114>(0u, x);        // row_shr:4
+    x += dpp_u32<0x118>(0u, x);        // row_shr:8
+    x += dpp_u32<0x142, 0xa>(0u, x);   // row_bcast:15
+    x += dpp_u32<0x143, 0xc>(0u, x);   // row_bcast:31
+    return (int)x;
+}
+// All tiles of the batch (every wave computes it for itself).
+__device__ __forceinline__ int share_total(const AttnArgs& a) {
+    int total = 0;
+    for (int b0 = 0; b0 < a.batch; b0 += kWave)
+        total += __builtin_amdgcn_readlane(wave_prefix_dpp(share_tiles(a, b0 + lane_id())), kWave - 1);
+    return total;
 }
 
 // Blocks are dealt to the 8 XCDs round-robin; renumber them so that
@@ -141,7 +185,9 @@ struct AttnLds {
     static constexpr int kV = kRing * kTile;                 // start of the V tiles
 };
 
-template <int D>
+// SHARES: a ragged batch cut into equal shares of key tiles (an instantiation
+// of its own: the loop over a share's sequences costs the dense key loop 9%).
+template <int D, bool SHARES>
 __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(AttnArgs a) {
     constexpr int KS = D / 16;                 // S^T contraction steps over the head dimension
     constexpr int DB = D / 32;                 // 32-wide blocks of the output head dimension
@@ -159,69 +205,23 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     // of at most kMaxAncWords words; with the ring this is 160 KB at D = 128
     __shared__ uint64_t s_anc[ROWS * kMaxAncWords];
 
-    int task, split, g, b;
-    if (a.compact) {
-        // task = ((pair * hkv) + g) * row_tiles + rt, pair = the index of
-        // (sequence b, split) among the splits the sequences actually have,
-        // in sequence order.  Every wave counts the pairs itself, then deals
-        // the tasks over the XCDs as in the dense case, but over the tasks
-        // that exist (the grid is an upper bound).
-        const int lane0 = lane_id();
-        auto splits_of = [&](int bb) {
-            if (bb >= a.batch) return 0;
-            const int kb = ctx_span(a.ctx_off, bb, a.ctx_slots).ctx + clamp_nodes(a.n_nodes[bb], a.n_max);
-            return (kb + a.split_len - 1) / a.split_len;
-        };
-        int pairs = 0;
-        for (int b0 = 0; b0 < a.batch; b0 += kWave) {
-            const int incl = wave_prefix_sum_i32(splits_of(b0 + lane0));
-            pairs += __builtin_amdgcn_readlane(incl, kWave - 1);
-        }
-        const int n_tasks = pairs * a.hkv * a.row_tiles;
-        const int n_blocks = (n_tasks + 7) / 8 * 8;
-        if ((int)blockIdx.x >= n_blocks) return;
-        task = xcd_task(blockIdx.x, n_blocks);
-        if (task >= n_tasks) return;
-        g = (task / a.row_tiles) % a.hkv;
-        const int item = task / a.row_tiles / a.hkv;
-        b = -1;
-        split = 0;
-        int base = 0;
-        for (int b0 = 0; b0 < a.batch; b0 += kWave) {
-            const int ns = splits_of(b0 + lane0);
-            const int incl = wave_prefix_sum_i32(ns);
-            const uint64_t hit = __ballot(ns > 0 && item >= base + incl - ns && item < base + incl);
-            if (hit) {
-                const int l = __ffsll((unsigned long long)hit) - 1;
-                b = b0 + l;
-                // last split first (see below)
-                split = __builtin_amdgcn_readlane(incl, l) - 1 - (item - base);
-                break;
-            }
-            base += __builtin_amdgcn_readlane(incl, kWave - 1);
-        }
-        if (b < 0) return;
-    } else {
-        task = xcd_task(blockIdx.x, a.n_blocks);
-        if (task >= a.n_tasks) return;
-        // task = ((b * splits + split') * hkv + g) * row_tiles + rt with the
-        // splits in reverse (split' = 0 is the last split): the XCDs start
-        // their workgroups a few microseconds apart in XCD order, and the
-        // last split, which holds the tree keys and their masks and so runs
-        // longest, then lands on the XCDs that start first.
-        g = (task / a.row_tiles) % a.hkv;
-        split = a.splits - 1 - (task / a.row_tiles / a.hkv) % a.splits;
-        b = task / a.row_tiles / a.hkv / a.splits;
-    }
+    const int task = xcd_task(blockIdx.x, a.n_blocks);
+    if (task >= a.n_tasks) return;
     const int rt = task % a.row_tiles;
+    const int g = (task / a.row_tiles) % a.hkv;
 
+    // One range of keys [key0, key1) (key1 cut at the sequence's end) of
+    // sequence b: the workgroup's rows against them.  Partials go to rows
+    // part_row + rho, their (m, l) to part_ml[ml_row + rho * ml_stride].
+    auto segment = [&](int b, int key0, int key1, int64_t part_row, int64_t ml_row, int ml_stride)
+                       __attribute__((always_inline)) {
     const CtxSpan cs = ctx_span(a.ctx_off, b, a.ctx_slots);
     const int c0 = cs.c0, ctx = cs.ctx;
     const int nn = clamp_nodes(a.n_nodes[b], a.n_max);
     const int keys = ctx + nn;
-    const int k_begin = split * a.split_len;
+    const int k_begin = key0;
     if (k_begin >= keys) return;  // nothing of this sequence in this split
-    const int k_end = min(keys, k_begin + a.split_len);
+    const int k_end = min(keys, key1);
     const int ntiles = (k_end - k_begin + kKeyTile - 1) / kKeyTile;
     const int nblocks = (k_end - k_begin + 31) / 32;
     const int live_rows = a.G * nn;
@@ -633,7 +633,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     // ---- epilogue: lane holds row l32, d = db*32 + 8(i/4) + 4h + i%4
     if (rho >= all_rows) return;
     const float l = l_run;  // whole-row sum
-    if (a.splits == 1) {
+    if (!SHARES && a.splits == 1) {
         uint16_t* op = a.out + (((int64_t)b * a.n_max + qn) * a.hq + g * a.G + qh) * D;
         const float inv = (rho < live_rows && l > 0.f) ? 1.f / l : 0.f;
 #pragma unroll
@@ -647,13 +647,9 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
             }
     } else {
         // normalised here, so bf16 holds it to the output's own precision
-        // output [b, g, split, row] (a workgroup's rows are contiguous: whole
-        // lines); (m, l) [b, g, row, split] (the merge reads a row's splits
-        // side by side)
-        const int64_t bg = (int64_t)b * a.hkv + g;
-        const int64_t pr = (bg * a.splits + split) * all_rows + rho;
-        const int64_t pm = (bg * all_rows + rho) * a.splits + split;
-        uint16_t* po = a.part_o + pr * D;
+        // (a workgroup's rows are contiguous: whole lines; the merge reads a
+        // row's (m, l) pairs side by side)
+        uint16_t* po = a.part_o + (part_row + rho) * D;
         const float inv = l > 0.f ? 1.f / l : 0.f;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -664,7 +660,55 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
                     make_uint2(pack_bf16x2(o[db][4 * q4] * inv, o[db][4 * q4 + 1] * inv),
                                pack_bf16x2(o[db][4 * q4 + 2] * inv, o[db][4 * q4 + 3] * inv));
             }
-        if (h == 0) a.part_ml[pm] = make_float2(l > 0.f ? m : -INFINITY, l);
+        if (h == 0) a.part_ml[ml_row + (int64_t)rho * ml_stride] = make_float2(l > 0.f ? m : -INFINITY, l);
+    }
+    };
+
+    const int all = a.G * a.n_max;
+    const int item = task / a.row_tiles / a.hkv;
+    if constexpr (!SHARES) {
+        // task = ((b * splits + split') * hkv + g) * row_tiles + rt with the
+        // splits in reverse (split' = 0 is the last split): the XCDs start
+        // their workgroups a few microseconds apart in XCD order, and the
+        // last split, which holds the tree keys and their masks and so runs
+        // longest, then lands on the XCDs that start first.
+        const int split = a.splits - 1 - item % a.splits;
+        const int b = item / a.splits;
+        const int64_t bg = (int64_t)b * a.hkv + g;
+        segment(b, split * a.split_len, (split + 1) * a.split_len, (bg * a.splits + split) * all,
+                bg * all * a.splits + split, a.splits);
+        return;
+    }
+    // task = (share * hkv + g) * row_tiles + rt
+    const TileShares sh(share_total(a), a.shares);
+    int from = sh.begin(item);
+    const int to = sh.begin(item + 1);
+    if (from >= to) return;
+    int b = -1, base = 0;  // the sequence and its first tile
+    for (int b0 = 0; b0 < a.batch && b < 0; b0 += kWave) {
+        const int n = share_tiles(a, b0 + lane_id()), incl = wave_prefix_dpp(n);
+        const uint64_t hit = __ballot(base + incl > from);
+        if (hit) {
+            const int l = __ffsll((unsigned long long)hit) - 1;
+            b = b0 + l;
+            base += __builtin_amdgcn_readlane(incl - n, l);
+        } else {
+            base += __builtin_amdgcn_readlane(incl, kWave - 1);
+        }
+    }
+    if (b < 0) return;
+    while (true) {
+        const int tiles = __builtin_amdgcn_readfirstlane(share_tiles(a, b));
+        const int slot = item + b;
+        const int t0 = max(from - base - kLeadTiles, 0), t1 = min(to - base, tiles) - kLeadTiles;
+        if (t1 > t0)
+            segment(b, t0 * kKeyTile, t1 * kKeyTile, ((int64_t)slot * a.hkv + g) * all,
+                    (int64_t)g * all * a.n_slots + slot, a.n_slots);
+        base += tiles;
+        if (base >= to) return;
+        from = base;
+        ++b;
+        __syncthreads();  // the tile ring and the ancestor rows are free again
     }
 }
 
@@ -690,12 +734,12 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
     const int bg = (int)blockIdx.y;
     const int b = bg / a.hkv, g = bg - b * a.hkv;
     const int n = rho / a.G, hh = rho - n * a.G;
-    // split s of this row: ((b, g) * splits + s) * rows + rho; every
-    // offset within one (b, g) block of partials fits 32 bits
-    const uint16_t* po = a.part_o + ((int64_t)bg * a.splits * rows_g + rho) * D + lane * PER;
-    const uint32_t sstride = (uint32_t)rows_g * D;  // elements from one split to the next
+    const uint16_t* po;  // this lane's dims of the row's first partial
+    int64_t sstride;     // elements from one partial of the row to the next
+    const float2* mlp;   // the row's (m, l) pairs
+    int nsplit, nn;
     auto load_out = [&](int sp, float (&v)[PER]) {
-        const uint16_t* q = po + (uint32_t)sp * sstride;
+        const uint16_t* q = po + (int64_t)sp * sstride;
         if constexpr (PER == 1) {
             v[0] = bf16_to_f(*q);
         } else {
@@ -704,42 +748,77 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
             v[1] = bf16hi(w2);
         }
     };
-    // everything independent is requested at once
-    const int nn_raw = a.n_nodes[b];
-    const CtxSpan cs = ctx_span(a.ctx_off, b, a.ctx_slots);
     float2 ml = make_float2(-INFINITY, 0.f);
-    if (lane < a.splits) ml = a.part_ml[((int64_t)bg * rows_g + rho) * a.splits + lane];
     float v0[kMergeUnroll][PER];
+    if (a.shares == 0) {
+        // split s of this row: ((b, g) * splits + s) * rows + rho; everything
+        // independent is requested at once
+        po = a.part_o + ((int64_t)bg * a.splits * rows_g + rho) * D + lane * PER;
+        sstride = (int64_t)rows_g * D;
+        mlp = a.part_ml + ((int64_t)bg * rows_g + rho) * a.splits;
+        const int nn_raw = a.n_nodes[b];
+        const CtxSpan cs = ctx_span(a.ctx_off, b, a.ctx_slots);
+        if (lane < a.splits) ml = mlp[lane];
 #pragma unroll
-    for (int u = 0; u < kMergeUnroll; ++u) load_out(min(u, a.splits - 1), v0[u]);
-
-    const int nn = clamp_nodes(nn_raw, a.n_max);
-    const int keys = cs.ctx + nn;
-    const int nsplit = min(a.splits, (keys + a.split_len - 1) / a.split_len);
+        for (int u = 0; u < kMergeUnroll; ++u) load_out(min(u, a.splits - 1), v0[u]);
+        nn = clamp_nodes(nn_raw, a.n_max);
+        nsplit = min(a.splits, (cs.ctx + nn + a.split_len - 1) / a.split_len);
+    } else {
+        // the sequence's key tiles lie in shares first .. last
+        nn = clamp_nodes(a.n_nodes[b], a.n_max);
+        int before = 0, total = 0;
+        for (int b0 = 0; b0 < a.batch; b0 += kWave) {
+            const int t = share_tiles(a, b0 + lane), incl = wave_prefix_dpp(t);
+            if (b >= b0 && b < b0 + kWave) before = total + __builtin_amdgcn_readlane(incl - t, b - b0);
+            total += __builtin_amdgcn_readlane(incl, kWave - 1);
+        }
+        const TileShares sh(total, a.shares);
+        const int first = sh.of(before + kLeadTiles);
+        nsplit = sh.of(before + share_tiles(a, b) - 1) - first + 1;
+        const int slot = first + b;
+        po = a.part_o + (((int64_t)slot * a.hkv + g) * rows_g + rho) * D + lane * PER;
+        sstride = (int64_t)a.hkv * rows_g * D;
+        mlp = a.part_ml + ((int64_t)g * rows_g + rho) * a.n_slots + slot;
+        if (lane < nsplit) ml = mlp[lane];
+#pragma unroll
+        for (int u = 0; u < kMergeUnroll; ++u) load_out(min(u, nsplit - 1), v0[u]);
+    }
     uint16_t* op = a.out + (((int64_t)b * a.n_max + n) * a.hq + g * a.G + hh) * D + lane * PER;
     float acc[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) acc[e] = 0.f;
     if (rho < a.G * nn) {
         if (lane >= nsplit) ml = make_float2(-INFINITY, 0.f);
-        const float M = wave_max_f32_dpp(ml.x);
-        const float wl = ml.x == -INFINITY ? 0.f : exp2f(ml.x - M) * ml.y;  // weight of split `lane`
-        const float L = wave_sum_f32_dpp(wl);
-        auto add = [&](int sp, const float (&v)[PER]) {
-            const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wl), sp));
+        float M = -INFINITY, L = 0.f;
+        // 64 splits at a time (more only with more than 64 shares)
+        for (int c0 = 0; c0 < nsplit; c0 += kWave) {
+            if (c0 > 0) ml = c0 + lane < nsplit ? mlp[c0 + lane] : make_float2(-INFINITY, 0.f);
+            const float Mc = fmaxf(M, wave_max_f32_dpp(ml.x));
+            const float old = M == -INFINITY ? 0.f : exp2f(M - Mc);
+            const float wl = ml.x == -INFINITY ? 0.f : exp2f(ml.x - Mc) * ml.y;  // weight of split `lane`
+            L = L * old + wave_sum_f32_dpp(wl);
+            M = Mc;
 #pragma unroll
-            for (int e = 0; e < PER; ++e) acc[e] += w * v[e];
-        };
+            for (int e = 0; e < PER; ++e) acc[e] *= old;
+            auto add = [&](int sp, const float (&v)[PER]) {
+                const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wl), sp - c0));
 #pragma unroll
-        for (int u = 0; u < kMergeUnroll; ++u)
-            if (u < nsplit) add(u, v0[u]);
-        for (int s0 = kMergeUnroll; s0 < nsplit; s0 += kMergeUnroll) {
-            float v[kMergeUnroll][PER];
+                for (int e = 0; e < PER; ++e) acc[e] += w * v[e];
+            };
+            const int end = min(nsplit, c0 + kWave);
+            for (int s0 = c0; s0 < end; s0 += kMergeUnroll) {
+                float v[kMergeUnroll][PER];
 #pragma unroll
-            for (int u = 0; u < kMergeUnroll; ++u) load_out(min(s0 + u, nsplit - 1), v[u]);
+                for (int u = 0; u < kMergeUnroll; ++u) {
+                    if (s0 > 0) load_out(min(s0 + u, end - 1), v[u]);
+                    else
 #pragma unroll
-            for (int u = 0; u < kMergeUnroll; ++u)
-                if (s0 + u < nsplit) add(s0 + u, v[u]);
+                        for (int e = 0; e < PER; ++e) v[u][e] = v0[u][e];
+                }
+#pragma unroll
+                for (int u = 0; u < kMergeUnroll; ++u)
+                    if (s0 + u < end) add(s0 + u, v[u]);
+            }
         }
         const float inv = L > 0.f ? 1.f / L : 0.f;
 #pragma unroll
@@ -1062,9 +1141,14 @@ namespace presto_host {
 using namespace presto;
 
 struct AttnPlan {
-    int G, rows, row_tiles, rows_per_tile, waves, rb, splits, split_len;
-    bool compact;
+    int G, rows, row_tiles, rows_per_tile, waves, splits, split_len;
+    int shares, n_slots;  // shares > 0: equal shares of a ragged batch's key tiles
     int64_t tasks, blocks;
+    bool merged() const { return shares > 0 || splits > 1; }
+    // query rows that leave a partial
+    size_t partial_rows(const presto_attn_desc* d) const {
+        return (size_t)(shares > 0 ? n_slots : d->batch * (int64_t)splits) * d->hkv * rows;
+    }
 };
 
 static AttnPlan attn_plan(const presto_attn_desc* d) {
@@ -1081,26 +1165,21 @@ static AttnPlan attn_plan(const presto_attn_desc* d) {
     // + about 3 for a workgroup's prologue) plus the merge, whose partials
     // (2 D + 8 bytes per query row and split, written and read back, about
     // 4 MB per key-block time) grow with the split count
-    // With ragged contexts and the caller's total, the workgroups are dealt
-    // over the (sequence, split) pairs that exist (about total/len + batch/2
-    // of them) rather than batch x splits of the longest sequence.
     const int64_t per_pair = (int64_t)d->hkv * p.row_tiles;  // workgroups per (sequence, split)
     const int keys = d->max_ctx + d->n_max;                  // the longest sequence
-    p.compact = d->batch > 1 && d->total_ctx > 0 && d->total_ctx < (int64_t)d->batch * d->max_ctx;
-    const double total_keys = (double)d->total_ctx + (double)d->batch * d->n_max;
     const int max_splits = (keys + 127) / 128;
+    const double row_bytes = 2.0 * d->head_dim + 8.0;
     double best_cost = 1e30;
+    p.shares = p.n_slots = 0;
     p.splits = 1;
     p.split_len = (keys + kKeyTile - 1) / kKeyTile * kKeyTile;
     for (int s = 1; s <= kWave && s <= max_splits; ++s) {  // the merge gives each split a lane
         int len = (keys + s - 1) / s;
         len = (len + kKeyTile - 1) / kKeyTile * kKeyTile;
         const int se = (keys + len - 1) / len;
-        const double pairs = p.compact ? fmin((double)d->batch * se, total_keys / len + 0.5 * d->batch)
-                                       : (double)d->batch * se;
+        const double pairs = (double)d->batch * se;
         const double rounds = ceil(pairs * per_pair / 256.0);
-        const double merge_bytes =
-            se > 1 ? 2.0 * d->hkv * p.rows * pairs * (2.0 * d->head_dim + 8.0) : 0.0;
+        const double merge_bytes = se > 1 ? 2.0 * d->hkv * p.rows * pairs * row_bytes : 0.0;
         const double cost = rounds * ((len + 31) / 32 + 3) + merge_bytes / 4.0e6;
         if (cost < best_cost - 1e-9) {
             best_cost = cost;
@@ -1108,7 +1187,29 @@ static AttnPlan attn_plan(const presto_attn_desc* d) {
             p.split_len = len;
         }
     }
-    p.tasks = (int64_t)d->batch * p.splits * per_pair;  // in compact mode an upper bound
+    p.tasks = (int64_t)d->batch * p.splits * per_pair;
+    // Ragged contexts whose total the caller knows: equal shares of all key
+    // tiles instead, one per workgroup of a (KV head, row tile), so that no
+    // workgroup waits for a longer one (16 contexts of 1024 .. 8192 keys, 33
+    // nodes: SHARES_NOW).  A few row tiles only: with more than 128 workgroups
+    // per share there is no choice of their number left.
+    if (d->batch > 1 && d->total_ctx > 0 && d->total_ctx < (int64_t)d->batch * d->max_ctx && per_pair <= 128 &&
+        (int64_t)d->batch * d->hkv <= 65535) {
+        const double tiles = ((double)d->total_ctx + (double)d->batch * d->n_max) / kKeyTile +
+                             (kLeadTiles + 0.5) * d->batch;
+        best_cost = 1e30;
+        for (int c = 1; c <= 256; ++c) {
+            const double rounds = ceil((double)c * per_pair / 256.0);
+            const double merge_bytes = 2.0 * d->hkv * p.rows * (c + d->batch) * row_bytes;
+            const double cost = rounds * (2.0 * tiles / c + 2.0 * kLeadTiles) + merge_bytes / 4.0e6;
+            if (cost < best_cost - 1e-9) {
+                best_cost = cost;
+                p.shares = c;
+            }
+        }
+        p.n_slots = p.shares + d->batch - 1;
+        p.tasks = p.shares * per_pair;
+    }
     p.blocks = (p.tasks + 7) / 8 * 8;
     // When the whole grid fits one round (one workgroup per CU), the tiles
     // are balanced: the same number of row tiles, each a multiple of 32 rows
@@ -1117,7 +1218,7 @@ static AttnPlan attn_plan(const presto_attn_desc* d) {
     // two waves per SIMD through every key block (about 1 us per block), one
     // of 160 rows one and a quarter (the idle waves share the fifth block's
     // keys), and the 4-row tiles, nearly idle, disappear.
-    if (!p.compact && p.tasks <= 256 && p.row_tiles > 1)
+    if (p.tasks <= 256 && p.row_tiles > 1)
         p.rows_per_tile = kRowsPerWave * ((p.rows + kRowsPerWave * p.row_tiles - 1) / (kRowsPerWave * p.row_tiles));
     return p;
 }
@@ -1175,8 +1276,8 @@ size_t attn_workspace_bytes(const presto_attn_desc* d) {
         return ((prs * d->head_dim * sizeof(float) + 255) & ~(size_t)255) + prs * sizeof(float2) + 256;
     }
     const AttnPlan p = attn_plan(d);
-    if (p.splits <= 1) return 0;
-    const size_t prs = (size_t)d->batch * d->hkv * p.G * d->n_max * p.splits;
+    if (!p.merged()) return 0;
+    const size_t prs = p.partial_rows(d);
     return ((prs * d->head_dim * sizeof(uint16_t) + 255) & ~(size_t)255) + prs * sizeof(float2) + 256;
 }
 
@@ -1238,7 +1339,7 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
         return launch_tree_attention_f32(d, q, k_cache, v_cache, ctx_offsets, k_tree, v_tree, anc, n_nodes, out,
                                          ws, stream);
     const AttnPlan p = attn_plan(d);
-    if (p.splits > 1 && (int64_t)d->batch * d->hkv > 65535)  // the merge's grid.y
+    if (p.merged() && (int64_t)d->batch * d->hkv > 65535)  // the merge's grid.y
         return set_error(PRESTO_ERR_UNSUPPORTED, "tree attention: batch x KV heads %lld above 65535",
                          (long long)d->batch * d->hkv);
     AttnArgs a;
@@ -1253,7 +1354,7 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
     a.n_nodes = n_nodes;
     a.out = (uint16_t*)out;
     {
-        const size_t prs = (size_t)d->batch * d->hkv * p.G * d->n_max * p.splits;
+        const size_t prs = p.partial_rows(d);
         a.part_o = (uint16_t*)ws;
         a.part_ml = (float2*)((char*)ws + ((prs * d->head_dim * sizeof(uint16_t) + 255) & ~(size_t)255));
     }
@@ -1268,16 +1369,24 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
     a.splits = p.splits;
     a.split_len = p.split_len;
     a.n_tasks = (int32_t)p.tasks;
-    a.compact = p.compact ? 1 : 0;
+    a.shares = p.shares;
+    a.n_slots = p.n_slots;
     a.n_blocks = (int32_t)p.blocks;
     a.scale_log2 = d->scale * kLog2e;
     const dim3 block(p.waves * kWave), grid((unsigned)p.blocks);
-    if (d->head_dim == 64)
-        tree_attn_bf16_kernel<64><<<grid, block, 0, stream>>>(a);
-    else
-        tree_attn_bf16_kernel<128><<<grid, block, 0, stream>>>(a);
+    if (p.shares > 0) {
+        if (d->head_dim == 64)
+            tree_attn_bf16_kernel<64, true><<<grid, block, 0, stream>>>(a);
+        else
+            tree_attn_bf16_kernel<128, true><<<grid, block, 0, stream>>>(a);
+    } else {
+        if (d->head_dim == 64)
+            tree_attn_bf16_kernel<64, false><<<grid, block, 0, stream>>>(a);
+        else
+            tree_attn_bf16_kernel<128, false><<<grid, block, 0, stream>>>(a);
+    }
     presto_status st = check_launch("tree_attn_bf16_kernel");
-    if (st != PRESTO_OK || p.splits == 1) return st;
+    if (st != PRESTO_OK || !p.merged()) return st;
     const dim3 mgrid((unsigned)((p.rows + 3) / 4), (unsigned)(d->batch * d->hkv));
     if (d->head_dim == 64)
         tree_attn_merge_kernel<64><<<mgrid, 256, 0, stream>>>(a);
