@@ -79,6 +79,7 @@ struct AttnArgs {
     // many equal shares (see TileShares); the partials are then [slot, g, row,
     // D] and [g, row, slot], slot = share + sequence < n_slots
     int32_t shares, n_slots;
+    int2* slots;  // [batch] first and last slot of each sequence
     float scale_log2;  // scale * log2(e)
 };
 
@@ -108,10 +109,6 @@ struct TileShares {
     int q, r;
     __device__ __forceinline__ TileShares(int total, int shares) : q(total / shares), r(total % shares) {}
     __device__ __forceinline__ int begin(int c) const { return c * q + min(c, r); }
-    __device__ __forceinline__ int of(int tile) const {
-        const int longer = r * (q + 1);
-        return tile < longer ? tile / (q + 1) : r + (tile - longer) / max(q, 1);
-    }
 };
 // (lead and key) tiles of sequence bb, 0 past the batch
 __device__ __forceinline__ int share_tiles(const AttnArgs& a, int bb) {
@@ -701,6 +698,11 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
         const int tiles = __builtin_amdgcn_readfirstlane(share_tiles(a, b));
         const int slot = item + b;
         const int t0 = max(from - base - kLeadTiles, 0), t1 = min(to - base, tiles) - kLeadTiles;
+        // the merge's note of the sequence's first and last part
+        if (rt == 0 && g == 0 && t1 > t0 && threadIdx.x == 0) {
+            if (t0 == 0) a.slots[b].x = slot;
+            if (t1 == tiles - kLeadTiles) a.slots[b].y = slot;
+        }
         if (t1 > t0)
             segment(b, t0 * kKeyTile, t1 * kKeyTile, ((int64_t)slot * a.hkv + g) * all,
                     (int64_t)g * all * a.n_slots + slot, a.n_slots);
@@ -712,24 +714,23 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     }
 }
 
-// Merge of the split partials: one wave per query row.  Lane s reads the
-// (m, l) pair of split s (at most 64 splits) and forms its weight
-// l exp2(m - M); the splits' normalised outputs are read in groups of
-// kMergeUnroll.  The pairs and the first group of outputs are requested
-// together with the row's node count and context length, before any of
-// them is known (entries of splits the row does not have are read but
-// never used), so a row with up to kMergeUnroll splits costs one memory
-// round trip.
+// Merge of the split partials.  D / 8 lanes per query row, 8 dims each (a
+// 16-byte load per partial and lane), four or eight rows per wave; every lane
+// weighs its row's splits itself, l exp2(m - M), kMergeUnroll of them with all
+// loads in flight.  Memory latency and the partials' bytes bound it: split by
+// split with one wave per row and 4-byte loads, weights across the lanes, it
+// took 12.9 us for 16 ragged sequences of 33 nodes (three partials per row)
+// and 20.7 us for 4 of 257 nodes (8 partials), 6.6 and 14.3 now.
 constexpr int kMergeUnroll = 8;
 template <int D>
 __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
-    constexpr int PER = D / kWave;  // output dims per lane
-    static_assert(PER == 1 || PER == 2, "head_dim 64 or 128");
-    const int lane = lane_id();
-    // grid: x covers the rows of one (sequence, KV head) four per block, y
-    // the (sequence, KV head) pairs
+    constexpr int LPR = D / 8;          // lanes per row
+    constexpr int RPB = 256 / LPR;      // rows per workgroup
+    // grid: x covers the rows of one (sequence, KV head), y the (sequence, KV
+    // head) pairs
     const int rows_g = a.G * a.n_max;
-    const int rho = (int)blockIdx.x * (blockDim.x / kWave) + (int)threadIdx.x / kWave;
+    const int rho = (int)blockIdx.x * RPB + (int)threadIdx.x / LPR;
+    const int dl = (int)threadIdx.x % LPR;
     if (rho >= rows_g) return;
     const int bg = (int)blockIdx.y;
     const int b = bg / a.hkv, g = bg - b * a.hkv;
@@ -737,99 +738,69 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
     const uint16_t* po;  // this lane's dims of the row's first partial
     int64_t sstride;     // elements from one partial of the row to the next
     const float2* mlp;   // the row's (m, l) pairs
-    int nsplit, nn;
-    auto load_out = [&](int sp, float (&v)[PER]) {
-        const uint16_t* q = po + (int64_t)sp * sstride;
-        if constexpr (PER == 1) {
-            v[0] = bf16_to_f(*q);
-        } else {
-            const uint32_t w2 = *reinterpret_cast<const uint32_t*>(q);
-            v[0] = bf16lo(w2);
-            v[1] = bf16hi(w2);
-        }
-    };
-    float2 ml = make_float2(-INFINITY, 0.f);
-    float v0[kMergeUnroll][PER];
+    int nsplit;
+    const int nn_raw = a.n_nodes[b];
     if (a.shares == 0) {
-        // split s of this row: ((b, g) * splits + s) * rows + rho; everything
-        // independent is requested at once
-        po = a.part_o + ((int64_t)bg * a.splits * rows_g + rho) * D + lane * PER;
+        po = a.part_o + ((int64_t)bg * a.splits * rows_g + rho) * D + dl * 8;
         sstride = (int64_t)rows_g * D;
         mlp = a.part_ml + ((int64_t)bg * rows_g + rho) * a.splits;
-        const int nn_raw = a.n_nodes[b];
-        const CtxSpan cs = ctx_span(a.ctx_off, b, a.ctx_slots);
-        if (lane < a.splits) ml = mlp[lane];
-#pragma unroll
-        for (int u = 0; u < kMergeUnroll; ++u) load_out(min(u, a.splits - 1), v0[u]);
-        nn = clamp_nodes(nn_raw, a.n_max);
-        nsplit = min(a.splits, (cs.ctx + nn + a.split_len - 1) / a.split_len);
+        nsplit = a.splits;  // cut below, once the loads are on their way
     } else {
-        // the sequence's key tiles lie in shares first .. last
-        nn = clamp_nodes(a.n_nodes[b], a.n_max);
-        int before = 0, total = 0;
-        for (int b0 = 0; b0 < a.batch; b0 += kWave) {
-            const int t = share_tiles(a, b0 + lane), incl = wave_prefix_dpp(t);
-            if (b >= b0 && b < b0 + kWave) before = total + __builtin_amdgcn_readlane(incl - t, b - b0);
-            total += __builtin_amdgcn_readlane(incl, kWave - 1);
-        }
-        const TileShares sh(total, a.shares);
-        const int first = sh.of(before + kLeadTiles);
-        nsplit = sh.of(before + share_tiles(a, b) - 1) - first + 1;
-        const int slot = first + b;
-        po = a.part_o + (((int64_t)slot * a.hkv + g) * rows_g + rho) * D + lane * PER;
+        const int2 s = a.slots[b];
+        nsplit = s.y - s.x + 1;
+        po = a.part_o + (((int64_t)s.x * a.hkv + g) * rows_g + rho) * D + dl * 8;
         sstride = (int64_t)a.hkv * rows_g * D;
-        mlp = a.part_ml + ((int64_t)g * rows_g + rho) * a.n_slots + slot;
-        if (lane < nsplit) ml = mlp[lane];
-#pragma unroll
-        for (int u = 0; u < kMergeUnroll; ++u) load_out(min(u, nsplit - 1), v0[u]);
+        mlp = a.part_ml + ((int64_t)g * rows_g + rho) * a.n_slots + s.x;
     }
-    uint16_t* op = a.out + (((int64_t)b * a.n_max + n) * a.hq + g * a.G + hh) * D + lane * PER;
-    float acc[PER];
+    float M = -INFINITY, L = 0.f;
+    float acc[8];
 #pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-    if (rho < a.G * nn) {
-        if (lane >= nsplit) ml = make_float2(-INFINITY, 0.f);
-        float M = -INFINITY, L = 0.f;
-        // 64 splits at a time (more only with more than 64 shares)
-        for (int c0 = 0; c0 < nsplit; c0 += kWave) {
-            if (c0 > 0) ml = c0 + lane < nsplit ? mlp[c0 + lane] : make_float2(-INFINITY, 0.f);
-            const float Mc = fmaxf(M, wave_max_f32_dpp(ml.x));
-            const float old = M == -INFINITY ? 0.f : exp2f(M - Mc);
-            const float wl = ml.x == -INFINITY ? 0.f : exp2f(ml.x - Mc) * ml.y;  // weight of split `lane`
-            L = L * old + wave_sum_f32_dpp(wl);
-            M = Mc;
+    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+    const int last = nsplit - 1;
+    for (int s0 = 0; s0 < nsplit; s0 += kMergeUnroll) {
+        float2 ml[kMergeUnroll];
+        uint4 v[kMergeUnroll];
 #pragma unroll
-            for (int e = 0; e < PER; ++e) acc[e] *= old;
-            auto add = [&](int sp, const float (&v)[PER]) {
-                const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wl), sp - c0));
+        for (int u = 0; u < kMergeUnroll; ++u) {
+            const int sp = min(s0 + u, last);
+            ml[u] = mlp[sp];
+            v[u] = *reinterpret_cast<const uint4*>(po + (int64_t)sp * sstride);
+        }
+        if (s0 == 0 && a.shares == 0) {
+            // splits past the sequence's end left nothing
+            const int keys = ctx_span(a.ctx_off, b, a.ctx_slots).ctx + clamp_nodes(nn_raw, a.n_max);
+            nsplit = min(nsplit, (keys + a.split_len - 1) / a.split_len);
+        }
+        float Mn = M;
 #pragma unroll
-                for (int e = 0; e < PER; ++e) acc[e] += w * v[e];
-            };
-            const int end = min(nsplit, c0 + kWave);
-            for (int s0 = c0; s0 < end; s0 += kMergeUnroll) {
-                float v[kMergeUnroll][PER];
+        for (int u = 0; u < kMergeUnroll; ++u)
+            if (s0 + u < nsplit) Mn = fmaxf(Mn, ml[u].x);
+        const float old = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+        L *= old;
 #pragma unroll
-                for (int u = 0; u < kMergeUnroll; ++u) {
-                    if (s0 > 0) load_out(min(s0 + u, end - 1), v[u]);
-                    else
+        for (int e = 0; e < 8; ++e) acc[e] *= old;
+        M = Mn;
 #pragma unroll
-                        for (int e = 0; e < PER; ++e) v[u][e] = v0[u][e];
+        for (int u = 0; u < kMergeUnroll; ++u) {
+            if (s0 + u < nsplit) {
+                const float w = ml[u].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - Mn) * ml[u].y;
+                L += w;
+                const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc[2 * e] = fmaf(w, bf16lo(x[e]), acc[2 * e]);
+                    acc[2 * e + 1] = fmaf(w, bf16hi(x[e]), acc[2 * e + 1]);
                 }
-#pragma unroll
-                for (int u = 0; u < kMergeUnroll; ++u)
-                    if (s0 + u < end) add(s0 + u, v[u]);
             }
         }
-        const float inv = L > 0.f ? 1.f / L : 0.f;
+    }
+    // rows of padding nodes are zeros
+    const float inv = n < clamp_nodes(nn_raw, a.n_max) && L > 0.f ? 1.f / L : 0.f;
+    uint32_t o[4];
 #pragma unroll
-        for (int e = 0; e < PER; ++e) acc[e] *= inv;
-    }
-    if constexpr (PER == 1) {
-        *op = f_to_bf16(acc[0]);
-    } else {
-        *reinterpret_cast<uint32_t*>(op) =
-            (uint32_t)f_to_bf16(acc[0]) | ((uint32_t)f_to_bf16(acc[1]) << 16);
-    }
+    for (int e = 0; e < 4; ++e) o[e] = inv != 0.f ? pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv) : 0u;
+    uint16_t* op = a.out + (((int64_t)b * a.n_max + n) * a.hq + g * a.G + hh) * D + dl * 8;
+    *reinterpret_cast<uint4*>(op) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
 // fp32 path, on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: exact fp32
@@ -1191,7 +1162,7 @@ static AttnPlan attn_plan(const presto_attn_desc* d) {
     // Ragged contexts whose total the caller knows: equal shares of all key
     // tiles instead, one per workgroup of a (KV head, row tile), so that no
     // workgroup waits for a longer one (16 contexts of 1024 .. 8192 keys, 33
-    // nodes: SHARES_NOW).  A few row tiles only: with more than 128 workgroups
+    // nodes: 97.1 -> 86.5 us per call).  A few row tiles only: with more than 128 workgroups
     // per share there is no choice of their number left.
     if (d->batch > 1 && d->total_ctx > 0 && d->total_ctx < (int64_t)d->batch * d->max_ctx && per_pair <= 128 &&
         (int64_t)d->batch * d->hkv <= 65535) {
@@ -1278,7 +1249,8 @@ size_t attn_workspace_bytes(const presto_attn_desc* d) {
     const AttnPlan p = attn_plan(d);
     if (!p.merged()) return 0;
     const size_t prs = p.partial_rows(d);
-    return ((prs * d->head_dim * sizeof(uint16_t) + 255) & ~(size_t)255) + prs * sizeof(float2) + 256;
+    return ((prs * d->head_dim * sizeof(uint16_t) + 255) & ~(size_t)255) + prs * sizeof(float2) + 256 +
+           (p.shares > 0 ? (size_t)d->batch * sizeof(int2) : 0);
 }
 
 static presto_status launch_tree_attention_f32(const presto_attn_desc* d, const void* q, const void* k_cache,
@@ -1357,6 +1329,7 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
         const size_t prs = p.partial_rows(d);
         a.part_o = (uint16_t*)ws;
         a.part_ml = (float2*)((char*)ws + ((prs * d->head_dim * sizeof(uint16_t) + 255) & ~(size_t)255));
+        a.slots = (int2*)(a.part_ml + prs);
     }
     a.batch = d->batch;
     a.n_max = d->n_max;
@@ -1387,7 +1360,8 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
     }
     presto_status st = check_launch("tree_attn_bf16_kernel");
     if (st != PRESTO_OK || !p.merged()) return st;
-    const dim3 mgrid((unsigned)((p.rows + 3) / 4), (unsigned)(d->batch * d->hkv));
+    const int rows_per_block = 256 / (d->head_dim / 8);
+    const dim3 mgrid((unsigned)((p.rows + rows_per_block - 1) / rows_per_block), (unsigned)(d->batch * d->hkv));
     if (d->head_dim == 64)
         tree_attn_merge_kernel<64><<<mgrid, 256, 0, stream>>>(a);
     else
