@@ -624,8 +624,19 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
                 m = M;
             }
         }
-        if (shared && sidx != 0) return;  // the combined state is wave A-1's
     }
+    // the blocks past the shared one hold padding rows only, which without a
+    // merge are the waves' own to clear
+    if (!SHARES && a.splits == 1 && nshare > 1 && wave >= A) {
+        const int r = rt * RT + wave * kRowsPerWave + l32;
+        if (wave * kRowsPerWave < RT && r < all_rows) {
+            uint16_t* op = a.out + (((int64_t)b * a.n_max + r / a.G) * a.hq + g * a.G + r % a.G) * D;
+#pragma unroll
+            for (int e = 0; e < D / 16; ++e)
+                *reinterpret_cast<uint4*>(op + (2 * e + h) * 8) = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+    if (shared && sidx != 0) return;  // a shared block's combined state is wave A-1's
 
     // ---- epilogue: lane holds row l32, d = db*32 + 8(i/4) + 4h + i%4
     if (rho >= all_rows) return;

@@ -251,3 +251,34 @@ def test_attention_f32_blocks(hq, hkv, d, how):
         # within about sqrt(d) 2^-24 of its magnitude: a few 1e-6
         assert _row_errors(got[s, :nn], reff[s, :nn]).max() <= 1e-5, s
         assert not got[s, nn:].any()
+
+
+@pytest.mark.parametrize("G,N", [(4, 33), (4, 69), (2, 40), (1, 300), (8, 16)])
+def test_attention_padding_rows_without_a_merge(G, N):
+    """Contexts short enough for one split: nobody but the attention kernel
+    itself clears the rows of padding nodes, whichever 32-row block they
+    start in (the waves of a row tile's dead blocks help with its last live
+    one)."""
+    rng = np.random.default_rng([G, N])
+    hkv, d, dtype = 2, 128, "bf16"
+    live = np.unique([1, 2, N // 4, N // 3, N // 2, N - 9, N - 1, N]).astype(np.int32)
+    b = len(live)
+    ctx = rng.integers(0, 40, b).astype(np.int32)
+    parent = np.full((b, N), -1, np.int32)
+    for s in range(b):
+        for n in range(1, int(live[s])):
+            parent[s, n] = rng.integers(max(0, n - 5), n)
+    att, anc = _edge_inputs(rng, b, N, G * hkv, hkv, d, ctx, dtype, parent, live)
+    out = torch.full((b, N, G * hkv, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    print(f"attn padding G={G} N={N} live={live.tolist()}", flush=True)
+    P.presto_tree_attention(to_dev(att["q"], dtype), to_dev(att["k_cache"], dtype), to_dev(att["v_cache"], dtype),
+                            to_dev(att["ctx_offsets"]), to_dev(att["k_tree"], dtype), to_dev(att["v_tree"], dtype),
+                            to_dev(anc), to_dev(live), int(ctx.max()), d ** -0.5, out=out)
+    torch.cuda.synchronize()
+    ref = oracle.tree_attention(dtype, att["q"], att["k_cache"], att["v_cache"], att["ctx_offsets"],
+                                att["k_tree"], att["v_tree"], anc, live, d ** -0.5)
+    got = sy.as_f32(to_host(out), dtype).astype(np.float64)
+    reff = sy.as_f32(ref, dtype).astype(np.float64)
+    for s in range(b):
+        assert _row_errors(got[s, :live[s]], reff[s, :live[s]]).max() <= 2e-2, s
+        assert not got[s, live[s]:].any(), s
