@@ -184,7 +184,17 @@ struct AttnLds {
 
 // SHARES: a ragged batch cut into equal shares of key tiles (an instantiation
 // of its own: the loop over a share's sequences costs the dense key loop 9%).
-template <int D, bool SHARES>
+//
+// TAIL: a tree of 2^i draft nodes has 2^i + 1 rows per query head, so that the
+// query rows often end 1 .. 16 past a multiple of 256.  A row tile of its own
+// for them streams all keys again through a workgroup that computes next to
+// nothing (4 sequences of 32768 keys: 560 us at 256 nodes, 663 at 257); here
+// the last full tile's workgroup takes them along on 16 x 16 MFMAs: of every
+// tile in LDS, waves 0 - 3 (one per SIMD) take sixteen keys each (scores
+// 16x16x32, P V 16x16x16, the query from LDS), about a tenth of a tile's matrix
+// work, and their states are combined at the end: 611 us; 129 nodes 383 -> 333,
+// 32 sequences of 2048 keys and 129 nodes 246 -> 218.
+template <int D, bool SHARES, bool TAIL>
 __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(AttnArgs a) {
     constexpr int KS = D / 16;                 // S^T contraction steps over the head dimension
     constexpr int DB = D / 32;                 // 32-wide blocks of the output head dimension
@@ -196,6 +206,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     constexpr int LPT = kKeyTile * CH / 64 / kAttnWaves;
     constexpr int ROWS_PER_LOAD = 64 / CH;     // key rows covered by one load instruction
     static_assert(LPT >= 1 && LPT * kAttnWaves * 64 == kKeyTile * CH, "tile loads must divide evenly");
+    static_assert(!(SHARES && TAIL), "registers");
     static_assert(AttnLds<D>::kV + kRing * AttnLds<D>::kTile <= 65536 * 2, "ring must fit 128 KB");
     __shared__ __align__(16) char s_kv[2 * kRing * AttnLds<D>::kTile];
     // ancestor rows of this workgroup's nodes: at most ROWS nodes (G = 1)
@@ -241,6 +252,35 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     const int sidx = shared ? wave - (A - 1) : 0;
     const int row0 = rt * RT + (shared ? A - 1 : wave) * kRowsPerWave;  // first query row of this wave
     const bool active = row0 < live_rows;
+    // the rows past the last full tile, when they ride along with it
+    const int tail0 = a.row_tiles * RT;
+    const bool tail_here = TAIL && rt == a.row_tiles - 1;
+    const bool tail_on = tail_here && live_rows > tail0;  // (the tile itself is then fully live)
+    constexpr int TD = D / 16;  // 16-dim blocks of the tail's O^T
+    char* const s_tq = reinterpret_cast<char*>(s_anc + (ROWS * kMaxAncWords - 16 * D / 4));
+    const int t16 = lane & 15, tq = lane >> 4;
+    const int tnode = min((tail0 + t16) / a.G, a.n_max - 1);
+    floatx4 ot[TAIL ? TD : 1];
+    float tm = -INFINITY, tl = 0.f;  // reference (log2 units) and this lane's part of the row sum
+    if constexpr (TAIL) {
+#pragma unroll
+        for (int i = 0; i < TD; ++i) ot[i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+        if (tail_on && tid < 16 * CH) {
+            // scaled queries, chunk c of row r at c ^ r
+            const int r = tid / CH, ck = tid % CH;
+            const int rr = min(tail0 + r, all_rows - 1);
+            const uint4 u = *reinterpret_cast<const uint4*>(
+                a.q + (((int64_t)b * a.n_max + rr / a.G) * a.hq + g * a.G + rr % a.G) * D + ck * 8);
+            const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+            uint32_t x[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                x[j] = pack_bf16x2(__uint_as_float(w[j] << 16) * a.scale_log2,
+                                   __uint_as_float(w[j] & 0xffff0000u) * a.scale_log2);
+            *reinterpret_cast<uint4*>(s_tq + r * D * 2 + ((ck ^ (r & (CH - 1))) * 16)) =
+                make_uint4(x[0], x[1], x[2], x[3]);
+        }
+    }
     const int rho = row0 + l32;  // this lane's query row
     const int qn = rho / a.G, qh = rho - qn * a.G;
     const int node = min(qn, a.n_max - 1);
@@ -268,7 +308,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     // split reaches the tree keys (masks then read LDS, not global memory)
     const int n_first = (rt * RT) / a.G;
     if (k_end > ctx) {
-        const int n_last = min((rt * RT + RT - 1) / a.G, a.n_max - 1);
+        const int n_last = tail_on ? a.n_max - 1 : min((rt * RT + RT - 1) / a.G, a.n_max - 1);
         const int words = (n_last - n_first + 1) * a.W;
         const uint64_t* src = a.anc + ((int64_t)b * a.n_max + n_first) * a.W;
         for (int w = tid; w < words; w += NT) s_anc[w] = src[w];
@@ -347,18 +387,25 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
 
     // per-lane LDS byte addresses of the fragment reads (ring buffer 0,
     // block 0); buffer, block and step offsets are immediates
-    constexpr uint32_t lds0 = 0;  // offsets from s_kv
-    uint32_t kaddr[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-        kaddr[ks] = lds0 + l32 * (D * 2) + ((((2 * ks + h) ^ (l32 & 15)) & (CH - 1)) * 16);
     const int vr = 4 * h + ((lane & 15) >> 2);                  // row within an 8-row group
     const int vc = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);   // chunk within a 4-chunk group
-    uint32_t vaddr[DB];
+    // step 0's address; the others differ in the chunk bits only (an xor)
+    uint32_t k_base = l32 * (D * 2) + ((h ^ (l32 & 15)) & (CH - 1)) * 16;
+    uint32_t v_base = AttnLds<D>::kV + vr * (D * 2) + ((4 * (vr & 3) + vc) & (CH - 1)) * 16 + (lane & 1) * 8;
+    uint32_t kaddr[TAIL ? 1 : KS], vaddr[TAIL ? 1 : DB];
+    if constexpr (!TAIL) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-        vaddr[db] = lds0 + AttnLds<D>::kV + vr * (D * 2) + (((4 * (db ^ (vr & 3))) + vc) & (CH - 1)) * 16 +
-                    (lane & 1) * 8;
+        for (int ks = 0; ks < KS; ++ks) kaddr[ks] = k_base ^ (ks << 5);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) vaddr[db] = v_base ^ (db << 6);
+    }
+    // with tail rows the registers for all twelve are missing: formed anew
+    // per read
+    auto k_at = [&](int ks) __attribute__((always_inline)) { return TAIL ? k_base ^ (ks << 5) : kaddr[TAIL ? 0 : ks]; };
+    auto v_at = [&](int db) __attribute__((always_inline)) { return TAIL ? v_base ^ (db << 6) : vaddr[TAIL ? 0 : db]; };
+    auto fresh = [&]() __attribute__((always_inline)) {
+        if constexpr (TAIL) asm volatile("" : "+v"(k_base), "+v"(v_base));
+    };
 
     auto row_max = [&](const floatx16& S) {
         float mx = S[0];
@@ -421,7 +468,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
         constexpr int buf = decltype(bufc)::value;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const uint4 u = *reinterpret_cast<const uint4*>(s_kv + kaddr[ks] + buf * AttnLds<D>::kTile +
+            const uint4 u = *reinterpret_cast<const uint4*>(s_kv + k_at(ks) + buf * AttnLds<D>::kTile +
                                                              blk * 32 * D * 2);
             Sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, u), qf[ks],
                                                          ks == 0 ? negm : Sx, 0, 0, 0);
@@ -468,6 +515,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     // K of block i+2 (tile t+1) in ring buffer bk
     auto step = [&](auto bvc, auto bkc, int i, int q) {
         constexpr int bv = decltype(bvc)::value, bk = decltype(bkc)::value;
+        fresh();
         const bool more = i + 1 < nblocks;
         if (more && masked(i + 1)) apply_mask(Sa, j0_of(i + 1));
         const int kblk = (i + 2) % kBlocksPerTile;
@@ -479,14 +527,14 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
                 __builtin_bit_cast(bf16x8, make_uint4(Pp[4 * st], Pp[4 * st + 1], Pp[4 * st + 2], Pp[4 * st + 3]));
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                const uint32_t v0 = vaddr[db] + bv * AttnLds<D>::kTile + q * 32 * D * 2 + st * 16 * D * 2;
+                const uint32_t v0 = v_at(db) + bv * AttnLds<D>::kTile + q * 32 * D * 2 + st * 16 * D * 2;
                 const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(s_kv + v0));
                 const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(s_kv + v0 + 8 * D * 2));
                 const uint2 ul = __builtin_bit_cast(uint2, lo), uh = __builtin_bit_cast(uint2, hi);
                 const bf16x8 va = __builtin_bit_cast(bf16x8, make_uint4(ul.x, ul.y, uh.x, uh.y));
                 o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb, o[db], 0, 0, 0);
                 const int ks = st * DB + db;
-                const uint4 u = *reinterpret_cast<const uint4*>(s_kv + kaddr[ks] + bk * AttnLds<D>::kTile +
+                const uint4 u = *reinterpret_cast<const uint4*>(s_kv + k_at(ks) + bk * AttnLds<D>::kTile +
                                                                  kblk * 32 * D * 2);
                 Sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, u), qf[ks],
                                                              ks == 0 ? negm : Sb, 0, 0, 0);
@@ -517,7 +565,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
                 __builtin_bit_cast(bf16x8, make_uint4(P[4 * st], P[4 * st + 1], P[4 * st + 2], P[4 * st + 3]));
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                const uint32_t v0 = vaddr[db] + bv * AttnLds<D>::kTile + q * 32 * D * 2 + st * 16 * D * 2;
+                const uint32_t v0 = v_at(db) + bv * AttnLds<D>::kTile + q * 32 * D * 2 + st * 16 * D * 2;
                 const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(s_kv + v0));
                 const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(s_kv + v0 + 8 * D * 2));
                 const uint2 ul = __builtin_bit_cast(uint2, lo), uh = __builtin_bit_cast(uint2, hi);
@@ -541,6 +589,63 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
         l_run += ls;
         pv(bvc, q, P);
     };
+    // the tail rows against sixteen keys of tile t (ring buffer bv): lane
+    // (t16, tq) holds row t16 and keys 4 tq .. 4 tq + 3 of wave's sixteen
+    auto tail_step = [&](auto bvc, int t) __attribute__((always_inline)) {
+        constexpr int bv = decltype(bvc)::value;
+        const int j0 = k_begin + t * kKeyTile + wave * 16;
+        if (j0 >= k_end) return;
+        const uint32_t toff = (uint32_t)((tq ^ t16) & (CH - 1)) * 16;
+        const uint32_t ka = (uint32_t)(wave * 16 + t16) * (D * 2) + bv * AttnLds<D>::kTile;
+        floatx4 S = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ++ks) {
+            const uint4 kf = *reinterpret_cast<const uint4*>(s_kv + ka + (toff ^ (ks * 64)));
+            const uint4 qv = *reinterpret_cast<const uint4*>(s_tq + t16 * (D * 2) + (toff ^ (ks * 64)));
+            S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf),
+                                                        __builtin_bit_cast(bf16x8, qv), S, 0, 0, 0);
+        }
+        if (j0 + 16 > mask_from) {
+            const uint64_t* arow = &s_anc[(tnode - n_first) * a.W];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int j = j0 + 4 * tq + e, s = j - ctx;
+                const bool vis = j < k_end && (s < 0 || ((arow[max(s, 0) >> 6] >> (s & 63)) & 1ull));
+                S[e] = vis ? S[e] : -INFINITY;
+            }
+        }
+        float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3]));
+        if (__ballot(mx > tm + 8.f)) {
+            // move the row's reference to its maximum over the sixteen keys
+            const auto h16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            mx = fmaxf(__uint_as_float(h16[0]), __uint_as_float(h16[1]));
+            const auto h32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            mx = fmaxf(__uint_as_float(h32[0]), __uint_as_float(h32[1]));
+            const float mn = fmaxf(tm, mx);
+            const float al = tm == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(tm - mn);
+            tm = mn;
+            tl *= al;
+#pragma unroll
+            for (int i = 0; i < TD; ++i) ot[i] *= al;
+        }
+        const float mr = tm == -INFINITY ? 0.f : tm;  // no key visible yet: every term is 0
+        uint32_t P[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            P[e] = pack_bf16x2(__builtin_amdgcn_exp2f(S[2 * e] - mr), __builtin_amdgcn_exp2f(S[2 * e + 1] - mr));
+            tl = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, P[e]), ones, tl, false);
+        }
+        const short4_t pb = __builtin_bit_cast(short4_t, make_uint2(P[0], P[1]));
+        const int x = t16 >> 2;
+        const uint32_t va = AttnLds<D>::kV + bv * AttnLds<D>::kTile +
+                            (uint32_t)(wave * 16 + 4 * tq + x) * (D * 2) + (t16 & 1) * 8;
+        const uint32_t vc0 = (uint32_t)(((t16 & 3) >> 1) ^ ((4 * x) & (CH - 1))) * 16;
+#pragma unroll
+        for (int i = 0; i < TD; ++i) {
+            const short4_t vf = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(s_kv + va + (vc0 ^ (i * 32))));
+            ot[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pb, ot[i], 0, 0, 0);
+        }
+    };
     // one tile: its two block steps, then the load of tile t+3 into the
     // buffer of tile t-1 (every wave finished it before the last barrier),
     // and the wait for tile t+2 before the barrier
@@ -559,6 +664,8 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
                 if (i < nblocks && i % nshare == sidx) shared_step(BV{}, i, q);
             }
         }
+        if constexpr (TAIL)
+            if (tail_on && wave < 4) tail_step(BV{}, t);
         PRESTO_WAIT_VM(2 * LPT);
         __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS reads are done
         __builtin_amdgcn_s_barrier();
@@ -625,11 +732,64 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
             }
         }
     }
+
+    // ---- the tail's four states, combined through the (now idle) tile ring
+    if constexpr (TAIL) {
+        if (tail_here) {
+            float* s_to = reinterpret_cast<float*>(s_kv);     // [4][16 rows][D]
+            float* s_tml = s_to + 4 * 16 * D;                 // [4][16 rows] m, then l
+            __syncthreads();  // every wave's loads have landed; the ring is free
+            if (tail_on && wave < 4) {
+                const auto h16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(tl), __float_as_uint(tl), false, false);
+                float ls = __uint_as_float(h16[0]) + __uint_as_float(h16[1]);
+                const auto h32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(ls), __float_as_uint(ls), false, false);
+                ls = __uint_as_float(h32[0]) + __uint_as_float(h32[1]);
+                if (tq == 0) {
+                    s_tml[wave * 16 + t16] = tm;
+                    s_tml[64 + wave * 16 + t16] = ls;
+                }
+#pragma unroll
+                for (int i = 0; i < TD; ++i)
+                    *reinterpret_cast<floatx4*>(&s_to[(wave * 16 + t16) * D + 16 * i + 4 * tq]) = ot[i];
+            }
+            __syncthreads();
+            for (int i = tid; i < 16 * (D / 4); i += NT) {
+                const int r = i / (D / 4), d = i % (D / 4) * 4;
+                const int tr = tail0 + r;
+                if (tr >= all_rows) break;
+                float M = -INFINITY, L = 0.f;
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+                if (tail_on) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) M = fmaxf(M, s_tml[w * 16 + r]);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const float mw = s_tml[w * 16 + r];
+                        const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+                        L += f * s_tml[64 + w * 16 + r];
+                        acc += f * *reinterpret_cast<const floatx4*>(&s_to[(w * 16 + r) * D + d]);
+                    }
+                }
+                const float inv = tr < live_rows && L > 0.f ? 1.f / L : 0.f;
+                acc *= inv;
+                const uint2 o2 = make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
+                if (a.splits == 1) {
+                    uint16_t* op = a.out + (((int64_t)b * a.n_max + tr / a.G) * a.hq + g * a.G + tr % a.G) * D + d;
+                    *reinterpret_cast<uint2*>(op) = o2;
+                } else {
+                    *reinterpret_cast<uint2*>(a.part_o + (part_row + tr) * D + d) = o2;
+                    if (d == 0) a.part_ml[ml_row + (int64_t)tr * ml_stride] = make_float2(L > 0.f ? M : -INFINITY, L);
+                }
+            }
+        }
+    }
+
+    // ---- epilogue: lane holds row l32, d = db*32 + 8(i/4) + 4h + i%4
     // the blocks past the shared one hold padding rows only, which without a
     // merge are the waves' own to clear
     if (!SHARES && a.splits == 1 && nshare > 1 && wave >= A) {
         const int r = rt * RT + wave * kRowsPerWave + l32;
-        if (wave * kRowsPerWave < RT && r < all_rows) {
+        if (wave * kRowsPerWave < RT && r < all_rows && (!TAIL || r < tail0)) {
             uint16_t* op = a.out + (((int64_t)b * a.n_max + r / a.G) * a.hq + g * a.G + r % a.G) * D;
 #pragma unroll
             for (int e = 0; e < D / 16; ++e)
@@ -637,9 +797,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
         }
     }
     if (shared && sidx != 0) return;  // a shared block's combined state is wave A-1's
-
-    // ---- epilogue: lane holds row l32, d = db*32 + 8(i/4) + 4h + i%4
-    if (rho >= all_rows) return;
+    if (rho >= all_rows || (TAIL && rho >= tail0)) return;
     const float l = l_run;  // whole-row sum
     if (!SHARES && a.splits == 1) {
         uint16_t* op = a.out + (((int64_t)b * a.n_max + qn) * a.hq + g * a.G + qh) * D;
@@ -1125,6 +1283,7 @@ using namespace presto;
 struct AttnPlan {
     int G, rows, row_tiles, rows_per_tile, waves, splits, split_len;
     int shares, n_slots;  // shares > 0: equal shares of a ragged batch's key tiles
+    bool tail;            // 1 .. 16 rows past the last full tile, taken along by it
     int64_t tasks, blocks;
     bool merged() const { return shares > 0 || splits > 1; }
     // query rows that leave a partial
@@ -1133,7 +1292,11 @@ struct AttnPlan {
     }
 };
 
-static AttnPlan attn_plan(const presto_attn_desc* d) {
+static bool attn_ragged(const presto_attn_desc* d) {
+    return d->batch > 1 && d->total_ctx > 0 && d->total_ctx < (int64_t)d->batch * d->max_ctx;
+}
+
+static AttnPlan attn_plan_rows(const presto_attn_desc* d, bool tail) {
     AttnPlan p;
     p.G = d->hq / d->hkv;
     p.rows = p.G * d->n_max;
@@ -1141,7 +1304,8 @@ static AttnPlan attn_plan(const presto_attn_desc* d) {
     // waves of two (each K/V fragment read from LDS then feeds two MFMAs)
     p.waves = kAttnWaves;
     p.rows_per_tile = kAttnRows;
-    p.row_tiles = (p.rows + p.rows_per_tile - 1) / p.rows_per_tile;
+    p.tail = tail;
+    p.row_tiles = p.tail ? p.rows / p.rows_per_tile : (p.rows + p.rows_per_tile - 1) / p.rows_per_tile;
     // context splits: one workgroup per CU, so the time in key-block units
     // (about 0.85 us each) is (rounds of workgroups) x (key blocks per split
     // + about 3 for a workgroup's prologue) plus the merge, whose partials
@@ -1170,13 +1334,13 @@ static AttnPlan attn_plan(const presto_attn_desc* d) {
         }
     }
     p.tasks = (int64_t)d->batch * p.splits * per_pair;
+    const bool ragged = attn_ragged(d);
     // Ragged contexts whose total the caller knows: equal shares of all key
     // tiles instead, one per workgroup of a (KV head, row tile), so that no
     // workgroup waits for a longer one (16 contexts of 1024 .. 8192 keys, 33
-    // nodes: 97.1 -> 86.5 us per call).  A few row tiles only: with more than 128 workgroups
-    // per share there is no choice of their number left.
-    if (d->batch > 1 && d->total_ctx > 0 && d->total_ctx < (int64_t)d->batch * d->max_ctx && per_pair <= 128 &&
-        (int64_t)d->batch * d->hkv <= 65535) {
+    // nodes: 97.1 -> 86.5 us per call).  A few row tiles only: with more than
+    // 128 workgroups per share there is no choice of their number left.
+    if (ragged && per_pair <= 128 && (int64_t)d->batch * d->hkv <= 65535) {
         const double tiles = ((double)d->total_ctx + (double)d->batch * d->n_max) / kKeyTile +
                              (kLeadTiles + 0.5) * d->batch;
         best_cost = 1e30;
@@ -1200,7 +1364,7 @@ static AttnPlan attn_plan(const presto_attn_desc* d) {
     // two waves per SIMD through every key block (about 1 us per block), one
     // of 160 rows one and a quarter (the idle waves share the fifth block's
     // keys), and the 4-row tiles, nearly idle, disappear.
-    if (p.tasks <= 256 && p.row_tiles > 1)
+    if (p.tasks <= 256 && p.row_tiles > 1 && !p.tail)
         p.rows_per_tile = kRowsPerWave * ((p.rows + kRowsPerWave * p.row_tiles - 1) / (kRowsPerWave * p.row_tiles));
     return p;
 }
@@ -1248,6 +1412,19 @@ static AttnF32Plan attn_f32_plan(const presto_attn_desc* d, bool may_split) {
 // part_o bytes (rounded up), then part_ml
 static size_t attn_f32_partial_rows(const presto_attn_desc* d, const AttnF32Plan& p) {
     return (size_t)d->batch * d->hkv * p.rows * p.splits;
+}
+
+// 1 .. 16 query rows past the last full tile ride along with it, unless the
+// tiles of their own come out balanced in one round of short splits, where a
+// workgroup's start and the merge weigh more than the keys read twice (1 x
+// 4096 keys, 65 nodes: 25.3 us balanced, 30.8 riding along; 16 x 4608 keys:
+// 125.7 and 117.2).  G >= 2: the ancestor rows of a tile then leave room for
+// the tail's queries; not with shares: that kernel has no registers left.
+static AttnPlan attn_plan(const presto_attn_desc* d) {
+    const AttnPlan p = attn_plan_rows(d, false);
+    if (p.G < 2 || attn_ragged(d) || p.rows <= kAttnRows || (p.rows - 1) % kAttnRows >= 16) return p;
+    if (p.tasks <= 256 && p.split_len < 1024) return p;
+    return attn_plan_rows(d, true);
 }
 
 size_t attn_workspace_bytes(const presto_attn_desc* d) {
@@ -1358,17 +1535,15 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
     a.n_blocks = (int32_t)p.blocks;
     a.scale_log2 = d->scale * kLog2e;
     const dim3 block(p.waves * kWave), grid((unsigned)p.blocks);
-    if (p.shares > 0) {
+    auto go = [&](auto shares, auto tail) {
         if (d->head_dim == 64)
-            tree_attn_bf16_kernel<64, true><<<grid, block, 0, stream>>>(a);
+            tree_attn_bf16_kernel<64, decltype(shares)::value, decltype(tail)::value><<<grid, block, 0, stream>>>(a);
         else
-            tree_attn_bf16_kernel<128, true><<<grid, block, 0, stream>>>(a);
-    } else {
-        if (d->head_dim == 64)
-            tree_attn_bf16_kernel<64, false><<<grid, block, 0, stream>>>(a);
-        else
-            tree_attn_bf16_kernel<128, false><<<grid, block, 0, stream>>>(a);
-    }
+            tree_attn_bf16_kernel<128, decltype(shares)::value, decltype(tail)::value><<<grid, block, 0, stream>>>(a);
+    };
+    if (p.shares > 0) go(std::true_type{}, std::false_type{});
+    else if (p.tail) go(std::false_type{}, std::true_type{});
+    else go(std::false_type{}, std::false_type{});
     presto_status st = check_launch("tree_attn_bf16_kernel");
     if (st != PRESTO_OK || !p.merged()) return st;
     const int rows_per_block = 256 / (d->head_dim / 8);

@@ -253,6 +253,44 @@ def test_attention_f32_blocks(hq, hkv, d, how):
         assert not got[s, nn:].any()
 
 
+@pytest.mark.parametrize("hq,hkv,d,N", [(32, 8, 128, 65), (32, 8, 128, 68), (32, 8, 128, 69), (8, 2, 64, 129),
+                                        (4, 2, 128, 136), (16, 2, 128, 34), (10, 2, 128, 52), (8, 2, 128, 257),
+                                        (2, 2, 128, 257), (4, 2, 64, 1023)])
+@pytest.mark.parametrize("b", [1, 3])
+def test_attention_rows_past_a_full_tile(hq, hkv, d, N, b):
+    """1 .. 16 query rows past a multiple of 256 ride along with the last full
+    tile (just past 16, and one head per KV head, they get a tile of their
+    own): whole trees, trees that end inside the tail's rows, at the tile's
+    edge and before it, contexts around a 64-key tile and a 16-key group, with
+    one split and with many."""
+    rng = np.random.default_rng([hq, hkv, d, N, b])
+    G, dtype = hq // hkv, "bf16"
+    full = (G * N // 256) * 256 // G  # nodes whose rows lie in full tiles
+    over = min(full + 1, N)
+    for ctx, live in (([0, 15, 16], [N, full, over]), ([4000, 65, 1], [over, N, 3]),
+                      ([63, 130, 700], [N, N, full])):
+        ctx, n_nodes = np.array(ctx[:b], np.int32), np.array(live[:b], np.int32)
+        parent = np.full((b, N), -1, np.int32)
+        for s in range(b):
+            for n in range(1, int(n_nodes[s])):
+                parent[s, n] = rng.integers(max(0, n - 9), n)
+        att, anc = _edge_inputs(rng, b, N, hq, hkv, d, ctx, dtype, parent, n_nodes)
+        print(f"attn tail hq={hq} hkv={hkv} d={d} N={N} ctx={ctx.tolist()} live={n_nodes.tolist()}", flush=True)
+        out = P.presto_tree_attention(
+            to_dev(att["q"], dtype), to_dev(att["k_cache"], dtype), to_dev(att["v_cache"], dtype),
+            to_dev(att["ctx_offsets"]), to_dev(att["k_tree"], dtype), to_dev(att["v_tree"], dtype),
+            to_dev(anc), to_dev(n_nodes), int(ctx.max()), d ** -0.5)
+        torch.cuda.synchronize()
+        ref = oracle.tree_attention(dtype, att["q"], att["k_cache"], att["v_cache"], att["ctx_offsets"],
+                                    att["k_tree"], att["v_tree"], anc, n_nodes, d ** -0.5)
+        got = sy.as_f32(to_host(out), dtype).astype(np.float64)
+        reff = sy.as_f32(ref, dtype).astype(np.float64)
+        for s in range(b):
+            nn = int(n_nodes[s])
+            assert _row_errors(got[s, :nn], reff[s, :nn]).max() <= 2e-2, s
+            assert not got[s, nn:].any()
+
+
 @pytest.mark.parametrize("G,N", [(4, 33), (4, 69), (2, 40), (1, 300), (8, 16)])
 def test_attention_padding_rows_without_a_merge(G, N):
     """Contexts short enough for one split: nobody but the attention kernel
