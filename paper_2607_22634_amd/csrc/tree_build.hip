@@ -87,6 +87,12 @@ __device__ __forceinline__ uint64_t sort8_desc(uint64_t key, int lane) {
     return key;
 }
 
+// Same within this lane's quad (quad_perm rotations by 1, 2, 3).
+__device__ __forceinline__ int quad_count_greater(uint64_t key) {
+    return (dpp_u64<0x39>(0ull, key) > key ? 1 : 0) + (dpp_u64<0x4e>(0ull, key) > key ? 1 : 0) +
+           (dpp_u64<0x93>(0ull, key) > key ? 1 : 0);
+}
+
 // Loads up to U words per lane of src[base ..] (batches of 64 words while
 // fewer than n; indices clamped, so every load is unconditional) into r.
 template <int U>
@@ -247,7 +253,7 @@ __device__ __forceinline__ void stage_tables(const TreeArgs& a, char* lds) {
 
 // Best-first search one node at a time, by one wave: the path of inputs that
 // the level search below cannot bound (its pool overflows on very many equal
-// scores, or candidates of probability 0 have to fill the budget).  Per
+// scores).  Per
 // committed node LDS holds one 8-byte record (parent, rank, depth, S) and its
 // children in commit order; the frontier lives in registers spread over the
 // 64 lanes (SL slots per lane), each slot only (S, packed metadata): a pop is
@@ -297,7 +303,7 @@ __device__ void tree_pop_search(const TreeArgs& a, char* lds) {
         const float sc = Sn + s;
         const uint32_t o = ord32(sc);  // nonzero for every non-NaN score
         const uint64_t key = in ? (((uint64_t)o << 8) | (uint64_t)(255 - lane)) : 0ull;
-        if (k <= 8) {
+        if (k > 4 && k <= 8) {
             // sorted in place: lane p holds the p-th child (key 0 past the
             // last child, which writes the end marker)
             const uint64_t sk = sort8_desc(key, lane);
@@ -311,7 +317,7 @@ __device__ void tree_pop_search(const TreeArgs& a, char* lds) {
         } else {
             // the lanes that are not children all land on the first free
             // position and write the end marker there
-            const int pos = row_count_greater<15>(key);
+            const int pos = k <= 4 ? quad_count_greater(key) : row_count_greater<15>(key);
             if (lane < k && live) {
                 s_kord[n * k + pos] = in ? o : 0u;
                 s_krank[n * k + pos] = (uint8_t)lane;
@@ -559,12 +565,13 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kPoolMax = 8191;  // 13 bits of parent entry
 constexpr int kBins = 512;      // histogram of -S, see score_bin
 
-// Monotone bin of a score: 64 bins per octave of 1 - S, so a bin is 1/64 nat
-// wide near S = 0 and 1/8 nat near S = -10; everything below -255 is in the
+// Monotone bin of a score: 32 bins per octave of 1 - S, so a bin is 1/32 nat
+// wide near S = 0 and 1/4 nat near S = -10; everything below -65535 is in the
 // last one.  score_bin(x) < score_bin(y) implies x > y.
+constexpr int kBinBits = 5;  // bins per octave: 2^kBinBits
 __device__ __forceinline__ uint32_t score_bin(float S) {
-    const uint32_t u = __float_as_uint(fmaxf(1.f - S, 1.f)) >> 17;
-    return min(u - (127u << 6), (uint32_t)(kBins - 1));
+    const uint32_t u = __float_as_uint(fmaxf(1.f - S, 1.f)) >> (23 - kBinBits);
+    return min(u - (127u << kBinBits), (uint32_t)(kBins - 1));
 }
 
 // Inclusive prefix sum over the wave (DPP, no LDS traffic).
@@ -666,15 +673,16 @@ struct Pool {
     }
 };
 
-// fine bins of finish_tree's sort (a power of two, at least the workgroup's threads)
-template <int NT>
-constexpr int kFineBins = NT < 512 ? 512 : NT;
+// Fine bins of finish_tree's sort, at least the workgroup's threads: 512 for
+// the small trees (budget 64: 10.2 us, 11.4 with 1024), 1024 for the others
+// and the beam (budget 512: 27 us, 32 with 512).
+constexpr int kFineMax = 1024;
 
-template <int NT, int KW>
+template <int NT, int NF, int KW>
 __device__ __forceinline__ void init_pool(const TreeArgs& a, const Pool<KW>& P) {
     const int tid = threadIdx.x;
     for (int i = tid; i < kBins; i += NT) P.hist[i] = 0u;
-    for (int i = tid; i < kFineBins<NT>; i += NT) P.fine[i] = 0u;
+    for (int i = tid; i < NF; i += NT) P.fine[i] = 0u;
     if (tid < 64) P.misc[tid] = 0u;
     if (tid == 0) {
         P.rec[0] = make_uint2(__float_as_uint(0.f), 0u);
@@ -685,15 +693,124 @@ __device__ __forceinline__ void init_pool(const TreeArgs& a, const Pool<KW>& P) 
     }
 }
 
+// Drops the entries of bins past J (with all their descendants: an entry's
+// score never exceeds its parent's) and closes the gaps; the parents' indices
+// and the frontier [lo, hi) move along.  Ends with a barrier.
+template <int NT, int KW>
+__device__ __forceinline__ void compact_pool(const Pool<KW>& P, uint32_t J, int& lo, int& hi) {
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    uint32_t* s_wave = P.misc + 40;  // [NT / kWave], past the level counts
+    int n = 1, below_lo = 0;
+    if (tid == 0) P.place[0] = 0;
+    for (int e0 = 1; e0 < hi; e0 += NT) {
+        const int e = e0 + tid;
+        uint2 rec = make_uint2(0u, 0u);
+        typename Pool<KW>::Key key = P.key[0];
+        bool alive = false;
+        if (e < hi) {
+            rec = P.rec[e];
+            key = P.key[e];
+            alive = score_bin(__uint_as_float(rec.x)) <= J;
+        }
+        const uint64_t m = __ballot(alive), ml = __ballot(alive & (e < lo));
+        if (lane == 0) s_wave[wv] = (uint32_t)__popcll(m) | ((uint32_t)__popcll(ml) << 16);
+        __syncthreads();
+        uint32_t off = 0u, all = 0u;
+#pragma unroll
+        for (int w = 0; w < NT / kWave; ++w) {
+            const uint32_t c = s_wave[w];
+            off += w < wv ? c : 0u;
+            all += c;
+        }
+        const int at = n + (int)(off & 0xffffu) + lanes_below(m);
+        if (alive) P.place[e] = (uint16_t)at;
+        __syncthreads();  // this chunk is read; its entries move down, never past it
+        if (alive) {
+            P.rec[at] = make_uint2(rec.x, (rec.y & ~8191u) | P.place[rec.y & 8191u]);
+            P.key[at] = key;
+        }
+        n += (int)(all & 0xffffu);
+        below_lo += (int)(all >> 16);
+    }
+    hi = n;
+    lo = 1 + below_lo;
+    __syncthreads();
+}
+
+// Rows nt + 1 .. budget from prefixes of S = -inf, which follow every finite
+// one, in rank-path order: a depth-first walk of the candidate tree by one
+// wave (every lane the same) that descends through the finite entries (child:
+// the entry of every (entry, rank), 0 if not finite) and takes the -inf
+// children as it meets them, each before its own descendants.  They become
+// entries n .. of the pool.  At most two steps per row; a prefix of S = -inf
+// has all its siblings' descendants tied with it, so the level search cannot
+// bound them.  Returns the non-root rows.
+template <int KW, typename Scores>
+__device__ int fill_below(const TreeArgs& a, const Pool<KW>& P, const uint16_t* child, int n, int nt,
+                          const Scores& scores) {
+    const int D = a.D, k = a.k;
+    uint32_t* stack = P.misc;  // per depth: entry | next rank << 16
+    int d = 0, node = 0, next = 0, rank = 0, prank = 0;
+    bool below = false;  // the node's own S is -inf
+    while (nt < a.budget) {
+        if (d == D || next == k) {
+            if (d == 0) break;
+            --d;
+            const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)stack[d]);
+            node = (int)(s & 0xffffu);
+            next = (int)(s >> 16);
+            const uint2 r = P.rec[node];
+            below = __builtin_amdgcn_readfirstlane((int)r.x) == (int)0xff800000u;
+            const uint32_t y = (uint32_t)__builtin_amdgcn_readfirstlane((int)r.y);
+            rank = (int)(y >> 13) & 15;
+            prank = (int)(y >> 17) & 15;
+            continue;
+        }
+        const int r = next++;
+        int c = below ? 0 : __builtin_amdgcn_readfirstlane((int)child[node * k + r]);
+        const bool finite = c != 0;
+        if (!finite) {
+            if (a.branch < k) {
+                // only the top-`branch` by token score are children
+                const float s = scores(d, prank, rank, r);
+                int sel = 0;
+                for (int j = 0; j < k; ++j) {
+                    const float sj = scores(d, prank, rank, j);
+                    sel += ((sj > s) | ((sj == s) & (j < r))) ? 1 : 0;
+                }
+                if (__builtin_amdgcn_readfirstlane(sel) >= a.branch) continue;
+            }
+            c = n++;
+            ++nt;
+            P.rec[c] = make_uint2(0xff800000u, Pool<KW>::meta(node, r, rank, d + 1));
+            P.place[c] = (uint16_t)nt;
+            P.row[nt] = (uint16_t)c;
+        }
+        stack[d] = (uint32_t)node | ((uint32_t)next << 16);
+        ++d;
+        node = c;
+        next = 0;
+        prank = rank;
+        rank = r;
+        below = !finite;
+    }
+    return nt;
+}
+
 // Places the pool's entries 1 .. n - 1 whose bin is at most the budget-th
 // best entry's and writes the tree: the `budget` best in the total order
 // (parents are among them: an entry never precedes its parent).  A counting
 // sort over fine bins of S, then each entry's place within its bin by
 // comparing it with the bin's few others; a handful of barriers, where
 // comparing all pairs of 1000 entries took about as long as the search.
-template <int NT, int KW>
-__device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const Pool<KW>& P, int n) {
-    constexpr int NF = kFineBins<NT>, PER = NF / NT > 0 ? NF / NT : 1;
+// `fill`: fewer than `budget` entries, and candidates of S = -inf were left
+// out of the pool (fill_below).
+template <int NT, int NF, int KW, typename Scores>
+__device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const Pool<KW>& P, int n,
+                                            const Scores& scores, bool fill) {
+    constexpr int PER = NF / NT;
+    static_assert(PER >= 1 && PER * NT == NF && NF <= kFineMax, "whole bins per thread");
     const int tid = threadIdx.x, lane = lane_id();
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int b = blockIdx.x, k = a.k, N = a.N, W = a.W;
@@ -713,7 +830,7 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const 
 #pragma unroll
         for (int i = 0; i < 8; ++i) last = (v[i] != 0u && 8 * lane + i <= (int)min(J, (uint32_t)kBins - 2)) ? 8 * lane + i : last;
         last = (int)wave_max_u32_dpp((uint32_t)last);
-        inv = 1.f / (__uint_as_float((uint32_t)(last + 1 + (127 << 6)) << 17) - 1.f);
+        inv = 1.f / (__uint_as_float((uint32_t)(last + 1 + (127 << kBinBits)) << (23 - kBinBits)) - 1.f);
     }
     auto fine_bin = [&](float S) {
         const float u = fminf(fmaxf(-S * inv, 0.f), 1.f);
@@ -750,25 +867,51 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const 
         if (score_bin(S) <= J) P.list[P.fine[fine_bin(S)] + P.place[e]] = (uint16_t)e;
     }
     __syncthreads();
-    const int nt = min((int)M, budget);  // non-root rows
+    int nt = min((int)M, budget);  // non-root rows
     for (int t = tid; t < (int)M; t += NT) {
         const int e = P.list[t];
         const float S = P.S(e);
         const int f = fine_bin(S);
         const int q0 = (int)P.fine[f], q1 = (int)P.fine[f + 1];
         int at = q0;
-        for (int q = q0; q < q1; ++q) {
-            const int o = P.list[q];
-            const float So = P.S(o);
-            bool before = So > S;
-            if (So == S && o != e) before = key_less<KW>(P.key[o], P.key[e]);
-            at += before ? 1 : 0;
+        if (q1 - q0 > 1) {
+            // four members of the bin at a time, every read unconditional (a
+            // key read behind the comparison of S made each member of a bin
+            // of 256 equal scores a chain of three LDS round trips)
+            const typename Pool<KW>::Key ke = P.key[e];
+            for (int q = q0; q < q1; q += 4) {
+                int o[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) o[u] = P.list[min(q + u, q1 - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float So = P.S(o[u]);
+                    const bool less = key_less<KW>(P.key[o[u]], ke);
+                    at += ((q + u < q1) & ((So > S) | ((So == S) & less))) ? 1 : 0;
+                }
+            }
         }
         P.place[e] = (uint16_t)(at + 1);
         if (at < nt) P.row[at + 1] = (uint16_t)e;
     }
     if (tid == 0) P.place[0] = 0;
     __syncthreads();
+    if (fill) {
+        uint16_t* child = reinterpret_cast<uint16_t*>(P.key);  // the keys have done their part
+        for (int i = tid; i < n * k; i += NT) child[i] = 0;
+        __syncthreads();
+        for (int e = 1 + tid; e < n; e += NT) {
+            const uint32_t y = P.rec[e].y;
+            child[(y & 8191u) * k + ((y >> 13) & 15u)] = (uint16_t)e;
+        }
+        __syncthreads();
+        if (tid < kWave) {
+            const int rows = fill_below<KW>(a, P, child, n, nt, scores);
+            if (tid == 0) P.misc[62] = (uint32_t)rows;
+        }
+        __syncthreads();
+        nt = (int)P.misc[62];
+    }
     // rows
     const int64_t ob = (int64_t)b * N;
     const int root_tok = __builtin_amdgcn_readfirstlane(a.root_token[b]);
@@ -827,7 +970,9 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const 
 // nothing: the trees are wide and shallow (6 to 15 levels at depths 16 to 32,
 // 1.2 to 4 entries per budgeted node on peaked, flat and Gaussian drafters),
 // and finish_tree sorts what remains at or above the threshold.  One barrier
-// per level, two where it is counted first.
+// per level, two where it is counted first.  A level that overflows the pool
+// is entered again after the entries that its own scores have ruled out are
+// dropped.
 //
 // Latency bounds it: a level is a chain of LDS round trips (count, record,
 // score, place, record) of about 1000 cycles, on one workgroup per sequence.
@@ -835,10 +980,10 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const 
 // by sweep (budgets 33 - 512) or popping one node at a time (others): budget
 // 64, k = 4: 29.8 -> 11.1 us; 32 sequences of budget 128, depth 32: 33.2 ->
 // 14.8; budget 256, k = 8: 89.4 -> 16.4.
-// Two kinds of input go to the one-node-at-a-time search instead: more equal
-// scores at the threshold than the pool holds, and trees that only candidates
-// of S = -inf can fill (the level search leaves those out, since all their
-// descendants tie with them).
+// Candidates of S = -inf are left out (all their descendants tie with them);
+// where only they can fill the tree, a depth-first walk adds them (fill_below).
+// More (nearly) equal scores at the threshold than the pool holds, as when two
+// candidates of probability 1 share a row, go to the one-node-at-a-time search.
 template <int NT, int SL, int RHO, int KW>
 __global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
     extern __shared__ __align__(16) char lds[];
@@ -846,14 +991,17 @@ __global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
     const int D = a.D, k = a.k;
     const Pool<KW> P(a, lds);
     typedef typename Pool<KW>::Key Key;
-    init_pool<NT, KW>(a, P);
+    constexpr int NF = NT < 512 ? 512 : kFineMax;
+    init_pool<NT, NF, KW>(a, P);
     stage_tables<NT, RHO>(a, lds);
     const TokenScores<RHO> scores(a, lds);
 
     int lo = 0, hi = 1;         // entries of the level above
     uint32_t J = kBins - 1;     // candidates in later bins are dropped
     bool below = false;         // a candidate of S = -inf was left out
-    for (int d = 1; d <= D; ++d) {
+    bool again = false;         // the level is entered for the second time
+    uint32_t known = 0u;
+    for (int d = 1; d <= D;) {
         const int total = (hi - lo) * k;
         const int wi = (d - 1) / a.per_word, sh = 32 - ((d - 1) % a.per_word + 1) * a.wbits;
         // candidate i of the level: entry p's child of rank r
@@ -880,9 +1028,8 @@ __global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
             bin = score_bin(S);
             return in & (S > -INFINITY) & (bin <= J);
         };
-        const bool counted = total > NT;
-        uint32_t known;
-        if (counted) {
+        const bool counted = total > NT || again;
+        if (counted && !again) {
             for (int i = tid; i < total; i += NT) {
                 int p, r;
                 uint2 rec;
@@ -907,30 +1054,45 @@ __global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
                     const Key pk = P.key[p];
                     P.rec[at] = make_uint2(rec.x, Pool<KW>::meta(p, r, (int)(rec.y >> 13) & 15, d));
                     P.key[at] = Pool<KW>::child_key(pk, wi, sh, r);
-                    if (!counted) atomicAdd(&P.hist[bin], 1u);
                 }
+                if (in & !counted) atomicAdd(&P.hist[bin], 1u);
             }
         }
         __syncthreads();
         const int entered = (int)P.misc[d];
+        if (hi + entered > a.cap) {
+            // the histogram holds every candidate of the level, entered or not
+            J = threshold_bin(P.hist, a.budget, known);
+            if ((int)known >= a.cap || again) {
+                hi += entered;
+                break;
+            }
+            __syncthreads();  // every wave has read the level's count
+            if (tid == 0) P.misc[d] = 0u;
+            compact_pool<NT, KW>(P, J, lo, hi);
+            again = true;
+            continue;
+        }
+        again = false;
         lo = hi;
         hi += entered;
-        if ((entered == 0) | (hi > a.cap)) break;
+        ++d;
+        if (entered == 0) break;
         if (!counted && hi > a.budget) J = threshold_bin(P.hist, a.budget, known);
     }
     // the whole workgroup agrees on the search's outcome (the counts are
     // shared; a wave's J may differ, finish_tree takes it anew)
-    bool redo = hi > a.cap;
-    if (!redo && hi - 1 < a.budget) {
-        if (below) P.misc[63] = 1u;
-        __syncthreads();
-        redo = P.misc[63] != 0u;
-    }
-    if (redo) {
+    if (hi > a.cap) {
         if (tid < kWave) tree_pop_search<SL, RHO>(a, lds);
         return;
     }
-    finish_tree<NT, KW>(a, lds, P, hi);
+    bool fill = false;
+    if (hi - 1 < a.budget) {
+        if (below) P.misc[63] = 1u;
+        __syncthreads();
+        fill = P.misc[63] != 0u;
+    }
+    finish_tree<NT, NF, KW>(a, lds, P, hi, scores, fill);
 }
 
 // Beam search with global retention (Alg. 1): per depth, every beam entry's
@@ -958,7 +1120,7 @@ __global__ __launch_bounds__(kBeamThreads) void tree_beam_kernel(TreeArgs a) {
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int D = a.D, k = a.k, width = a.beam_width;
     const Pool<KW> P(a, lds);
-    init_pool<NT, KW>(a, P);
+    init_pool<NT, kFineMax, KW>(a, P);
     if (tid == 0) s_beam[0][0] = 0;
     stage_tables<NT, RHO>(a, lds);
     const TokenScores<RHO> scores(a, lds);
@@ -1020,7 +1182,7 @@ __global__ __launch_bounds__(kBeamThreads) void tree_beam_kernel(TreeArgs a) {
         cur ^= 1;
         __syncthreads();
     }
-    finish_tree<NT, KW>(a, lds, P, min(n, a.cap));
+    finish_tree<NT, kFineMax, KW>(a, lds, P, min(n, a.cap), scores, false);
 }
 
 // Literal Alg. 2 (Sec. 4.2): T grows by whole expansions.  The root is
@@ -1344,7 +1506,7 @@ struct PoolLayout {
     int o_kord, o_krank, o_rec, o_pkey;
 };
 
-static PoolLayout pool_layout_cap(int D, int k, int N, int threads, bool pops, bool lattice, int cap) {
+static PoolLayout pool_layout_cap(int D, int k, int N, bool pops, bool lattice, int cap) {
     PoolLayout L;
     L.kw = D <= 2 * (32 / tree_key_bits(k)) ? 2 : 4;
     L.cap = cap;
@@ -1356,7 +1518,7 @@ static PoolLayout pool_layout_cap(int D, int k, int N, int threads, bool pops, b
     L.o_pool = off; off = align16(off + cap * 8);
     L.o_key = off; off = align16(off + cap * 4 * L.kw);
     L.o_hist = off; off = align16(off + kBins * 4);
-    L.o_fine = off; off = align16(off + ((threads < 512 ? 512 : threads) + 1) * 4);
+    L.o_fine = off; off = align16(off + (kFineMax + 1) * 4);
     L.o_list = off; off = align16(off + cap * 2);
     L.o_place = off; off = align16(off + cap * 2);
     L.o_row = off; off = align16(off + N * 2);
@@ -1375,18 +1537,18 @@ static PoolLayout pool_layout_cap(int D, int k, int N, int threads, bool pops, b
     return L;
 }
 
-// The pool holds four entries per budgeted node (three to four is what the
+// The pool holds five entries per budgeted node (three to four is what most
 // searches enter) and 256 more, or what fits; the lattice is in LDS whenever
 // that leaves room for two per node and 256.
 static PoolLayout level_layout(int D, int k, int budget, bool lattice) {
-    const int threads = level_threads(budget), N = budget + 1;
-    const int want = 4 * budget + 257 < kPoolMax ? 4 * budget + 257 : kPoolMax;
+    const int N = budget + 1;
+    const int want = 5 * budget + 257 < kPoolMax ? 5 * budget + 257 : kPoolMax;
     for (int in_lds = lattice ? 1 : 0; in_lds >= 0; --in_lds)
         for (int cap = want; cap >= 2 * budget + 257; cap -= 64) {
-            const PoolLayout L = pool_layout_cap(D, k, N, threads, true, in_lds != 0, cap);
+            const PoolLayout L = pool_layout_cap(D, k, N, true, in_lds != 0, cap);
             if (L.total <= kTreeLdsBudget) return L;
         }
-    return pool_layout_cap(D, k, N, threads, true, false, 2 * budget + 257);
+    return pool_layout_cap(D, k, N, true, false, 2 * budget + 257);
 }
 
 // static LDS of the beam kernel, taken off the dynamic budget
@@ -1394,9 +1556,9 @@ static constexpr int kBeamStatic = 4096;
 
 static PoolLayout beam_layout(int D, int k, int budget, int width, bool lattice) {
     const int cap = budget + width * k + 1;  // root, T below the budget, one more depth
-    const PoolLayout L = pool_layout_cap(D, k, budget + 1, kBeamThreads, false, lattice, cap);
+    const PoolLayout L = pool_layout_cap(D, k, budget + 1, false, lattice, cap);
     if (!lattice || L.total <= kTreeLdsBudget - kBeamStatic) return L;
-    return pool_layout_cap(D, k, budget + 1, kBeamThreads, false, false, cap);
+    return pool_layout_cap(D, k, budget + 1, false, false, cap);
 }
 
 bool tree_build_fits(int D, int k, int branch, int N, int beam_width, bool alg2) {

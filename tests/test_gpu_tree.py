@@ -237,21 +237,25 @@ def _shape_table(kind, rng, b, D, k):
     elif kind == "masked":
         for s, d in np.ndindex(b, D):
             lp[s, d, rng.integers(1, k + 1):] = -np.inf
+    elif kind == "single":
+        lp[:, :, 1:] = -np.inf
     elif kind == "steep":
         lp *= 300.0
+    elif kind == "deep":
+        lp[:, :, 0] *= 0.05
     return lp.astype(np.float32)
 
 
-@pytest.mark.parametrize("kind", ["flat", "zero", "masked", "steep", "mixed"])
+@pytest.mark.parametrize("kind", ["flat", "zero", "masked", "single", "steep", "deep", "mixed"])
 @pytest.mark.parametrize("D,k,branch,B", [(16, 4, 4, 63), (16, 4, 4, 64), (16, 4, 4, 65), (32, 4, 3, 128),
                                           (20, 4, 4, 129), (12, 8, 8, 256), (13, 8, 8, 257), (16, 10, 10, 512),
                                           (17, 10, 7, 513), (5, 16, 16, 1023), (24, 1, 1, 30)])
 def test_tree_level_search_routes(kind, D, k, branch, B):
     """Budgets at the edges of the level kernel's sizes, two- and four-word
     rank-path keys (D = 16 | 17 at k = 10), levels that are counted before
-    they are entered, and both ways into the one-node-at-a-time search (a pool
-    that overflows with ties; candidates of S = -inf filling the budget);
-    beam search on the same tables.  Bit-exact."""
+    they are entered, pools that overflow and are closed up, the way into the
+    one-node-at-a-time search (more ties than the pool holds) and trees that
+    candidates of S = -inf fill; beam search on the same tables.  Bit-exact."""
     rng = np.random.default_rng([D, k, B, len(kind)])
     b = 3
     lp = _shape_table(kind, rng, b, D, k)
