@@ -131,16 +131,12 @@ __global__ __launch_bounds__(kTopkWavesPerBlock * kWave) void topk_partial_kerne
     __shared__ uint32_t cand_n[kTopkWavesPerBlock];
     __shared__ uint32_t rank_keys[kTopkWavesPerBlock][kWave];  // valid bf16 keys, one per lane
 
-    // the wave's index as a scalar (rows x chunks is below 2^31): the row, the
-    // chunk and the addresses are then scalar, too, where a 64-bit division
-    // per lane and 64-bit vector addresses took about as many vector
-    // instructions as a fifth of the chunk's entries
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
-    const uint32_t gw = blockIdx.x * (uint32_t)kTopkWavesPerBlock + (uint32_t)wave;
-    if (gw == 0u && lane == 0) *n_fallback = 0u;  // counted by the merge kernel
-    if (gw >= (uint32_t)rows * (uint32_t)chunks) return;
-    const uint32_t row = gw / (uint32_t)chunks;
-    const int32_t chunk = (int32_t)(gw - row * (uint32_t)chunks);
+    const int wave = threadIdx.x / kWave, lane = lane_id();
+    const int64_t gw = (int64_t)blockIdx.x * kTopkWavesPerBlock + wave;
+    if (gw == 0 && lane == 0) *n_fallback = 0u;  // counted by the merge kernel
+    if (gw >= rows * chunks) return;
+    const int64_t row = gw / chunks;
+    const int32_t chunk = (int32_t)(gw % chunks);
     const int64_t c0 = (int64_t)chunk * CH;
     // with a row index, output row `row` reads logits row row_index[row]; an
     // index outside the logits reads as an empty row (and is flagged)
@@ -249,7 +245,7 @@ __global__ __launch_bounds__(kTopkWavesPerBlock * kWave) void topk_partial_kerne
     }
     __builtin_amdgcn_wave_barrier();
     const uint32_t ngroups = __builtin_amdgcn_readfirstlane(cand_n[wave]);
-    uint64_t* out = part_keys + (int64_t)gw * k;
+    uint64_t* out = part_keys + gw * k;
 
     const int total = (int)ngroups * P;
     // key of list entry e (0 if it is past the list, past the row or below
