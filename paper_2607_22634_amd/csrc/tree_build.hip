@@ -1083,6 +1083,11 @@ __global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
     // the whole workgroup agrees on the search's outcome (the counts are
     // shared; a wave's J may differ, finish_tree takes it anew)
     if (hi > a.cap) {
+        // every wave has read the counts and the histogram that led here: the
+        // one-node-at-a-time search writes over that memory (its records reach
+        // the histogram, and at some shapes the counts, from k = 9 on), and a
+        // wave that read zeros there would take another way out
+        __syncthreads();
         if (tid < kWave) tree_pop_search<SL, RHO>(a, lds);
         return;
     }

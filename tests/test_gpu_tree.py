@@ -268,3 +268,28 @@ def test_tree_level_search_routes(kind, D, k, branch, B):
             print(f"routes {kind} D={D} k={k} branch={branch} B={B} lam={lam_v} W={width}", flush=True)
             g, o = _gpu_and_oracle(ids, lp, rho, lam, root, D, k, B, branch=branch, beam_width=width)
             _assert_same(g, o)
+
+
+@pytest.mark.parametrize("D,k,branch,B", [(6, 16, 16, 300), (6, 16, 16, 512), (6, 16, 16, 800), (6, 15, 15, 400),
+                                          (6, 14, 14, 400), (12, 12, 12, 1023), (16, 10, 10, 1023), (14, 16, 12, 600)])
+@pytest.mark.parametrize("lattice", [False, True])
+def test_tree_more_ties_than_the_pool(D, k, branch, B, lattice):
+    """Equal scores past the level search's pool: all scores alike (k >= 14:
+    a level of k^3 ties outgrows the pool) and candidates of probability 1
+    beside each other (every prefix of them ties).  The one-node-at-a-time
+    search then takes over the memory in which the workgroup's waves have just
+    read that the pool overflowed, so the shapes are those where its records
+    reach the histogram and the level counts.  Many sequences, bit-exact."""
+    b = 24
+    ids = np.stack([[np.random.default_rng([s, d]).choice(5000, k, replace=False) for d in range(D)]
+                    for s in range(b)]).astype(np.int32)
+    root = np.arange(b, dtype=np.int32)
+    flat = np.full((b, D, k), -1.5, np.float32)
+    sure = np.full((b, D, k), -3.0, np.float32)
+    sure[:, :, :3] = 0.0
+    rho = np.full((b, D, k, k, k), -0.5, np.float32) if lattice else None
+    for name, lp, lam_v in (("flat", flat, 0.25), ("sure", sure, 0.0)):
+        lam = np.full(D, lam_v, np.float32)
+        print(f"pool ties {name} D={D} k={k} branch={branch} B={B} lattice={lattice}", flush=True)
+        g, o = _gpu_and_oracle(ids, lp, rho, lam, root, D, k, B, branch=branch)
+        _assert_same(g, o)
