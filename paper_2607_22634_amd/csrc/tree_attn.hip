@@ -770,9 +770,11 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
                         acc += f * *reinterpret_cast<const floatx4*>(&s_to[(w * 16 + r) * D + d]);
                     }
                 }
-                const float inv = tr < live_rows && L > 0.f ? 1.f / L : 0.f;
-                acc *= inv;
-                const uint2 o2 = make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
+                acc *= L > 0.f ? 1.f / L : 0.f;
+                // (rows of padding nodes are zeros whatever their q holds)
+                const uint2 o2 = tr < live_rows
+                                     ? make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]))
+                                     : make_uint2(0u, 0u);
                 if (a.splits == 1) {
                     uint16_t* op = a.out + (((int64_t)b * a.n_max + tr / a.G) * a.hq + g * a.G + tr % a.G) * D + d;
                     *reinterpret_cast<uint2*>(op) = o2;
@@ -801,15 +803,16 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     const float l = l_run;  // whole-row sum
     if (!SHARES && a.splits == 1) {
         uint16_t* op = a.out + (((int64_t)b * a.n_max + qn) * a.hq + g * a.G + qh) * D;
-        const float inv = (rho < live_rows && l > 0.f) ? 1.f / l : 0.f;
+        const float inv = l > 0.f ? 1.f / l : 0.f;
+        const bool is_live = rho < live_rows;  // rows of padding nodes are zeros whatever their q holds
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
                 const int dd = db * 32 + 8 * q4 + 4 * h;
-                *reinterpret_cast<uint2*>(op + dd) =
-                    make_uint2(pack_bf16x2(o[db][4 * q4] * inv, o[db][4 * q4 + 1] * inv),
-                               pack_bf16x2(o[db][4 * q4 + 2] * inv, o[db][4 * q4 + 3] * inv));
+                const uint2 v = make_uint2(pack_bf16x2(o[db][4 * q4] * inv, o[db][4 * q4 + 1] * inv),
+                                           pack_bf16x2(o[db][4 * q4 + 2] * inv, o[db][4 * q4 + 3] * inv));
+                *reinterpret_cast<uint2*>(op + dd) = is_live ? v : make_uint2(0u, 0u);
             }
     } else {
         // normalised here, so bf16 holds it to the output's own precision
@@ -1219,7 +1222,8 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void tree_attn_f32_kernel(Att
     }
     if (wave != 0 || rho >= all_rows) return;
     // lane: row l32, dimensions DB (8 (e / 4) + 4 h + e % 4) + db
-    const float inv = is_live && l > 0.f ? 1.f / l : 0.f;
+    // (rows of padding nodes are zeros whatever their q holds)
+    const float inv = l > 0.f ? 1.f / l : 0.f;
     float* op;
     if (a.splits == 1) {
         op = a.out + (((int64_t)b * a.n_max + qn) * a.hq + g * a.G + qh) * D;
@@ -1231,7 +1235,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void tree_attn_f32_kernel(Att
     for (int e = 0; e < 16; ++e) {
         fdb v;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) v[db] = o[db][e] * inv;
+        for (int db = 0; db < DB; ++db) v[db] = is_live ? o[db][e] * inv : 0.f;
         *reinterpret_cast<fdb*>(op + DB * (8 * (e >> 2) + 4 * h + (e & 3))) = v;
     }
 }

@@ -320,3 +320,49 @@ def test_attention_padding_rows_without_a_merge(G, N):
     for s in range(b):
         assert _row_errors(got[s, :live[s]], reff[s, :live[s]]).max() <= 2e-2, s
         assert not got[s, live[s]:].any(), s
+
+
+def _attend(att, anc, n_nodes, ctx, d, dtype, **kw):
+    out = P.presto_tree_attention(
+        to_dev(att["q"], dtype), to_dev(att["k_cache"], dtype), to_dev(att["v_cache"], dtype),
+        to_dev(att["ctx_offsets"]), to_dev(att["k_tree"], dtype), to_dev(att["v_tree"], dtype),
+        to_dev(anc), to_dev(n_nodes), int(ctx.max()), d ** -0.5, **kw)
+    torch.cuda.synchronize()
+    ref = oracle.tree_attention(dtype, att["q"], att["k_cache"], att["v_cache"], att["ctx_offsets"],
+                                att["k_tree"], att["v_tree"], anc, n_nodes, d ** -0.5)
+    return sy.as_f32(to_host(out), dtype).astype(np.float64), sy.as_f32(ref, dtype).astype(np.float64)
+
+
+def _not_numbers(dtype, shape):
+    """NaN and infinities of both signs, as storage values."""
+    x = np.resize(np.array([np.nan, np.inf, -np.inf], np.float32), shape)
+    return x if dtype == "f32" else (np.ascontiguousarray(x).view(np.uint32) >> 16).astype(np.uint16)
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,N,ctx", [
+    ("f32", 4, 2, 128, 40, [0, 5, 20]), ("f32", 4, 2, 64, 40, [0, 5, 700]), ("f32", 32, 8, 128, 40, [0, 5, 1500]),
+    ("bf16", 8, 2, 128, 40, [0, 5, 20]), ("bf16", 8, 2, 128, 65, [0, 5, 20]), ("bf16", 8, 2, 64, 68, [0, 5, 9000]),
+    ("bf16", 8, 8, 128, 40, [0, 5, 4000])])
+def test_attention_queries_that_are_not_numbers(dtype, hq, hkv, d, N, ctx):
+    """A query of a padding node may hold anything (uninitialised memory): its
+    row is zeros, however the context is split and merged."""
+    rng = np.random.default_rng([hq, hkv, d, N])
+    ctx = np.array(ctx, np.int32)
+    n_nodes = np.array([N - 3, 7, N], np.int32)
+    b = len(ctx)
+    parent = np.full((b, N), -1, np.int32)
+    for s in range(b):
+        for n in range(1, int(n_nodes[s])):
+            parent[s, n] = rng.integers(max(0, n - 5), n)
+    att, anc = _edge_inputs(rng, b, N, hq, hkv, d, ctx, dtype, parent, n_nodes)
+    for s in range(b):
+        nn = int(n_nodes[s])
+        att["q"][s, nn:] = _not_numbers(dtype, att["q"][s, nn:].shape)
+    print(f"attn NaN queries {dtype} hq={hq} hkv={hkv} d={d} N={N} ctx={ctx.tolist()}", flush=True)
+    kw = {"workspace": torch.empty(4, dtype=torch.uint8, device="cuda")} if dtype == "f32" and N == 40 and d == 64 else {}
+    got, ref = _attend(att, anc, n_nodes, ctx, d, dtype, **kw)
+    tol = 2e-2 if dtype == "bf16" else 1e-5
+    for s in range(b):
+        nn = int(n_nodes[s])
+        assert (got[s, nn:] == 0).all(), s
+        assert _row_errors(got[s, :nn], ref[s, :nn]).max() <= tol, s
