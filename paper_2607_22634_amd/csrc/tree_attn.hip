@@ -966,11 +966,13 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
             }
         }
     }
-    // rows of padding nodes are zeros
-    const float inv = n < clamp_nodes(nn_raw, a.n_max) && L > 0.f ? 1.f / L : 0.f;
+    // rows of padding nodes are zeros; a live row whose every partial is NaN (no
+    // part has a maximum then, so L is 0) stays NaN
+    const bool live = n < clamp_nodes(nn_raw, a.n_max);
+    const float inv = L > 0.f ? 1.f / L : 0.f;
     uint32_t o[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = inv != 0.f ? pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv) : 0u;
+    for (int e = 0; e < 4; ++e) o[e] = live ? pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv) : 0u;
     uint16_t* op = a.out + (((int64_t)b * a.n_max + n) * a.hq + g * a.G + hh) * D + dl * 8;
     *reinterpret_cast<uint4*>(op) = make_uint4(o[0], o[1], o[2], o[3]);
 }
@@ -1222,8 +1224,9 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void tree_attn_f32_kernel(Att
     }
     if (wave != 0 || rho >= all_rows) return;
     // lane: row l32, dimensions DB (8 (e / 4) + 4 h + e % 4) + db
-    // (rows of padding nodes are zeros whatever their q holds)
-    const float inv = l > 0.f ? 1.f / l : 0.f;
+    // (a row that sees no key of this split leaves zeros; rows of padding nodes
+    // are zeros whatever their q holds)
+    const float inv = l == 0.f ? 0.f : 1.f / l;
     float* op;
     if (a.splits == 1) {
         op = a.out + (((int64_t)b * a.n_max + qn) * a.hq + g * a.G + qh) * D;
@@ -1262,7 +1265,8 @@ __global__ __launch_bounds__(256) void tree_attn_f32_merge_kernel(AttnF32Args a)
         float2 ml = make_float2(-INFINITY, 0.f);
         if (lane < nsplit) ml = a.part_ml[((int64_t)bg * rows + rho) * a.splits + lane];
         const float M = wave_max_f32_dpp(ml.x);
-        const float wl = ml.x == -INFINITY ? 0.f : expf(ml.x - M) * ml.y;
+        // (a sum without a maximum is 0, or NaN where no score is a number)
+        const float wl = ml.x == -INFINITY ? ml.y : expf(ml.x - M) * ml.y;
         const float L = wave_sum_f32_dpp(wl);
         const float* po = a.part_o + ((int64_t)bg * a.splits * rows + rho) * D + lane * PER;
         for (int s = 0; s < nsplit; ++s) {

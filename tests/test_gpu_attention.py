@@ -345,7 +345,8 @@ def _not_numbers(dtype, shape):
     ("bf16", 8, 8, 128, 40, [0, 5, 4000])])
 def test_attention_queries_that_are_not_numbers(dtype, hq, hkv, d, N, ctx):
     """A query of a padding node may hold anything (uninitialised memory): its
-    row is zeros, however the context is split and merged."""
+    row is zeros.  A live node's query that is NaN gives NaN in its own rows,
+    and in no other, however the context is split and merged."""
     rng = np.random.default_rng([hq, hkv, d, N])
     ctx = np.array(ctx, np.int32)
     n_nodes = np.array([N - 3, 7, N], np.int32)
@@ -358,11 +359,16 @@ def test_attention_queries_that_are_not_numbers(dtype, hq, hkv, d, N, ctx):
     for s in range(b):
         nn = int(n_nodes[s])
         att["q"][s, nn:] = _not_numbers(dtype, att["q"][s, nn:].shape)
+        att["q"][s, 1] = _not_numbers(dtype, (1,))[0]
+        att["q"][s, nn - 1] = _not_numbers(dtype, (1,))[0]
     print(f"attn NaN queries {dtype} hq={hq} hkv={hkv} d={d} N={N} ctx={ctx.tolist()}", flush=True)
     kw = {"workspace": torch.empty(4, dtype=torch.uint8, device="cuda")} if dtype == "f32" and N == 40 and d == 64 else {}
     got, ref = _attend(att, anc, n_nodes, ctx, d, dtype, **kw)
     tol = 2e-2 if dtype == "bf16" else 1e-5
     for s in range(b):
         nn = int(n_nodes[s])
+        bad = [1, nn - 1]
+        good = [n for n in range(nn) if n not in bad]
         assert (got[s, nn:] == 0).all(), s
-        assert _row_errors(got[s, :nn], ref[s, :nn]).max() <= tol, s
+        assert np.isnan(got[s, bad]).all(), s
+        assert _row_errors(got[s, good], ref[s, good]).max() <= tol, s
