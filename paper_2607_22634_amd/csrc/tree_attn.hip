@@ -1038,6 +1038,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void tree_attn_f32_kernel(Att
     // Q rows, chunk c of row r at c ^ r (sixteen rows read one chunk each:
     // different banks); after the key loop the waves' states
     __shared__ __align__(16) float s_mem[NW / 2 * SLOT > 32 * D ? NW / 2 * SLOT : 32 * D];
+    __shared__ int s_odd;  // a live row's sums are not all finite
 
     const int task = xcd_task(blockIdx.x, a.n_blocks);
     if (task >= a.n_tasks) return;
@@ -1114,6 +1115,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void tree_attn_f32_kernel(Att
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
     float m = -INFINITY, l = 0.f;
+    if (tid == 0) s_odd = 0;
     f4 kr[KJ];
     if (wave < nblk) load_k(k_begin + 32 * wave, kr);  // in flight under the staging of Q
     for (int i = tid; i < 32 * QC; i += NT) {
@@ -1195,11 +1197,68 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void tree_attn_f32_kernel(Att
                 o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vb[e][db], S[8 + e], o[db], 0, 0, 0);
     }
 
+    // A tree node that a row does not see takes no part in it, whatever its V
+    // holds, but the MFMAs have added 0 times that, NaN where V is not finite.
+    // Where a live row's sums are not all finite, the workgroup starts over key
+    // by key (looked for here: a test of V within the key loop cost it 8%).
+    uint32_t big = 0u;  // the largest |sum|, as bits
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) big = max(big, __float_as_uint(o[db][e]) & 0x7fffffffu);
+    if (__ballot(is_live && big >= 0x7f800000u)) s_odd = 1;
+    __syncthreads();
+    if (s_odd) {
+        // one row per wave at a time, 64 keys per step, a key per lane for the
+        // score and D / 64 dimensions per lane for the output
+        constexpr int PER = D / kWave;
+        for (int r = wave; r < 32 && row0 + r < all_rows; r += NW) {
+            const int row = row0 + r, n = row / a.G;
+            const uint64_t* ar = a.anc + ((int64_t)b * a.n_max + n) * a.W;
+            float m1 = -INFINITY, l1 = 0.f, acc[PER];
+#pragma unroll
+            for (int e = 0; e < PER; ++e) acc[e] = 0.f;
+            for (int j0 = k_begin; j0 < k_end && n < nn; j0 += kWave) {
+                const int j = j0 + lane, s = j - ctx;
+                const bool vis = j < k_end && (s < 0 || ((ar[s >> 6] >> (s & 63)) & 1ull));
+                const float* kp = row_of(a.kc, a.kt, j);
+                float x = 0.f;
+                for (int d = 0; d < D; ++d) x = fmaf(s_mem[r * D + 4 * ((d >> 2) ^ (r & (QC - 1))) + (d & 3)], kp[d], x);
+                x = vis ? x * a.scale : -INFINITY;
+                const float mn = fmaxf(m1, wave_max_f32_dpp(x));
+                const float al = m1 == -INFINITY ? 0.f : expf(m1 - mn);
+                const float pj = expf(x - (mn == -INFINITY ? 0.f : mn));
+                m1 = mn;
+                l1 = l1 * al + wave_sum_f32_dpp(pj);
+#pragma unroll
+                for (int e = 0; e < PER; ++e) acc[e] *= al;
+                for (uint64_t left = __ballot(vis); left != 0ull; left &= left - 1ull) {
+                    const int t = __ffsll((unsigned long long)left) - 1;
+                    const float pt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pj), t));
+                    const float* vp = row_of(a.vc, a.vt, j0 + t) + lane * PER;
+#pragma unroll
+                    for (int e = 0; e < PER; ++e) acc[e] = fmaf(pt, vp[e], acc[e]);
+                }
+            }
+            const float inv = l1 == 0.f ? 0.f : 1.f / l1;
+            float* op;
+            if (a.splits == 1) {
+                op = a.out + (((int64_t)b * a.n_max + n) * a.hq + g * a.G + row % a.G) * D;
+            } else {
+                op = a.part_o + (((int64_t)bg * a.splits + split) * all_rows + row) * D;
+                if (lane == 0) a.part_ml[((int64_t)bg * all_rows + row) * a.splits + split] = make_float2(m1, l1);
+            }
+#pragma unroll
+            for (int e = 0; e < PER; ++e) op[lane * PER + e] = acc[e] * inv;
+        }
+        return;
+    }
+
     // the waves' states, combined pairwise: odd multiples of `step` write,
     // their partners fold them in
 #pragma unroll
     for (int step = 1; step < NW; step *= 2) {
-        __syncthreads();
+        if (step > 1) __syncthreads();
         float* st = s_mem + wave / (2 * step) * SLOT + lane;
         if (wave % (2 * step) == step) {
             st[0] = m;

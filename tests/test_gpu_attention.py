@@ -372,3 +372,35 @@ def test_attention_queries_that_are_not_numbers(dtype, hq, hkv, d, N, ctx):
         assert (got[s, nn:] == 0).all(), s
         assert np.isnan(got[s, bad]).all(), s
         assert _row_errors(got[s, good], ref[s, good]).max() <= tol, s
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 2, 128), (6, 2, 64), (32, 8, 128)])
+@pytest.mark.parametrize("split", [True, False])
+def test_attention_f32_branches_are_isolated(hq, hkv, d, split):
+    """fp32: a tree node whose K or V is not a number reaches its descendants
+    only; every other row is what it would be without it."""
+    rng = np.random.default_rng([hq, hkv, d])
+    N, dtype = 70, "f32"
+    ctx = np.array([0, 31, 64, 1300], np.int32)
+    n_nodes = np.array([70, 40, 69, 70], np.int32)
+    b = len(ctx)
+    parent = np.full((b, N), -1, np.int32)
+    for s in range(b):
+        for n in range(1, int(n_nodes[s])):
+            parent[s, n] = (n - 1) // 3
+    att, anc = _edge_inputs(rng, b, N, hq, hkv, d, ctx, dtype, parent, n_nodes)
+    for s in range(b):
+        for n in (5, 33, int(n_nodes[s]) - 1):
+            att["v_tree"][s, n, :, n % 7::9] = _not_numbers(dtype, (hkv, len(range(n % 7, d, 9))))
+        att["k_tree"][s, 11, :, 3] = np.nan
+    print(f"attn f32 isolation hq={hq} hkv={hkv} d={d} split={split}", flush=True)
+    kw = {} if split else {"workspace": torch.empty(4, dtype=torch.uint8, device="cuda")}
+    got, ref = _attend(att, anc, n_nodes, ctx, d, dtype, **kw)
+    for s in range(b):
+        nn = int(n_nodes[s])
+        fin = np.isfinite(ref[s, :nn])
+        np.testing.assert_array_equal(np.isfinite(got[s, :nn]), fin, err_msg=str(s))
+        assert not fin.all() and fin.any()
+        # the errors of the numbers alone, against their rows' size
+        assert _row_errors(np.where(fin, got[s, :nn], 0), np.where(fin, ref[s, :nn], 0)).max() <= 1e-5, s
+        assert not got[s, nn:].any()
