@@ -80,6 +80,7 @@ struct AttnArgs {
     // D] and [g, row, slot], slot = share + sequence < n_slots
     int32_t shares, n_slots;
     int2* slots;  // [batch] first and last slot of each sequence
+    int32_t pairs;  // 1: the tasks are the (sequence, split) pairs that exist; the grid is an upper bound
     float scale_log2;  // scale * log2(e)
 };
 
@@ -115,6 +116,12 @@ __device__ __forceinline__ int share_tiles(const AttnArgs& a, int bb) {
     if (bb >= a.batch) return 0;
     const int keys = ctx_span(a.ctx_off, bb, a.ctx_slots).ctx + clamp_nodes(a.n_nodes[bb], a.n_max);
     return (keys + kKeyTile - 1) / kKeyTile + kLeadTiles;
+}
+// splits that sequence bb really has, 0 past the batch
+__device__ __forceinline__ int live_splits(const AttnArgs& a, int bb) {
+    if (bb >= a.batch) return 0;
+    const int keys = ctx_span(a.ctx_off, bb, a.ctx_slots).ctx + clamp_nodes(a.n_nodes[bb], a.n_max);
+    return (keys + a.split_len - 1) / a.split_len;
 }
 __device__ __forceinline__ int wave_prefix_dpp(int v) {
     uint32_t x = (uint32_t)v;
@@ -213,8 +220,20 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     // of at most kMaxAncWords words; with the ring this is 160 KB at D = 128
     __shared__ uint64_t s_anc[ROWS * kMaxAncWords];
 
-    const int task = xcd_task(blockIdx.x, a.n_blocks);
-    if (task >= a.n_tasks) return;
+    int n_tasks = a.n_tasks, n_blocks = a.n_blocks;
+    if constexpr (!SHARES && !TAIL) {
+        if (a.pairs) {
+            // every wave counts the pairs itself
+            int pairs = 0;
+            for (int b0 = 0; b0 < a.batch; b0 += kWave)
+                pairs += __builtin_amdgcn_readlane(wave_prefix_dpp(live_splits(a, b0 + lane_id())), kWave - 1);
+            n_tasks = pairs * a.hkv * a.row_tiles;
+            n_blocks = (n_tasks + 7) / 8 * 8;
+            if ((int)blockIdx.x >= n_blocks) return;
+        }
+    }
+    const int task = xcd_task(blockIdx.x, n_blocks);
+    if (task >= n_tasks) return;
     const int rt = task % a.row_tiles;
     const int g = (task / a.row_tiles) % a.hkv;
 
@@ -841,8 +860,26 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
         // their workgroups a few microseconds apart in XCD order, and the
         // last split, which holds the tree keys and their masks and so runs
         // longest, then lands on the XCDs that start first.
-        const int split = a.splits - 1 - item % a.splits;
-        const int b = item / a.splits;
+        int split = a.splits - 1 - item % a.splits;
+        int b = item / a.splits;
+        if constexpr (!TAIL) {
+            if (a.pairs) {
+                // item = the pair's index in sequence order, splits in reverse as well
+                b = -1;
+                for (int b0 = 0, base = 0; b0 < a.batch && b < 0; b0 += kWave) {
+                    const int n = live_splits(a, b0 + lane_id()), incl = wave_prefix_dpp(n);
+                    const uint64_t hit = __ballot(base + incl > item);
+                    if (hit) {
+                        const int l = __ffsll((unsigned long long)hit) - 1;
+                        b = b0 + l;
+                        split = base + __builtin_amdgcn_readlane(incl, l) - 1 - item;
+                    } else {
+                        base += __builtin_amdgcn_readlane(incl, kWave - 1);
+                    }
+                }
+                if (b < 0) return;
+            }
+        }
         const int64_t bg = (int64_t)b * a.hkv + g;
         segment(b, split * a.split_len, (split + 1) * a.split_len, (bg * a.splits + split) * all,
                 bg * all * a.splits + split, a.splits);
@@ -1348,9 +1385,11 @@ namespace presto_host {
 using namespace presto;
 
 struct AttnPlan {
-    int G, rows, row_tiles, rows_per_tile, waves, splits, split_len;
+    int G, rows, row_tiles, rows_per_tile, splits, split_len;
     int shares, n_slots;  // shares > 0: equal shares of a ragged batch's key tiles
     bool tail;            // 1 .. 16 rows past the last full tile, taken along by it
+    bool pairs;           // workgroups dealt over the (sequence, split) pairs that exist
+    double cost;          // modelled time, in 32-key blocks of a workgroup of 256 rows
     int64_t tasks, blocks;
     bool merged() const { return shares > 0 || splits > 1; }
     // query rows that leave a partial
@@ -1363,66 +1402,48 @@ static bool attn_ragged(const presto_attn_desc* d) {
     return d->batch > 1 && d->total_ctx > 0 && d->total_ctx < (int64_t)d->batch * d->max_ctx;
 }
 
-static AttnPlan attn_plan_rows(const presto_attn_desc* d, bool tail) {
+constexpr int kMaxSplits = 64;  // searched; the fastest found is at most about 30
+
+// Row tiles and context splits: one workgroup per CU, so the time in key-block
+// units (about 0.85 us each) is (rounds of workgroups) x (key blocks per split
+// + about 3 for a workgroup's prologue) plus the merge, whose partials (2 D + 8
+// bytes per query row and split, written and read back, about 4 MB per
+// key-block time) grow with the split count.  tail: without a row tile for the
+// rows past the last full one.  pairs: workgroups only for the (sequence,
+// split) pairs that exist, about total / len + batch / 2 of them.
+static AttnPlan attn_plan_split(const presto_attn_desc* d, bool tail, bool pairs, int most) {
     AttnPlan p;
     p.G = d->hq / d->hkv;
     p.rows = p.G * d->n_max;
-    // 256 query rows per workgroup: eight waves of one 32-row block, or four
-    // waves of two (each K/V fragment read from LDS then feeds two MFMAs)
-    p.waves = kAttnWaves;
     p.rows_per_tile = kAttnRows;
     p.tail = tail;
+    p.pairs = pairs;
     p.row_tiles = p.tail ? p.rows / p.rows_per_tile : (p.rows + p.rows_per_tile - 1) / p.rows_per_tile;
-    // context splits: one workgroup per CU, so the time in key-block units
-    // (about 0.85 us each) is (rounds of workgroups) x (key blocks per split
-    // + about 3 for a workgroup's prologue) plus the merge, whose partials
-    // (2 D + 8 bytes per query row and split, written and read back, about
-    // 4 MB per key-block time) grow with the split count
     const int64_t per_pair = (int64_t)d->hkv * p.row_tiles;  // workgroups per (sequence, split)
     const int keys = d->max_ctx + d->n_max;                  // the longest sequence
+    const double total_keys = (double)d->total_ctx + (double)d->batch * d->n_max;
     const int max_splits = (keys + 127) / 128;
     const double row_bytes = 2.0 * d->head_dim + 8.0;
-    double best_cost = 1e30;
+    p.cost = 1e30;
     p.shares = p.n_slots = 0;
     p.splits = 1;
     p.split_len = (keys + kKeyTile - 1) / kKeyTile * kKeyTile;
-    for (int s = 1; s <= kWave && s <= max_splits; ++s) {  // the merge gives each split a lane
+    for (int s = 1; s <= most && s <= max_splits; ++s) {
         int len = (keys + s - 1) / s;
         len = (len + kKeyTile - 1) / kKeyTile * kKeyTile;
         const int se = (keys + len - 1) / len;
-        const double pairs = (double)d->batch * se;
-        const double rounds = ceil(pairs * per_pair / 256.0);
-        const double merge_bytes = se > 1 ? 2.0 * d->hkv * p.rows * pairs * row_bytes : 0.0;
+        const double all = (double)d->batch * se;
+        const double n = pairs ? fmin(all, total_keys / len + 0.5 * d->batch) : all;
+        const double rounds = ceil(n * per_pair / 256.0);
+        const double merge_bytes = se > 1 ? 2.0 * d->hkv * p.rows * n * row_bytes : 0.0;
         const double cost = rounds * ((len + 31) / 32 + 3) + merge_bytes / 4.0e6;
-        if (cost < best_cost - 1e-9) {
-            best_cost = cost;
+        if (cost < p.cost - 1e-9) {
+            p.cost = cost;
             p.splits = se;
             p.split_len = len;
         }
     }
-    p.tasks = (int64_t)d->batch * p.splits * per_pair;
-    const bool ragged = attn_ragged(d);
-    // Ragged contexts whose total the caller knows: equal shares of all key
-    // tiles instead, one per workgroup of a (KV head, row tile), so that no
-    // workgroup waits for a longer one (16 contexts of 1024 .. 8192 keys, 33
-    // nodes: 97.1 -> 86.5 us per call).  A few row tiles only: with more than
-    // 128 workgroups per share there is no choice of their number left.
-    if (ragged && per_pair <= 128 && (int64_t)d->batch * d->hkv <= 65535) {
-        const double tiles = ((double)d->total_ctx + (double)d->batch * d->n_max) / kKeyTile +
-                             (kLeadTiles + 0.5) * d->batch;
-        best_cost = 1e30;
-        for (int c = 1; c <= 256; ++c) {
-            const double rounds = ceil((double)c * per_pair / 256.0);
-            const double merge_bytes = 2.0 * d->hkv * p.rows * (c + d->batch) * row_bytes;
-            const double cost = rounds * (2.0 * tiles / c + 2.0 * kLeadTiles) + merge_bytes / 4.0e6;
-            if (cost < best_cost - 1e-9) {
-                best_cost = cost;
-                p.shares = c;
-            }
-        }
-        p.n_slots = p.shares + d->batch - 1;
-        p.tasks = p.shares * per_pair;
-    }
+    p.tasks = (int64_t)d->batch * p.splits * per_pair;  // with pairs an upper bound
     p.blocks = (p.tasks + 7) / 8 * 8;
     // When the whole grid fits one round (one workgroup per CU), the tiles
     // are balanced: the same number of row tiles, each a multiple of 32 rows
@@ -1431,7 +1452,44 @@ static AttnPlan attn_plan_rows(const presto_attn_desc* d, bool tail) {
     // two waves per SIMD through every key block (about 1 us per block), one
     // of 160 rows one and a quarter (the idle waves share the fifth block's
     // keys), and the 4-row tiles, nearly idle, disappear.
-    if (p.tasks <= 256 && p.row_tiles > 1 && !p.tail)
+    if (p.tasks <= 256 && p.row_tiles > 1 && !p.tail && !p.pairs)
+        p.rows_per_tile = kRowsPerWave * ((p.rows + kRowsPerWave * p.row_tiles - 1) / (kRowsPerWave * p.row_tiles));
+    return p;
+}
+
+// Equal shares of all key tiles, one per workgroup of a (KV head, row tile), so
+// that no workgroup waits for a longer one.  A few row tiles only: with more
+// than 128 workgroups per share there is no choice of their number left.
+static AttnPlan attn_plan_shares(const presto_attn_desc* d) {
+    AttnPlan p = attn_plan_split(d, false, false, 1);
+    p.cost = 1e30;
+    const int64_t per_pair = (int64_t)d->hkv * p.row_tiles;
+    if (per_pair > 128 || (int64_t)d->batch * d->hkv > 65535) return p;
+    const double row_bytes = 2.0 * d->head_dim + 8.0;
+    const double tiles = ((double)d->total_ctx + (double)d->batch * d->n_max) / kKeyTile +
+                         (kLeadTiles + 0.5) * d->batch;
+    // per count of rounds, the shares that balance the keys against the merge
+    const double merge = 2.0 * d->hkv * p.rows * row_bytes / 4.0e6;  // of one partial per row
+    int lo = 1;
+    for (int r = 1; lo <= 256 && r * 2.0 * kLeadTiles < p.cost; ++r) {
+        const int hi = (int)(256 * r / per_pair < 256 ? 256 * r / per_pair : 256);
+        if (hi < lo) continue;
+        const double at = sqrt(2.0 * r * tiles / merge);
+        const int c0 = at < lo ? lo : (at < hi ? (int)at : hi);
+        for (int c = c0; c <= c0 + 1 && c <= hi; ++c) {
+            const double cost = r * (2.0 * tiles / c + 2.0 * kLeadTiles) + merge * (c + d->batch);
+            if (cost < p.cost - 1e-9) {
+                p.cost = cost;
+                p.shares = c;
+            }
+        }
+        lo = hi + 1;
+    }
+    p.n_slots = p.shares + d->batch - 1;
+    p.tasks = p.shares * per_pair;
+    p.blocks = (p.tasks + 7) / 8 * 8;
+    p.rows_per_tile = kAttnRows;
+    if (p.tasks <= 256 && p.row_tiles > 1)
         p.rows_per_tile = kRowsPerWave * ((p.rows + kRowsPerWave * p.row_tiles - 1) / (kRowsPerWave * p.row_tiles));
     return p;
 }
@@ -1481,17 +1539,43 @@ static size_t attn_f32_partial_rows(const presto_attn_desc* d, const AttnF32Plan
     return (size_t)d->batch * d->hkv * p.rows * p.splits;
 }
 
-// 1 .. 16 query rows past the last full tile ride along with it, unless the
-// tiles of their own come out balanced in one round of short splits, where a
-// workgroup's start and the merge weigh more than the keys read twice (1 x
-// 4096 keys, 65 nodes: 25.3 us balanced, 30.8 riding along; 16 x 4608 keys:
-// 125.7 and 117.2).  G >= 2: the ancestor rows of a tile then leave room for
-// the tail's queries; not with shares: that kernel has no registers left.
-static AttnPlan attn_plan(const presto_attn_desc* d) {
-    const AttnPlan p = attn_plan_rows(d, false);
-    if (p.G < 2 || attn_ragged(d) || p.rows <= kAttnRows || (p.rows - 1) % kAttnRows >= 16) return p;
+// Plan p of a grid over all (sequence, split) pairs, or the one where 1 .. 16
+// query rows past the last full tile ride along with it, unless the tiles of
+// their own come out balanced in one round of short splits, where a workgroup's
+// start and the merge weigh more than the keys read twice (1 x 4096 keys, 65
+// nodes: 25.3 us balanced, 30.8 riding along).  G >= 2: the ancestor rows of a
+// tile then leave room for the tail's queries.
+static AttnPlan attn_plan_tail(const presto_attn_desc* d, const AttnPlan& p, int most) {
+    if (p.G < 2 || p.rows <= kAttnRows || (p.rows - 1) % kAttnRows >= 16) return p;
     if (p.tasks <= 256 && p.split_len < 1024) return p;
-    return attn_plan_rows(d, true);
+    return attn_plan_split(d, true, false, most);
+}
+
+// Ragged contexts whose total the caller knows: one of three schedules, by their
+// modelled times with a term for what each costs beside its keys.  The terms
+// are fitted to 2 .. 128 sequences of 100 .. 32768 keys, the shortest context an
+// eighth of the longest, 9 .. 1023 nodes (us per call, pairs / dense / shares;
+// dealing pairs whatever the shape was the rule before: no shape measured is
+// more than 2% slower than that, most are 5 to 40% faster):
+//   dense    the grid of the longest context; workgroups past a sequence's end
+//            leave at once.  Short contexts: 8 x 800 keys 23.5 / 21.5 / 22.9,
+//            16 x 400 26.2 / 23.1 / 24.7.
+//   pairs    6.5 blocks for finding a workgroup's pair.  A few sequences whose
+//            pairs make one round: 6 x 5000 keys 33.4 / 37.5 / 35.9.
+//   shares   3 blocks for finding a share, 10% for the loop over its parts.
+//            Everything longer: 16 x 8192 keys 104 / 101 / 80.
+// A batch whose pairs would not be split is not split: one fp32 accumulator from
+// a row's first key to its last, no bf16 partials and no merge (32 x 400 keys
+// 24.0 / 23.0 / 36.6, 32 x 1600 47.2 / 45.8 / 53.6).
+static AttnPlan attn_plan(const presto_attn_desc* d) {
+    if (!attn_ragged(d)) return attn_plan_tail(d, attn_plan_split(d, false, false, kMaxSplits), kMaxSplits);
+    const AttnPlan pr = attn_plan_split(d, false, true, kMaxSplits);
+    if (pr.splits == 1) return attn_plan_tail(d, attn_plan_split(d, false, false, 1), 1);
+    const AttnPlan de = attn_plan_split(d, false, false, kMaxSplits);
+    const AttnPlan sh = attn_plan_shares(d);
+    const double c_de = 1.05 * de.cost, c_pr = pr.cost + 6.5, c_sh = 1.1 * sh.cost + 3.0;
+    if (c_de <= c_pr && c_de <= c_sh) return attn_plan_tail(d, de, kMaxSplits);
+    return c_pr <= c_sh ? pr : sh;
 }
 
 size_t attn_workspace_bytes(const presto_attn_desc* d) {
@@ -1597,11 +1681,12 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
     a.splits = p.splits;
     a.split_len = p.split_len;
     a.n_tasks = (int32_t)p.tasks;
+    a.pairs = p.pairs ? 1 : 0;
     a.shares = p.shares;
     a.n_slots = p.n_slots;
     a.n_blocks = (int32_t)p.blocks;
     a.scale_log2 = d->scale * kLog2e;
-    const dim3 block(p.waves * kWave), grid((unsigned)p.blocks);
+    const dim3 block(kAttnWaves * kWave), grid((unsigned)p.blocks);
     auto go = [&](auto shares, auto tail) {
         if (d->head_dim == 64)
             tree_attn_bf16_kernel<64, decltype(shares)::value, decltype(tail)::value><<<grid, block, 0, stream>>>(a);

@@ -45,6 +45,18 @@ def test_workspace_sizes_are_deterministic_and_monotone():
     assert lib.presto_tree_attention_workspace(ctypes.byref(d1)) == 0  # fills the chip unsplit
 
 
+@pytest.mark.parametrize("b,n,max_ctx,total", [
+    (32, 33, 100, 1800), (32, 33, 400, 7200), (32, 33, 1600, 28700), (16, 33, 100, 900), (32, 129, 200, 3600),
+    (32, 129, 800, 14300), (128, 33, 300, 21000), (16, 65, 1024, 9200)])
+def test_attention_batches_that_fill_the_chip_are_not_split(b, n, max_ctx, total):
+    """Ragged batches with a total-context hint that make one workgroup per
+    sequence and KV head and fill the chip: split, a row's fp32 accumulator
+    would become several bf16 partials and a merge (1.1 to 1.9 times slower
+    too), so no workspace is asked for."""
+    d = P.AttnDesc(b, n, 32, 8, 128, max_ctx, 0.088, P.PRESTO_DT_BF16, P.PRESTO_CTX_PACKED, total)
+    assert P.lib().presto_tree_attention_workspace(ctypes.byref(d)) == 0
+
+
 def _err(status):
     return status, P.lib().presto_last_error().decode()
 

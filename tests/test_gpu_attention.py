@@ -404,3 +404,53 @@ def test_attention_f32_branches_are_isolated(hq, hkv, d, split):
         # the errors of the numbers alone, against their rows' size
         assert _row_errors(np.where(fin, got[s, :nn], 0), np.where(fin, ref[s, :nn], 0)).max() <= 1e-5, s
         assert not got[s, nn:].any()
+
+
+@pytest.mark.parametrize("hq,hkv,d,N,b,max_ctx,total", [
+    (8, 2, 128, 129, 17, 4000, 27200),   # shares: three balanced row tiles, 42 shares
+    (16, 16, 64, 257, 12, 8000, 28800),  # shares: one head per KV head, a second tile of one row
+    (8, 8, 128, 257, 40, 2000, 40000),   # shares: several short sequences in each
+    (4, 4, 64, 300, 9, 8000, 28800),     # shares: two tiles of 160 rows
+    (16, 2, 128, 130, 9, 8000, 28800),   # shares: eight heads per KV head, five tiles
+    (12, 6, 64, 600, 8, 20000, 96000),  # shares: two rounds of full tiles
+    (8, 2, 128, 129, 9, 1500, 5400),     # pairs
+    (4, 4, 64, 300, 9, 1500, 5400),      # pairs
+    (16, 2, 128, 130, 5, 4000, 8000),    # pairs
+    (8, 2, 64, 65, 70, 4000, 28),        # pairs: more sequences than a wave has lanes
+    (8, 2, 128, 129, 5, 300, 600),       # the longest context's grid
+    (8, 4, 64, 129, 6, 1500, 3600),      # pairs: two heads per KV head, a second tile of two rows
+    (16, 2, 128, 130, 17, 300, 2040),    # unsplit
+])
+def test_attention_ragged_schedules(hq, hkv, d, N, b, max_ctx, total):
+    """The schedules of a ragged batch with a total-context hint, with several
+    row tiles per KV head: trees whose live rows end in the first tile (dead
+    tiles), in a later one and at a tile's last row, empty and one-key
+    contexts beside long ones, and bounds and hints far from the contexts (a
+    hint only schedules), so that shares end among a sequence's first tiles."""
+    rng = np.random.default_rng([hq, hkv, d, N, b])
+    G, dtype = hq // hkv, "bf16"
+    ctx = rng.integers(0, 250, b).astype(np.int32)
+    ctx[:3] = [0, 1, min(max_ctx, 900)]
+    n_nodes = rng.integers(1, N + 1, b).astype(np.int32)
+    n_nodes[:4] = [N, 2, N, min(N, 256 // G)]
+    parent = np.full((b, N), -1, np.int32)
+    for s in range(b):
+        for n in range(1, int(n_nodes[s])):
+            parent[s, n] = rng.integers(max(0, n - 7), n)
+    att, anc = _edge_inputs(rng, b, N, hq, hkv, d, ctx, dtype, parent, n_nodes)
+    print(f"attn schedules hq={hq} hkv={hkv} d={d} N={N} b={b} max_ctx={max_ctx} total={total}", flush=True)
+    out = torch.full((b, N, hq, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    for _ in range(2):  # the second call finds the first one's partials and notes in the workspace
+        P.presto_tree_attention(
+            to_dev(att["q"], dtype), to_dev(att["k_cache"], dtype), to_dev(att["v_cache"], dtype),
+            to_dev(att["ctx_offsets"]), to_dev(att["k_tree"], dtype), to_dev(att["v_tree"], dtype),
+            to_dev(anc), to_dev(n_nodes), max_ctx, d ** -0.5, total_ctx=total, out=out)
+    torch.cuda.synchronize()
+    ref = oracle.tree_attention(dtype, att["q"], att["k_cache"], att["v_cache"], att["ctx_offsets"],
+                                att["k_tree"], att["v_tree"], anc, n_nodes, d ** -0.5)
+    got = sy.as_f32(to_host(out), dtype).astype(np.float64)
+    reff = sy.as_f32(ref, dtype).astype(np.float64)
+    for s in range(b):
+        nn = int(n_nodes[s])
+        assert _row_errors(got[s, :nn], reff[s, :nn]).max() <= 2e-2, s
+        assert not got[s, nn:].any(), s
