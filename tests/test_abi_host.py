@@ -57,6 +57,15 @@ def test_attention_batches_that_fill_the_chip_are_not_split(b, n, max_ctx, total
     assert P.lib().presto_tree_attention_workspace(ctypes.byref(d)) == 0
 
 
+@pytest.mark.parametrize("b,max_ctx", [(16, 1024), (16, 4608), (16, 8192)])
+def test_attention_tail_rows_do_not_split_a_batch(b, max_ctx):
+    """65 nodes of four heads per KV head: four rows past a full tile.  Tiles
+    of their own serve these batches unsplit; taken along by the full tile,
+    they must not bring bf16 partials in the place of one fp32 accumulator."""
+    d = P.AttnDesc(b, 65, 32, 8, 128, max_ctx, 0.088, P.PRESTO_DT_BF16)
+    assert P.lib().presto_tree_attention_workspace(ctypes.byref(d)) == 0
+
+
 def _err(status):
     return status, P.lib().presto_last_error().decode()
 

@@ -258,11 +258,11 @@ def test_attention_f32_blocks(hq, hkv, d, how):
                                         (2, 2, 128, 257), (4, 2, 64, 1023)])
 @pytest.mark.parametrize("b", [1, 3])
 def test_attention_rows_past_a_full_tile(hq, hkv, d, N, b):
-    """1 .. 16 query rows past a multiple of 256 ride along with the last full
-    tile (just past 16, and one head per KV head, they get a tile of their
-    own): whole trees, trees that end inside the tail's rows, at the tile's
-    edge and before it, contexts around a 64-key tile and a 16-key group, with
-    one split and with many."""
+    """1 .. 16 query rows past a multiple of 256 (and just past 16, and with one
+    head per KV head) in tiles of their own, which these short contexts get:
+    whole trees, trees that end inside the last rows, at the full tile's edge
+    and before it, contexts around a 64-key tile and a 16-key group, with one
+    split and with many."""
     rng = np.random.default_rng([hq, hkv, d, N, b])
     G, dtype = hq // hkv, "bf16"
     full = (G * N // 256) * 256 // G  # nodes whose rows lie in full tiles
@@ -454,3 +454,56 @@ def test_attention_ragged_schedules(hq, hkv, d, N, b, max_ctx, total):
         nn = int(n_nodes[s])
         assert _row_errors(got[s, :nn], reff[s, :nn]).max() <= 2e-2, s
         assert not got[s, nn:].any(), s
+
+
+@pytest.mark.parametrize("hq,hkv,d,N,b,max_ctx,split_len", [
+    (32, 8, 128, 65, 3, 60000, 6016),   # four rows past a full tile
+    (32, 8, 128, 68, 3, 60000, 6016),   # sixteen
+    (8, 2, 64, 129, 3, 60000, 2880),    # the second of two full tiles takes them
+    (4, 2, 128, 136, 3, 60000, 1472),   # two heads per KV head
+    (16, 2, 128, 34, 3, 60000, 1472),   # eight
+    (10, 2, 128, 52, 3, 60000, 1472),   # five: a node on both sides of the tile's edge
+    (8, 2, 128, 257, 3, 60000, 6080),   # five ancestor words
+    (8, 2, 128, 129, 64, 100, 0),       # not split
+    (32, 8, 64, 65, 32, 200, 0),        # not split
+])
+def test_attention_rows_that_ride_along(hq, hkv, d, N, b, max_ctx, split_len):
+    """1 .. 16 query rows past a multiple of 256 that the last full tile takes
+    along (long or many sequences; a bound on the context far above the
+    contexts gives the long ones' plan): whole trees, trees that end inside the
+    tail's rows, at the tile's edge and before it; contexts around a 64-key
+    tile, a 16-key group and a split's end, with one part and with several."""
+    rng = np.random.default_rng([hq, hkv, d, N, b])
+    G, dtype = hq // hkv, "bf16"
+    full = (G * N // 256) * 256 // G  # nodes whose rows lie in full tiles
+    over = min(full + 1, N)
+    if split_len:
+        sets = [([0, 15, 16], [N, full, over]), ([split_len + 70, 65, 1], [over, N, 3]),
+                ([2 * split_len - 20, split_len - N, split_len - 1], [N, N, N])]
+    else:
+        sets = [(rng.integers(0, max_ctx, b), rng.choice([N, N, N, full, over, over - 1, 1, N // 2], b))]
+    for ctx, live in sets:
+        ctx, n_nodes = np.array(ctx, np.int32), np.array(live, np.int32)
+        parent = np.full((b, N), -1, np.int32)
+        for s in range(b):
+            for n in range(1, int(n_nodes[s])):
+                parent[s, n] = rng.integers(max(0, n - 9), n)
+        att, anc = _edge_inputs(rng, b, N, hq, hkv, d, ctx, dtype, parent, n_nodes)
+        for s in range(b):  # queries of padding nodes are whatever memory held
+            att["q"][s, n_nodes[s]:] = _not_numbers(dtype, att["q"][s, n_nodes[s]:].shape)
+        print(f"attn along hq={hq} hkv={hkv} d={d} N={N} b={b} ctx={ctx[:3].tolist()} live={n_nodes[:3].tolist()}",
+              flush=True)
+        out = torch.full((b, N, hq, d), 7.0, dtype=torch.bfloat16, device="cuda")
+        P.presto_tree_attention(
+            to_dev(att["q"], dtype), to_dev(att["k_cache"], dtype), to_dev(att["v_cache"], dtype),
+            to_dev(att["ctx_offsets"]), to_dev(att["k_tree"], dtype), to_dev(att["v_tree"], dtype),
+            to_dev(anc), to_dev(n_nodes), max_ctx, d ** -0.5, out=out)
+        torch.cuda.synchronize()
+        ref = oracle.tree_attention(dtype, att["q"], att["k_cache"], att["v_cache"], att["ctx_offsets"],
+                                    att["k_tree"], att["v_tree"], anc, n_nodes, d ** -0.5)
+        got = sy.as_f32(to_host(out), dtype).astype(np.float64)
+        reff = sy.as_f32(ref, dtype).astype(np.float64)
+        for s in range(b):
+            nn = int(n_nodes[s])
+            assert _row_errors(got[s, :nn], reff[s, :nn]).max() <= 2e-2, s
+            assert (got[s, nn:] == 0).all(), s
