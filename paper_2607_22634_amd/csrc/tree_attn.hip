@@ -923,17 +923,27 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     }
 }
 
-// Merge of the split partials.  D / 8 lanes per query row, 8 dims each (a
-// 16-byte load per partial and lane), four or eight rows per wave; every lane
-// weighs its row's splits itself, l exp2(m - M), kMergeUnroll of them with all
-// loads in flight.  Memory latency and the partials' bytes bound it: split by
-// split with one wave per row and 4-byte loads, weights across the lanes, it
-// took 12.9 us for 16 ragged sequences of 33 nodes (three partials per row)
-// and 20.7 us for 4 of 257 nodes (8 partials), 6.6 and 14.3 now.
+// Merge of the split partials.  D / E lanes per query row, E dims each; every
+// lane weighs its row's splits itself, l exp2(m - M), kMergeUnroll of them with
+// all loads in flight.  Eight dims (16-byte loads, four or eight rows per wave)
+// where that makes a workgroup per CU: memory latency and the partials' bytes
+// bound those (split by split with one wave per row and 4-byte loads, weights
+// across the lanes, 12.9 us for 16 ragged sequences of 33 nodes, three partials
+// per row, and 20.7 us for 4 of 257 nodes, 8 partials; 6.6 and 14.3 now).  A
+// small grid has one wave per SIMD, which spends its time on the weights and
+// sums (about 25 vector instructions per split and lane), so two dims per lane
+// spread it over four times the waves: whole calls of 1 x 4096 keys, 33 nodes
+// 22.3 -> 21.8 us, 9 nodes at 2048 keys 17.3 -> 16.4; at 264 workgroups of
+// eight dims (129 nodes) 30.2 -> 30.7, at 136 (65 nodes) 25.1 -> 24.8.
 constexpr int kMergeUnroll = 8;
-template <int D>
+template <int E>
+struct Bf16Chunk {
+    typedef uint32_t type __attribute__((ext_vector_type(E / 2)));
+};
+template <int D, int E>
 __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
-    constexpr int LPR = D / 8;          // lanes per row
+    typedef typename Bf16Chunk<E>::type chunk;
+    constexpr int LPR = D / E;          // lanes per row
     constexpr int RPB = 256 / LPR;      // rows per workgroup
     // grid: x covers the rows of one (sequence, KV head), y the (sequence, KV
     // head) pairs
@@ -950,30 +960,30 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
     int nsplit;
     const int nn_raw = a.n_nodes[b];
     if (a.shares == 0) {
-        po = a.part_o + ((int64_t)bg * a.splits * rows_g + rho) * D + dl * 8;
+        po = a.part_o + ((int64_t)bg * a.splits * rows_g + rho) * D + dl * E;
         sstride = (int64_t)rows_g * D;
         mlp = a.part_ml + ((int64_t)bg * rows_g + rho) * a.splits;
         nsplit = a.splits;  // cut below, once the loads are on their way
     } else {
         const int2 s = a.slots[b];
         nsplit = s.y - s.x + 1;
-        po = a.part_o + (((int64_t)s.x * a.hkv + g) * rows_g + rho) * D + dl * 8;
+        po = a.part_o + (((int64_t)s.x * a.hkv + g) * rows_g + rho) * D + dl * E;
         sstride = (int64_t)a.hkv * rows_g * D;
         mlp = a.part_ml + ((int64_t)g * rows_g + rho) * a.n_slots + s.x;
     }
     float M = -INFINITY, L = 0.f;
-    float acc[8];
+    float acc[E];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+    for (int e = 0; e < E; ++e) acc[e] = 0.f;
     const int last = nsplit - 1;
     for (int s0 = 0; s0 < nsplit; s0 += kMergeUnroll) {
         float2 ml[kMergeUnroll];
-        uint4 v[kMergeUnroll];
+        chunk v[kMergeUnroll];
 #pragma unroll
         for (int u = 0; u < kMergeUnroll; ++u) {
             const int sp = min(s0 + u, last);
             ml[u] = mlp[sp];
-            v[u] = *reinterpret_cast<const uint4*>(po + (int64_t)sp * sstride);
+            v[u] = *reinterpret_cast<const chunk*>(po + (int64_t)sp * sstride);
         }
         if (s0 == 0 && a.shares == 0) {
             // splits past the sequence's end left nothing
@@ -987,18 +997,17 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
         const float old = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
         L *= old;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] *= old;
+        for (int e = 0; e < E; ++e) acc[e] *= old;
         M = Mn;
 #pragma unroll
         for (int u = 0; u < kMergeUnroll; ++u) {
             if (s0 + u < nsplit) {
                 const float w = ml[u].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - Mn) * ml[u].y;
                 L += w;
-                const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[2 * e] = fmaf(w, bf16lo(x[e]), acc[2 * e]);
-                    acc[2 * e + 1] = fmaf(w, bf16hi(x[e]), acc[2 * e + 1]);
+                for (int e = 0; e < E / 2; ++e) {
+                    acc[2 * e] = fmaf(w, bf16lo(v[u][e]), acc[2 * e]);
+                    acc[2 * e + 1] = fmaf(w, bf16hi(v[u][e]), acc[2 * e + 1]);
                 }
             }
         }
@@ -1007,11 +1016,11 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
     // part has a maximum then, so L is 0) stays NaN
     const bool live = n < clamp_nodes(nn_raw, a.n_max);
     const float inv = L > 0.f ? 1.f / L : 0.f;
-    uint32_t o[4];
+    chunk o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = live ? pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv) : 0u;
-    uint16_t* op = a.out + (((int64_t)b * a.n_max + n) * a.hq + g * a.G + hh) * D + dl * 8;
-    *reinterpret_cast<uint4*>(op) = make_uint4(o[0], o[1], o[2], o[3]);
+    for (int e = 0; e < E / 2; ++e) o[e] = live ? pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv) : 0u;
+    uint16_t* op = a.out + (((int64_t)b * a.n_max + n) * a.hq + g * a.G + hh) * D + dl * E;
+    *reinterpret_cast<chunk*>(op) = o;
 }
 
 // fp32 path, on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: exact fp32
@@ -1708,12 +1717,20 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
     else go(std::false_type{}, std::false_type{});
     presto_status st = check_launch("tree_attn_bf16_kernel");
     if (st != PRESTO_OK || !p.merged()) return st;
-    const int rows_per_block = 256 / (d->head_dim / 8);
-    const dim3 mgrid((unsigned)((p.rows + rows_per_block - 1) / rows_per_block), (unsigned)(d->batch * d->hkv));
-    if (d->head_dim == 64)
-        tree_attn_merge_kernel<64><<<mgrid, 256, 0, stream>>>(a);
-    else
-        tree_attn_merge_kernel<128><<<mgrid, 256, 0, stream>>>(a);
+    const int pairs = d->batch * d->hkv;
+    auto merge = [&](auto dims) {
+        constexpr int E = decltype(dims)::value;
+        const int rpb = 256 * E / d->head_dim;
+        const dim3 mgrid((unsigned)((p.rows + rpb - 1) / rpb), (unsigned)pairs);
+        if (d->head_dim == 64)
+            tree_attn_merge_kernel<64, E><<<mgrid, 256, 0, stream>>>(a);
+        else
+            tree_attn_merge_kernel<128, E><<<mgrid, 256, 0, stream>>>(a);
+    };
+    // eight dims per lane where that makes most of a workgroup per CU
+    const int64_t wide = (int64_t)pairs * ((p.rows * d->head_dim + 2047) / 2048);
+    if (wide >= 200) merge(std::integral_constant<int, 8>{});
+    else merge(std::integral_constant<int, 2>{});
     return check_launch("tree_attn_merge_kernel");
 }
 
