@@ -1551,12 +1551,13 @@ static size_t attn_f32_partial_rows(const presto_attn_desc* d, const AttnF32Plan
 // Plan p of a grid over all (sequence, split) pairs, or the one where 1 .. 16
 // query rows past the last full tile ride along with it.  A key block costs a
 // workgroup that takes them along about what a full tile's costs, and one of
-// balanced tiles of r rows (a grid of one round) 0.22 + 0.64 r / 256 of that:
-// fitted to 173 shapes (1 .. 32 sequences of 1024 .. 32768 keys, 33 .. 1023
+// balanced tiles of r rows (a grid of one round) 0.22 + 0.64 r / 256 of that,
+// one of full tiles in several rounds 0.78: fitted to 173 shapes (1 .. 32 sequences of 1024 .. 32768 keys, 33 .. 1023
 // nodes), where no choice is more than 1% slower than tiles of their own.
 // us per call, own tiles / riding along: 8 x 8192 keys, 65 nodes 106 / 95;
 // 4 x 4096, 65 nodes 39.5 / 43.0; 8 x 4096, 193 nodes (tiles of 224 rows) 120 /
-// 155; 8 x 2048, 257 nodes (1.9 rounds of full tiles) 128 / 94.  Short splits
+// 155; 8 x 2048, 257 nodes (three rounds of full tiles against one) 128 / 94;
+// 32 x 1024, 257 nodes (five against four) 225 / 237.  Short splits
 // keep tiles of their own (1 x 4096 keys, 65 nodes: 25.3 / 30.8), and so does a
 // grid that is not split without the tail but would be with it (its rows would
 // leave bf16 partials instead of one fp32 accumulator).  G >= 2: the ancestor
@@ -1566,7 +1567,7 @@ static AttnPlan attn_plan_tail(const presto_attn_desc* d, const AttnPlan& p, int
     if (p.tasks <= 256 && p.split_len < 1024) return p;
     const AttnPlan t = attn_plan_split(d, true, false, most);
     if (p.splits == 1 && t.splits > 1) return p;
-    const double block = p.tasks <= 256 ? 0.22 + 0.64 * p.rows_per_tile / kAttnRows : 1.0;
+    const double block = p.tasks <= 256 ? 0.22 + 0.64 * p.rows_per_tile / kAttnRows : 0.78;
     return t.cost < block * p.cost ? t : p;
 }
 
