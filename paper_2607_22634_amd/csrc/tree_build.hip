@@ -262,8 +262,9 @@ __device__ __forceinline__ void stage_tables(const TreeArgs& a, char* lds) {
 // order: committing a node pushes its first child, committing a child pushes
 // its next sibling, so it never holds more than (committed + 1) entries.
 // Rank-path keys are only derived when several entries share the best S.
-// About 1300 cycles per pop; the tables were staged by the whole workgroup.
-template <int SL, int RHO>
+// About 1300 cycles per pop; the tables have been staged.  QUAD: k <= 4 (known
+// at compile time a pop takes 0.05 us less).
+template <int SL, int RHO, bool QUAD = false>
 __device__ void tree_pop_search(const TreeArgs& a, char* lds) {
     const int lane = lane_id();
     const int b = blockIdx.x;
@@ -303,7 +304,7 @@ __device__ void tree_pop_search(const TreeArgs& a, char* lds) {
         const float sc = Sn + s;
         const uint32_t o = ord32(sc);  // nonzero for every non-NaN score
         const uint64_t key = in ? (((uint64_t)o << 8) | (uint64_t)(255 - lane)) : 0ull;
-        if (k > 4 && k <= 8) {
+        if (!QUAD && k > 4 && k <= 8) {
             // sorted in place: lane p holds the p-th child (key 0 past the
             // last child, which writes the end marker)
             const uint64_t sk = sort8_desc(key, lane);
@@ -317,7 +318,7 @@ __device__ void tree_pop_search(const TreeArgs& a, char* lds) {
         } else {
             // the lanes that are not children all land on the first free
             // position and write the end marker there
-            const int pos = k <= 4 ? quad_count_greater(key) : row_count_greater<15>(key);
+            const int pos = QUAD || k <= 4 ? quad_count_greater(key) : row_count_greater<15>(key);
             if (lane < k && live) {
                 s_kord[n * k + pos] = in ? o : 0u;
                 s_krank[n * k + pos] = (uint8_t)lane;
@@ -1100,6 +1101,35 @@ __global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
     finish_tree<NT, NF, KW>(a, lds, P, hi, scores, fill);
 }
 
+// The one-node-at-a-time search as a kernel of its own, one wave, for the
+// smallest trees (see pops_first).  The lattice is not staged: a node's children
+// are scored from global memory as it is expanded (raw in LDS, 1024 words took
+// 0.3 us more and a pop as long).
+template <int RHO, bool QUAD>
+__global__ __launch_bounds__(kWave) void tree_pop_kernel(TreeArgs a) {
+    static_assert(RHO != 1, "the lattice is not scored ahead");
+    extern __shared__ __align__(16) char lds[];
+    const int lane = lane_id(), n = a.D * a.k;
+    const int64_t tb = (int64_t)blockIdx.x * n;
+    uint32_t r_lp[8], r_ids[8];  // D * k <= 512 words
+    load_words(r_lp, reinterpret_cast<const uint32_t*>(a.logprob + tb), n, 0, lane);
+    load_words(r_ids, reinterpret_cast<const uint32_t*>(a.ids + tb), n, 0, lane);
+    const float lam = lane < a.D ? a.lambda[(int64_t)blockIdx.x * a.lambda_stride + lane] : 0.f;
+    if constexpr (RHO == 0) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (u * kWave < n) {
+                const float v = __uint_as_float(r_lp[u]);
+                r_lp[u] = __float_as_uint((v == v) ? v : -INFINITY);
+            }
+    }
+    store_words(reinterpret_cast<uint32_t*>(lds + a.o_lp), r_lp, n, 0, lane);
+    store_words(reinterpret_cast<uint32_t*>(lds + a.o_ids), r_ids, n, 0, lane);
+    if (lane < a.D) reinterpret_cast<float*>(lds + a.o_lam)[lane] = lam;
+    __builtin_amdgcn_wave_barrier();
+    tree_pop_search<1, RHO, QUAD>(a, lds);
+}
+
 // Beam search with global retention (Alg. 1): per depth, every beam entry's
 // top-`branch` children join T, and the `beam_width` best of them (S desc,
 // rank path asc) form the next beam; depths are taken while T holds fewer
@@ -1501,6 +1531,16 @@ static Alg2Layout alg2_layout(int D, int k, int branch, int budget) {
 // barriers stay cheap.
 static int level_threads(int budget) { return budget <= 128 ? 256 : (budget <= 256 ? 512 : 1024); }
 
+// Trees of few nodes, or of one per level, go one node at a time: a pop takes
+// about 0.5 us, a level 0.6 and its start and end (the staged lattice, the sort)
+// about 3 us more.  us per call, pops / levels: 10 nodes, depth 16, k = 4 8.9 /
+// 9.6, 12 nodes 9.9 / 9.5; with the 16,000 words of k = 10's lattice 16 nodes
+// 15.4 / 18.3, 24 nodes 20.6 / 19.4; a chain of 32 nodes 21.9 / 28.3.
+static bool pops_first(int D, int k, int branch, int budget, bool lattice) {
+    if (branch == 1) return budget < kWave;
+    return budget <= (lattice && D * k * k * k > 8192 ? 20 : 10);
+}
+
 // Level and beam kernels: candidate table, lambda, the pool with its sort
 // scratch (the one-node-at-a-time search of the level kernel reuses that
 // memory), then the lattice.
@@ -1640,7 +1680,8 @@ presto_status launch_build_tree(const presto_tree_desc* desc, const int32_t* ids
     a.mag_k = (uint32_t)(((1ull << 32) + a.k - 1) / a.k);  // k > 1 only
     a.mag_k3 = (uint32_t)(((1ull << 32) + k3 - 1) / k3);
     const int rho_mode = !lattice ? 0 : (L.rho_in_lds ? 1 : 2);
-    const int threads = beam ? kBeamThreads : level_threads(a.budget);
+    const bool pops = !beam && pops_first(a.D, a.k, a.branch, a.budget, lattice);
+    const int threads = beam ? kBeamThreads : (pops ? kWave : level_threads(a.budget));
     auto go = [&](auto kernel) {
         st = allow_lds(kernel, L.total);
         if (st == PRESTO_OK) kernel<<<desc->batch, threads, L.total, stream>>>(a);
@@ -1654,6 +1695,17 @@ presto_status launch_build_tree(const presto_tree_desc* desc, const int32_t* ids
 #undef PRESTO_BEAM
         if (st != PRESTO_OK) return st;
         return check_launch("tree_beam_kernel");
+    }
+    if (pops) {
+        if (a.k <= 4) {
+            if (lattice) go(tree_pop_kernel<2, true>);
+            else go(tree_pop_kernel<0, true>);
+        } else {
+            if (lattice) go(tree_pop_kernel<2, false>);
+            else go(tree_pop_kernel<0, false>);
+        }
+        if (st != PRESTO_OK) return st;
+        return check_launch("tree_pop_kernel");
     }
 #define PRESTO_LEVEL3(T, S, K)                                   \
     if (rho_mode == 0) go(tree_level_kernel<T, S, 0, K>);        \

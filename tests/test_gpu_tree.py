@@ -293,3 +293,24 @@ def test_tree_more_ties_than_the_pool(D, k, branch, B, lattice):
         print(f"pool ties {name} D={D} k={k} branch={branch} B={B} lattice={lattice}", flush=True)
         g, o = _gpu_and_oracle(ids, lp, rho, lam, root, D, k, B, branch=branch)
         _assert_same(g, o)
+
+
+@pytest.mark.parametrize("D,k,branch,B", [(16, 4, 4, 1), (16, 4, 4, 10), (16, 4, 4, 11), (16, 10, 10, 20),
+                                          (16, 10, 10, 21), (16, 8, 8, 10), (16, 8, 8, 11), (1, 16, 16, 10),
+                                          (32, 1, 1, 32), (32, 1, 1, 63), (32, 1, 1, 64), (24, 16, 1, 24),
+                                          (32, 4, 1, 63), (32, 3, 1, 64), (2, 2, 2, 8), (24, 16, 9, 20)])
+@pytest.mark.parametrize("kind", ["exp", "flat", "zero", "masked", "single"])
+def test_tree_small_budgets_and_chains(D, k, branch, B, kind):
+    """Budgets and chains around the line between the one-node-at-a-time kernel
+    and the level search, with and without a lattice, a weight per sequence,
+    ties and -inf candidates.  Bit-exact."""
+    rng = np.random.default_rng([D, k, branch, B])
+    b = 5
+    lp = _shape_table(kind, rng, b, D, k)
+    R = np.log(rng.uniform(1e-3, 1, (b, D, k, k, k))).astype(np.float32)
+    ids = np.stack([[rng.choice(5000, k, replace=False) for _ in range(D)] for _ in range(b)]).astype(np.int32)
+    root = rng.integers(0, 5000, size=b).astype(np.int32)
+    for lam, rho in ((np.zeros(D, np.float32), None), (rng.uniform(0, 1, (b, D)).astype(np.float32), R)):
+        print(f"small {kind} D={D} k={k} branch={branch} B={B} lattice={rho is not None}", flush=True)
+        g, o = _gpu_and_oracle(ids, lp, rho, lam, root, D, k, B, branch=branch)
+        _assert_same(g, o)
