@@ -1,8 +1,9 @@
 // Stage 2: prefix-aligned scoring and draft-tree construction.
 //
 // One workgroup builds one sequence's tree; the batch runs in parallel.
-// Three kernels, one per mode:
+// The kernels:
 //   tree_level_kernel   best-first (the budget best prefixes), level by level
+//   tree_pop_kernel     the same for few nodes and chains, one node at a time
 //   tree_beam_kernel    beam search with global retention
 //   tree_alg2_kernel    Alg. 2 as printed
 #include <math.h>
@@ -39,7 +40,7 @@ struct TreeArgs {
     // the level and beam kernels,
     int o_lam, o_pool, o_key, o_hist, o_fine, o_list, o_place, o_row, o_par, o_misc;
     int32_t cap;  // entries the pool holds, the root included
-    // one-node-at-a-time search (shares the pool's memory),
+    // the one-node-at-a-time kernel,
     int o_kord, o_krank, o_rec, o_pkey;
     // literal Alg. 2: T (capacity budget + branch - 1)
     int o_tmeta, o_tS, o_tkey, o_tplace;
@@ -137,12 +138,6 @@ __device__ __forceinline__ uint32_t write_lane(uint32_t x, uint32_t v, int l) {
     asm("v_writelane_b32 %0, %1, m0" : "+v"(x) : "s"(sv), "{m0}"(sl));
     return x;
 }
-
-// Number of frontier slots per lane a pop works on (a compile-time tag).
-template <int A>
-struct SlotCount {
-    static constexpr int value = A;
-};
 
 // Token scores fl(log q + fl(lambda * log rho)), NaN -> -inf, of candidate r
 // at drafter row `row` in the trigram context (c2, c1) of candidate ranks.
@@ -251,24 +246,21 @@ __device__ __forceinline__ void stage_tables(const TreeArgs& a, char* lds) {
     __syncthreads();
 }
 
-// Best-first search one node at a time, by one wave: the path of inputs that
-// the level search below cannot bound (its pool overflows on very many equal
-// scores).  Per
-// committed node LDS holds one 8-byte record (parent, rank, depth, S) and its
-// children in commit order; the frontier lives in registers spread over the
-// 64 lanes (SL slots per lane), each slot only (S, packed metadata): a pop is
-// a per-lane max, one DPP wave max and a ballot.  The frontier holds, for
-// every committed node, only its next not-yet-committed child in commit
-// order: committing a node pushes its first child, committing a child pushes
-// its next sibling, so it never holds more than (committed + 1) entries.
-// Rank-path keys are only derived when several entries share the best S.
-// About 1300 cycles per pop; the tables have been staged.  QUAD: k <= 4 (known
-// at compile time a pop takes 0.05 us less).
-template <int SL, int RHO, bool QUAD = false>
+// Best-first search one node at a time, by one wave, for trees of at most 64
+// rows (see pops_first).  Per committed node LDS holds one 8-byte record (parent,
+// rank, depth, S) and its children in commit order; the frontier lives in
+// registers, one entry per lane, (S, packed metadata) each: a pop is a DPP wave
+// max and a ballot.  The frontier holds, for every committed node, only its next
+// not-yet-committed child in commit order: committing a node pushes its first
+// child, committing a child pushes its next sibling, so it never holds more than
+// (committed + 1) entries.  Rank-path keys are only derived when several entries
+// share the best S.  About 1300 cycles per pop; the tables have been staged.
+// QUAD: k <= 4 (known at compile time a pop takes 0.05 us less).
+template <int RHO, bool QUAD>
 __device__ void tree_pop_search(const TreeArgs& a, char* lds) {
     const int lane = lane_id();
     const int b = blockIdx.x;
-    const int D = a.D, k = a.k, N = a.N, W = a.W, wbits = a.wbits, per_word = a.per_word;
+    const int D = a.D, k = a.k, N = a.N, wbits = a.wbits, per_word = a.per_word;
     const TokenScores<RHO> scores(a, lds);
     const int32_t* s_ids = reinterpret_cast<const int32_t*>(lds + a.o_ids);
     // children of every committed node in commit order: ord(S) (0 ends the
@@ -354,85 +346,48 @@ __device__ void tree_pop_search(const TreeArgs& a, char* lds) {
     int c_rank;
     expand(0, 0, 0, 0, 0.f, c_ord, c_rank);
 
-    // frontier slots: slot j of lane l is entry j * 64 + l
-    uint32_t fS[SL], fM[SL];
-#pragma unroll
-    for (int j = 0; j < SL; ++j) fS[j] = fM[j] = 0u;
-    if (lane == 0) {
-        fS[0] = c_ord;
-        fM[0] = pack_meta(0, c_rank, 1, 0, 0);
-    }
+    // the frontier: entry l in lane l (S as ord32, 0 for none)
+    uint32_t fS = lane == 0 ? c_ord : 0u, fM = lane == 0 ? pack_meta(0, c_rank, 1, 0, 0) : 0u;
     int fcount = 1, committed = 1;
 
-    // One pop: commit the best frontier entry and push its successors;
-    // false once the frontier is exhausted.  Slots fill lane-major (slot j
-    // holds entries 64 j .. 64 j + 63), so only the first A slots of every
-    // lane can be occupied, A = fcount / 64 + 1 counting the next fresh one:
-    // the per-slot work follows the frontier allocated so far.
-    auto pop = [&](auto act) -> bool {
-        constexpr int A = decltype(act)::value;
-        uint32_t lm = 0u;
-#pragma unroll
-        for (int j = 0; j < A; ++j) lm = max(lm, fS[j]);
-        const uint32_t M = wave_max_u32_dpp(lm);
-        if (M == 0u) return false;  // frontier exhausted: the whole candidate tree is committed
-
+    // commit the best frontier entry and push its successors, until the budget
+    // is spent or the frontier exhausted (the whole candidate tree committed)
+    while (committed - 1 < a.budget) {
+        const uint32_t M = wave_max_u32_dpp(fS);
+        if (M == 0u) break;
         // winner: the unique entry holding M, else the one with the smallest path key
-        int cnt = 0, jsel = 0;
-#pragma unroll
-        for (int j = A - 1; j >= 0; --j) {
-            const bool hit = fS[j] == M;
-            cnt += hit ? 1 : 0;
-            jsel = hit ? j : jsel;
-        }
-        const uint64_t any = __ballot(cnt > 0);
+        const uint64_t any = __ballot(fS == M);
         int w;
-        if (__popcll(any) == 1 && __ballot(cnt > 1) == 0ull) {
+        if (__popcll(any) == 1) {
             w = __ffsll((unsigned long long)any) - 1;
         } else {
-            uint32_t bk[4] = {~0u, ~0u, ~0u, ~0u};
-            int bj = 0;
-            for (int j = 0; j < A; ++j) {
-                if (fS[j] == M) {
-                    const int p = fM[j] & 1023;
-                    uint4 acc = make_uint4(0u, 0u, 0u, 0u);
-                    int y = p;
-                    uint4 st = s_pkey[y];
-                    uint32_t m = s_rec[y].x;
-                    while (y != 0 && st.x == 0u) {
-                        acc = add_digit(acc, (m >> 14) & 63, (m >> 10) & 15);
-                        y = m & 1023;
-                        st = s_pkey[y];
-                        m = s_rec[y].x;
-                    }
-                    const uint4 kp = make_uint4(acc.x | st.x, acc.y | st.y, acc.z | st.z, acc.w | st.w);
-                    if (y != p) s_pkey[p] = kp;  // lanes storing the same node store the same key
-                    const uint4 kv = add_digit(kp, (fM[j] >> 14) & 63, (fM[j] >> 10) & 15);
-                    const uint32_t kw[4] = {kv.x, kv.y, kv.z, kv.w};
-                    const bool less =
-                        kw[0] != bk[0] ? kw[0] < bk[0]
-                                       : (kw[1] != bk[1] ? kw[1] < bk[1]
-                                                         : (kw[2] != bk[2] ? kw[2] < bk[2] : kw[3] < bk[3]));
-                    if (less) {
-                        bk[0] = kw[0]; bk[1] = kw[1]; bk[2] = kw[2]; bk[3] = kw[3];
-                        bj = j;
-                    }
+            bool t = fS == M;
+            uint32_t kw[4] = {~0u, ~0u, ~0u, ~0u};
+            if (t) {
+                const int p = fM & 1023;
+                uint4 acc = make_uint4(0u, 0u, 0u, 0u);
+                int y = p;
+                uint4 st = s_pkey[y];
+                uint32_t m = s_rec[y].x;
+                while (y != 0 && st.x == 0u) {
+                    acc = add_digit(acc, (m >> 14) & 63, (m >> 10) & 15);
+                    y = m & 1023;
+                    st = s_pkey[y];
+                    m = s_rec[y].x;
                 }
+                const uint4 kp = make_uint4(acc.x | st.x, acc.y | st.y, acc.z | st.z, acc.w | st.w);
+                if (y != p) s_pkey[p] = kp;  // lanes storing the same node store the same key
+                const uint4 kv = add_digit(kp, (fM >> 14) & 63, (fM >> 10) & 15);
+                kw[0] = kv.x; kw[1] = kv.y; kw[2] = kv.z; kw[3] = kv.w;
             }
-            bool t = cnt > 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint32_t mq = wave_min_u32_dpp(t ? bk[q] : ~0u);
-                t = t && bk[q] == mq;
+                const uint32_t mq = wave_min_u32_dpp(t ? kw[q] : ~0u);
+                t = t && kw[q] == mq;
             }
             w = __ffsll((unsigned long long)__ballot(t)) - 1;
-            jsel = bj;
         }
-        uint32_t lmeta = 0u;
-#pragma unroll
-        for (int j = 0; j < A; ++j) lmeta = j == jsel ? fM[j] : lmeta;
-        const uint32_t meta = (uint32_t)__builtin_amdgcn_readlane((int)lmeta, w);
-        const int eslot = __builtin_amdgcn_readlane(jsel, w);
+        const uint32_t meta = (uint32_t)__builtin_amdgcn_readlane((int)fM, w);
         const int p = meta & 1023, r = (meta >> 10) & 15, d = (meta >> 14) & 63, rp = (meta >> 20) & 15;
         const int pos = (meta >> 24) & 15;
         const float S = unord32(M);
@@ -453,7 +408,7 @@ __device__ void tree_pop_search(const TreeArgs& a, char* lds) {
         expand(n, d, r, rp, S, kid_ord, kid_rank);
         const uint32_t sib_ord = pos + 1 < k ? sib_raw : 0u;
 
-        // pushes: the first reuses the popped slot, the second takes a fresh slot
+        // pushes: the first takes the popped entry's lane, the second a fresh one
         uint32_t xS = 0u, xM = 0u, yS = 0u, yM = 0u;
         if (kid_ord != 0u) {
             xS = kid_ord;
@@ -469,84 +424,45 @@ __device__ void tree_pop_search(const TreeArgs& a, char* lds) {
                 xM = m;
             }
         }
-        const bool second = yS != 0u;
-        const int ylane = fcount & (kWave - 1), yslot = fcount >> 6;
-        if constexpr (A <= 2) {
-            // one lane of one slot each: lane writes from scalar values (with
-            // a single slot in use both go to slot 0)
-#pragma unroll
-            for (int j = 0; j < A; ++j) {
-                if (A == 1 || j == eslot) {
-                    fS[j] = write_lane(fS[j], xS, w);
-                    fM[j] = write_lane(fM[j], xM, w);
-                }
-                if (second && (A == 1 || j == yslot)) {
-                    fS[j] = write_lane(fS[j], yS, ylane);
-                    fM[j] = write_lane(fM[j], yM, ylane);
-                }
-            }
-        } else {
-            // more slots: one select per slot instead of a branch per slot
-#pragma unroll
-            for (int j = 0; j < A; ++j) {
-                const bool px = lane == w && j == eslot;
-                const bool py = second && lane == ylane && j == yslot;
-                fS[j] = px ? xS : (py ? yS : fS[j]);
-                fM[j] = px ? xM : (py ? yM : fM[j]);
-            }
+        fS = write_lane(fS, xS, w);
+        fM = write_lane(fM, xM, w);
+        if (yS != 0u) {
+            fS = write_lane(fS, yS, fcount);
+            fM = write_lane(fM, yM, fcount);
+            ++fcount;
         }
-        if (second) ++fcount;
-        return true;
-    };
-    while (committed - 1 < a.budget) {
-        const int need = min((fcount >> 6) + 1, SL);
-        bool go;
-        if (need <= 1) go = pop(SlotCount<1>{});
-        else if (SL <= 2 || need <= 2) go = pop(SlotCount<(SL < 2 ? SL : 2)>{});
-        else if (SL <= 3 || need <= 3) go = pop(SlotCount<(SL < 3 ? SL : 3)>{});
-        else if (SL <= 4 || need <= 4) go = pop(SlotCount<(SL < 4 ? SL : 4)>{});
-        else if (SL <= 5 || need <= 5) go = pop(SlotCount<(SL < 5 ? SL : 5)>{});
-        else if (SL <= 8 || need <= 8) go = pop(SlotCount<(SL < 8 ? SL : 8)>{});
-        else go = pop(SlotCount<SL>{});
-        if (!go) break;
     }
     __builtin_amdgcn_wave_barrier();
 
     // Output rows and ancestor masks, one node per lane: the mask of node n has
-    // the bits of n and of every node on its parent chain (SL >= W =
-    // ceil(N / 64) words suffice).
+    // the bits of n and of every node on its parent chain.
     const int64_t ob = (int64_t)b * N;
     const int root_tok = __builtin_amdgcn_readfirstlane(a.root_token[b]);
-    for (int i = lane; i < N; i += kWave) {
-        uint64_t words[SL];
-#pragma unroll
-        for (int q = 0; q < SL; ++q) words[q] = 0ull;
-        if (i < committed) {
-            const uint2 rec = s_rec[i];
-            const int p = i == 0 ? -1 : (int)(rec.x & 1023);
-            const int r = (rec.x >> 10) & 15, d = i == 0 ? 0 : (rec.x >> 14) & 63;
-            a.parent[ob + i] = p;
-            a.token[ob + i] = i == 0 ? root_tok : s_ids[(d > 0 ? d - 1 : 0) * k + r];
-            a.depth[ob + i] = d;
-            a.rank[ob + i] = i == 0 ? -1 : r;
-            a.score[ob + i] = __uint_as_float(rec.y);
-            int x = i;
+    if (lane < N) {
+        int par = -1, tok = -1, dep = -1, rank = -1;
+        float S = -INFINITY;
+        uint64_t mask = 0ull;
+        if (lane < committed) {
+            const uint2 rec = s_rec[lane];
+            dep = lane == 0 ? 0 : (int)(rec.x >> 14) & 63;
+            const int r = (int)(rec.x >> 10) & 15;
+            tok = lane == 0 ? root_tok : s_ids[(dep > 0 ? dep - 1 : 0) * k + r];
+            par = lane == 0 ? -1 : (int)(rec.x & 1023);
+            rank = lane == 0 ? -1 : r;
+            S = __uint_as_float(rec.y);
+            int x = lane;
             while (true) {
-#pragma unroll
-                for (int q = 0; q < SL; ++q) words[q] |= q == (x >> 6) ? 1ull << (x & 63) : 0ull;
+                mask |= 1ull << x;
                 if (x == 0) break;
                 x = (int)(s_rec[x].x & 1023);
             }
-        } else {
-            a.parent[ob + i] = -1;
-            a.token[ob + i] = -1;
-            a.depth[ob + i] = -1;
-            a.rank[ob + i] = -1;
-            a.score[ob + i] = -INFINITY;
         }
-#pragma unroll
-        for (int q = 0; q < SL; ++q)
-            if (q < W) a.anc[(ob + i) * W + q] = words[q];
+        a.parent[ob + lane] = par;
+        a.token[ob + lane] = tok;
+        a.depth[ob + lane] = dep;
+        a.rank[ob + lane] = rank;
+        a.score[ob + lane] = S;
+        a.anc[ob + lane] = mask;
     }
     if (lane == 0) a.n_nodes[b] = committed;
 }
@@ -678,6 +594,9 @@ struct Pool {
 // the small trees (budget 64: 10.2 us, 11.4 with 1024), 1024 for the others
 // and the beam (budget 512: 27 us, 32 with 512).
 constexpr int kFineMax = 1024;
+// A fine bin is crowded (equal scores) from here on: placing its entries takes
+// 0.3 us per four of them, finding the budget-th best first about 10 us.
+constexpr int kCrowd = 128;
 
 template <int NT, int NF, int KW>
 __device__ __forceinline__ void init_pool(const TreeArgs& a, const Pool<KW>& P) {
@@ -694,11 +613,11 @@ __device__ __forceinline__ void init_pool(const TreeArgs& a, const Pool<KW>& P) 
     }
 }
 
-// Drops the entries of bins past J (with all their descendants: an entry's
-// score never exceeds its parent's) and closes the gaps; the parents' indices
-// and the frontier [lo, hi) move along.  Ends with a barrier.
-template <int NT, int KW>
-__device__ __forceinline__ void compact_pool(const Pool<KW>& P, uint32_t J, int& lo, int& hi) {
+// Drops the entries that keep(S, key) refuses (with all their descendants: keep
+// refuses none that precedes one it takes) and closes the gaps; the parents'
+// indices and the frontier [lo, hi) move along.  Ends with a barrier.
+template <int NT, int KW, typename Keep>
+__device__ __forceinline__ void compact_pool(const Pool<KW>& P, const Keep& keep, int& lo, int& hi) {
     const int tid = threadIdx.x, lane = lane_id();
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     uint32_t* s_wave = P.misc + 40;  // [NT / kWave], past the level counts
@@ -712,7 +631,7 @@ __device__ __forceinline__ void compact_pool(const Pool<KW>& P, uint32_t J, int&
         if (e < hi) {
             rec = P.rec[e];
             key = P.key[e];
-            alive = score_bin(__uint_as_float(rec.x)) <= J;
+            alive = keep(__uint_as_float(rec.x), key);
         }
         const uint64_t m = __ballot(alive), ml = __ballot(alive & (e < lo));
         if (lane == 0) s_wave[wv] = (uint32_t)__popcll(m) | ((uint32_t)__popcll(ml) << 16);
@@ -737,6 +656,91 @@ __device__ __forceinline__ void compact_pool(const Pool<KW>& P, uint32_t J, int&
     hi = n;
     lo = 1 + below_lo;
     __syncthreads();
+}
+
+// The place of the `budget`-th best of a set of prefixes in the total order:
+// a prefix is among them iff at_most(S, key).
+template <int KW>
+struct Bound {
+    typedef typename PathKey<KW>::type Key;
+    uint32_t s;  // ~ord32(S)
+    Key key;
+    __device__ __forceinline__ bool at_most(float S, Key k) const {
+        const uint32_t x = ~ord32(S);
+        return (x < s) | ((x == s) & !key_less<KW>(key, k));
+    }
+};
+
+// That bound over the members member(i, S, key), i < n, that return true (at
+// least `budget` of them), by nine bits of (~ord32(S), rank path) at a time: a
+// count of the members that agree with the bits known so far, in P.fine (zeros
+// on entry and on return).  Each pass takes every member anew, so that nothing
+// but the counts is stored; it ends as soon as the members left are the ones
+// missing.  Ends with a barrier.  (Eight bits and four sets of counters, one
+// barrier a pass instead of three, took 10% less here and, by the registers it
+// takes from the kernel, 20% more of the searches without ties at depth 32.)
+template <int NT, int KW, typename Member>
+__device__ __forceinline__ Bound<KW> select_best(const Pool<KW>& P, int n, uint32_t budget, const Member& member) {
+    const int tid = threadIdx.x, lane = lane_id();
+    uint32_t want[KW + 1];
+#pragma unroll
+    for (int w = 0; w <= KW; ++w) want[w] = 0u;
+    uint32_t need = budget;
+    int word = 0, shift = 23;  // shifts 23, 14, 5, and the last five bits
+    while (true) {
+        const uint32_t above = shift == 23 ? 0u : (~0u << (shift == 0 ? 5 : shift + 9));  // known bits of this word
+        for (int i0 = 0; i0 < n; i0 += NT) {
+            float S = 0.f;
+            typename Pool<KW>::Key key = P.key[0];
+            bool in = i0 + tid < n;
+            if (in) in = member(i0 + tid, S, key);
+            uint32_t x[KW + 1];
+            x[0] = ~ord32(S);
+#pragma unroll
+            for (int w = 0; w < KW; ++w) x[w + 1] = key[w];
+            uint32_t digit = 0u;
+#pragma unroll
+            for (int w = 0; w <= KW; ++w) {
+                in &= w >= word || x[w] == want[w];
+                if (w == word) {
+                    in &= (x[w] & above) == (want[w] & above);
+                    digit = shift == 0 ? x[w] & 31u : (x[w] >> shift) & 511u;
+                }
+            }
+            // equal digits, as ties have them, as one addition
+            const uint64_t m = __ballot(in);
+            if (m != 0ull) {
+                const int first = __ffsll((unsigned long long)m) - 1;
+                const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)digit, first);
+                const uint64_t same = __ballot(in & (digit == d0));
+                if (lane == first) atomicAdd(&P.fine[d0], (uint32_t)__popcll(same));
+                if (in & (digit != d0)) atomicAdd(&P.fine[digit], 1u);
+            }
+        }
+        __syncthreads();
+        uint32_t upto;
+        const uint32_t digit = threshold_bin(P.fine, need, upto);
+        const uint32_t here = P.fine[digit];
+        need -= upto - here;
+        const bool done = here == need;
+#pragma unroll
+        for (int w = 0; w <= KW; ++w) {
+            if (w == word) want[w] |= (digit << shift) | (done ? (1u << shift) - 1u : 0u);
+            if (w > word && done) want[w] = ~0u;
+        }
+        __syncthreads();  // the counts have been read
+        for (int i = tid; i < 512; i += NT) P.fine[i] = 0u;
+        __syncthreads();
+        if (done) break;
+        shift = shift == 0 ? 23 : (shift == 5 ? 0 : shift - 9);
+        word += shift == 23 ? 1 : 0;
+        if (word > KW) break;  // not reached: the paths are distinct
+    }
+    Bound<KW> r;
+    r.s = want[0];
+#pragma unroll
+    for (int w = 0; w < KW; ++w) r.key[w] = want[w + 1];
+    return r;
 }
 
 // Rows nt + 1 .. budget from prefixes of S = -inf, which follow every finite
@@ -807,9 +811,11 @@ __device__ int fill_below(const TreeArgs& a, const Pool<KW>& P, const uint16_t* 
 // comparing all pairs of 1000 entries took about as long as the search.
 // `fill`: fewer than `budget` entries, and candidates of S = -inf were left
 // out of the pool (fill_below).
-template <int NT, int NF, int KW, typename Scores>
-__device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const Pool<KW>& P, int n,
-                                            const Scores& scores, bool fill) {
+// CUT: entries past `bound` are left out.  Without it, false is returned, with
+// nothing written, where a bin is crowded and many entries are too many.
+template <int NT, int NF, int KW, bool CUT, typename Scores>
+__device__ __forceinline__ bool place_tree(const TreeArgs& a, char* lds, const Pool<KW>& P, int n,
+                                           const Scores& scores, bool fill, const Bound<KW>& bound) {
     constexpr int PER = NF / NT;
     static_assert(PER >= 1 && PER * NT == NF && NF <= kFineMax, "whole bins per thread");
     const int tid = threadIdx.x, lane = lane_id();
@@ -837,21 +843,28 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const 
         const float u = fminf(fmaxf(-S * inv, 0.f), 1.f);
         return (int)fminf(u * u * (float)NF, (float)(NF - 1));
     };
+    if constexpr (CUT) M = budget;
+    auto takes = [&](int e, float S) __attribute__((always_inline)) {
+        if constexpr (CUT) return score_bin(S) <= J && bound.at_most(S, P.key[e]);
+        return score_bin(S) <= J;
+    };
     for (int e = 1 + tid; e < n; e += NT) {
         const float S = P.S(e);
-        if (score_bin(S) <= J) P.place[e] = (uint16_t)atomicAdd(&P.fine[fine_bin(S)], 1u);
+        if (takes(e, S)) P.place[e] = (uint16_t)atomicAdd(&P.fine[fine_bin(S)], 1u);
     }
     __syncthreads();
     // counts -> offsets, PER consecutive bins per thread
     {
-        uint32_t c[PER], sum = 0u;
+        uint32_t c[PER], sum = 0u, most = 0u;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             c[i] = P.fine[tid * PER + i];
             sum += c[i];
+            most = max(most, c[i]);
         }
         const uint32_t incl = wave_scan_dpp(sum);
         if (lane == kWave - 1) P.misc[wv] = incl;
+        if (!CUT && most > kCrowd) P.misc[61] = 1u;
         __syncthreads();
         uint32_t off = incl - sum;
         for (int w = 0; w < wv; ++w) off += P.misc[w];
@@ -863,9 +876,10 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const 
         if (tid == NT - 1) P.fine[NF] = off;
     }
     __syncthreads();
+    if (!CUT && (int)M >= budget + kCrowd / 2 && P.misc[61] != 0u) return false;
     for (int e = 1 + tid; e < n; e += NT) {
         const float S = P.S(e);
-        if (score_bin(S) <= J) P.list[P.fine[fine_bin(S)] + P.place[e]] = (uint16_t)e;
+        if (takes(e, S)) P.list[P.fine[fine_bin(S)] + P.place[e]] = (uint16_t)e;
     }
     __syncthreads();
     int nt = min((int)M, budget);  // non-root rows
@@ -953,6 +967,25 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const 
         }
     }
     if (tid == 0) a.n_nodes[b] = nt + 1;
+    return true;
+}
+
+template <int NT, int NF, int KW, typename Scores>
+__device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const Pool<KW>& P, int n,
+                                            const Scores& scores, bool fill) {
+    if (place_tree<NT, NF, KW, false>(a, lds, P, n, scores, fill, Bound<KW>())) return;
+    // without the entries past the budget-th best
+    for (int i = threadIdx.x; i < NF; i += NT) P.fine[i] = 0u;
+    __syncthreads();
+    uint32_t M;
+    const uint32_t J = threshold_bin(P.hist, a.budget, M);
+    const Bound<KW> bound =
+        select_best<NT, KW>(P, n - 1, a.budget, [&](int i, float& S, typename Pool<KW>::Key& key) {
+            S = P.S(i + 1);
+            key = P.key[i + 1];
+            return score_bin(S) <= J;
+        });
+    place_tree<NT, NF, KW, true>(a, lds, P, n, scores, fill, bound);
 }
 
 // Best-first tree, level by level.
@@ -973,7 +1006,14 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const 
 // and finish_tree sorts what remains at or above the threshold.  One barrier
 // per level, two where it is counted first.  A level that overflows the pool
 // is entered again after the entries that its own scores have ruled out are
-// dropped.
+// dropped, and where (nearly) equal scores at the threshold alone are more than
+// the pool holds, after the budget-th best is found exactly, path and all
+// (select_best, 10 to 40 us; its bound also holds for the levels below).
+// All scores alike, 8 sequences, against the merged set: depth 12, k = 12,
+// budget 256 207 -> 38 us; 32, 4, 128 44 -> 24; 16, 16, 512 925 -> 66.  Two
+// candidates of probability 1 in every row, which no softmax gives, tie at
+// every level anew: 16, 4, 64 55 -> 101; 32, 4, 128 238 -> 510; larger budgets
+// gain (16, 10, 1023 1953 -> 577).
 //
 // Latency bounds it: a level is a chain of LDS round trips (count, record,
 // score, place, record) of about 1000 cycles, on one workgroup per sequence.
@@ -983,26 +1023,24 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const 
 // 14.8; budget 256, k = 8: 89.4 -> 16.4.
 // Candidates of S = -inf are left out (all their descendants tie with them);
 // where only they can fill the tree, a depth-first walk adds them (fill_below).
-// More (nearly) equal scores at the threshold than the pool holds, as when two
-// candidates of probability 1 share a row, go to the one-node-at-a-time search.
-template <int NT, int SL, int RHO, int KW>
-__global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
-    extern __shared__ __align__(16) char lds[];
+//
+// search_levels: levels d .. D from the pool's entries [lo, hi) of the one above.
+// False (TIES = false only): more (nearly) equal scores at the threshold than
+// the pool holds; the pool is as before level d, but for entries past hi, the
+// histogram holds all the level's candidates.  TIES goes on from there.
+template <int NT, int RHO, int KW, bool TIES>
+__device__ __forceinline__ bool search_levels(const TreeArgs& a, const Pool<KW>& P, const TokenScores<RHO>& scores,
+                                              int& d, int& lo, int& hi, uint32_t& J, bool& below) {
+    typedef typename Pool<KW>::Key Key;
     const int tid = threadIdx.x, lane = lane_id();
     const int D = a.D, k = a.k;
-    const Pool<KW> P(a, lds);
-    typedef typename Pool<KW>::Key Key;
-    constexpr int NF = NT < 512 ? 512 : kFineMax;
-    init_pool<NT, NF, KW>(a, P);
-    stage_tables<NT, RHO>(a, lds);
-    const TokenScores<RHO> scores(a, lds);
-
-    int lo = 0, hi = 1;         // entries of the level above
-    uint32_t J = kBins - 1;     // candidates in later bins are dropped
-    bool below = false;         // a candidate of S = -inf was left out
-    bool again = false;         // the level is entered for the second time
+    bool again = false;    // the level is entered for the second time, counted as it is
+    bool over = TIES;      // its ties are too many
+    bool recount = false;  // entered after that, to be counted anew
+    bool bounded = false;  // candidates past `bound` are dropped
+    Bound<KW> bound;
     uint32_t known = 0u;
-    for (int d = 1; d <= D;) {
+    while (d <= D) {
         const int total = (hi - lo) * k;
         const int wi = (d - 1) / a.per_word, sh = 32 - ((d - 1) % a.per_word + 1) * a.wbits;
         // candidate i of the level: entry p's child of rank r
@@ -1027,9 +1065,41 @@ __global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
             below |= in & (S == -INFINITY);
             rec.x = __float_as_uint(S);
             bin = score_bin(S);
-            return in & (S > -INFINITY) & (bin <= J);
+            in = in & (S > -INFINITY) & (bin <= J);
+            if constexpr (TIES)
+                if (bounded) in = in && bound.at_most(S, Pool<KW>::child_key(P.key[p], wi, sh, r));
+            return in;
         };
-        const bool counted = total > NT || again;
+        if constexpr (TIES) {
+            if (over) {
+                // the exact bound over the pool and the level, and the pool without what it rules out
+                const int held = hi - 1;
+                bound = select_best<NT, KW>(P, held + total, a.budget, [&](int i, float& S, Key& key) {
+                    if (i < held) {
+                        S = P.S(i + 1);
+                        key = P.key[i + 1];
+                        return true;
+                    }
+                    int p, r;
+                    uint2 rec;
+                    uint32_t bin;
+                    const bool in = score(i - held, p, r, rec, bin);
+                    S = __uint_as_float(rec.x);
+                    key = Pool<KW>::child_key(P.key[p], wi, sh, r);
+                    return in;
+                });
+                bounded = true;
+                if (tid == 0) P.misc[d] = 0u;
+                compact_pool<NT, KW>(P, [&](float S, Key key) { return bound.at_most(S, key); }, lo, hi);
+                for (int i = tid; i < kBins; i += NT) P.hist[i] = 0u;
+                __syncthreads();
+                for (int e = 1 + tid; e < hi; e += NT) atomicAdd(&P.hist[score_bin(P.S(e))], 1u);
+                over = again = false;
+                recount = true;
+                continue;
+            }
+        }
+        const bool counted = (total > NT && !recount) || again;
         if (counted && !again) {
             for (int i = tid; i < total; i += NT) {
                 int p, r;
@@ -1064,34 +1134,42 @@ __global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
         if (hi + entered > a.cap) {
             // the histogram holds every candidate of the level, entered or not
             J = threshold_bin(P.hist, a.budget, known);
-            if ((int)known >= a.cap || again) {
-                hi += entered;
-                break;
-            }
             __syncthreads();  // every wave has read the level's count
+            if ((int)known >= a.cap) {
+                if constexpr (!TIES) return false;
+                over = true;
+                continue;
+            }
             if (tid == 0) P.misc[d] = 0u;
-            compact_pool<NT, KW>(P, J, lo, hi);
+            compact_pool<NT, KW>(P, [&](float S, Key) { return score_bin(S) <= J; }, lo, hi);
             again = true;
             continue;
         }
-        again = false;
+        again = recount = false;
         lo = hi;
         hi += entered;
         ++d;
         if (entered == 0) break;
         if (!counted && hi > a.budget) J = threshold_bin(P.hist, a.budget, known);
     }
-    // the whole workgroup agrees on the search's outcome (the counts are
-    // shared; a wave's J may differ, finish_tree takes it anew)
-    if (hi > a.cap) {
-        // every wave has read the counts and the histogram that led here: the
-        // one-node-at-a-time search writes over that memory (its records reach
-        // the histogram, and at some shapes the counts, from k = 9 on), and a
-        // wave that read zeros there would take another way out
-        __syncthreads();
-        if (tid < kWave) tree_pop_search<SL, RHO>(a, lds);
-        return;
-    }
+    return true;
+}
+
+template <int NT, int RHO, int KW>
+__global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
+    extern __shared__ __align__(16) char lds[];
+    const Pool<KW> P(a, lds);
+    constexpr int NF = NT < 512 ? 512 : kFineMax;
+    init_pool<NT, NF, KW>(a, P);
+    stage_tables<NT, RHO>(a, lds);
+    const TokenScores<RHO> scores(a, lds);
+    int d = 1, lo = 0, hi = 1;  // next level, entries of the one above
+    uint32_t J = kBins - 1;     // candidates in later bins are dropped
+    bool below = false;         // a candidate of S = -inf was left out
+    if (!search_levels<NT, RHO, KW, false>(a, P, scores, d, lo, hi, J, below))
+        search_levels<NT, RHO, KW, true>(a, P, scores, d, lo, hi, J, below);
+    // the counts are shared, so the whole workgroup agrees on the outcome (a
+    // wave's J may differ, finish_tree takes it anew)
     bool fill = false;
     if (hi - 1 < a.budget) {
         if (below) P.misc[63] = 1u;
@@ -1127,7 +1205,7 @@ __global__ __launch_bounds__(kWave) void tree_pop_kernel(TreeArgs a) {
     store_words(reinterpret_cast<uint32_t*>(lds + a.o_ids), r_ids, n, 0, lane);
     if (lane < a.D) reinterpret_cast<float*>(lds + a.o_lam)[lane] = lam;
     __builtin_amdgcn_wave_barrier();
-    tree_pop_search<1, RHO, QUAD>(a, lds);
+    tree_pop_search<RHO, QUAD>(a, lds);
 }
 
 // Beam search with global retention (Alg. 1): per depth, every beam entry's
@@ -1542,16 +1620,14 @@ static bool pops_first(int D, int k, int branch, int budget, bool lattice) {
 }
 
 // Level and beam kernels: candidate table, lambda, the pool with its sort
-// scratch (the one-node-at-a-time search of the level kernel reuses that
-// memory), then the lattice.
+// scratch, then the lattice.
 struct PoolLayout {
     int kw, cap, total;
     bool rho_in_lds;
     int o_lp, o_ids, o_lam, o_pool, o_key, o_hist, o_fine, o_list, o_place, o_row, o_par, o_misc, o_rho;
-    int o_kord, o_krank, o_rec, o_pkey;
 };
 
-static PoolLayout pool_layout_cap(int D, int k, int N, bool pops, bool lattice, int cap) {
+static PoolLayout pool_layout_cap(int D, int k, int N, bool lattice, int cap) {
     PoolLayout L;
     L.kw = D <= 2 * (32 / tree_key_bits(k)) ? 2 : 4;
     L.cap = cap;
@@ -1559,7 +1635,6 @@ static PoolLayout pool_layout_cap(int D, int k, int N, bool pops, bool lattice, 
     L.o_lp = off; off = align16(off + D * k * 4);
     L.o_ids = off; off = align16(off + D * k * 4);
     L.o_lam = off; off = align16(off + D * 4);
-    const int base = off;
     L.o_pool = off; off = align16(off + cap * 8);
     L.o_key = off; off = align16(off + cap * 4 * L.kw);
     L.o_hist = off; off = align16(off + kBins * 4);
@@ -1569,16 +1644,9 @@ static PoolLayout pool_layout_cap(int D, int k, int N, bool pops, bool lattice, 
     L.o_row = off; off = align16(off + N * 2);
     L.o_par = off; off = align16(off + N * 2);
     L.o_misc = off; off = align16(off + 64 * 4);
-    int end = off;
-    off = base;
-    L.o_kord = off; off = align16(off + N * k * 4);
-    L.o_krank = off; off = align16(off + N * k);
-    L.o_rec = off; off = align16(off + N * 8);
-    L.o_pkey = off; off = align16(off + N * 16);
-    if (pops && off > end) end = off;
-    L.o_rho = end;
+    L.o_rho = off;
     L.rho_in_lds = lattice;
-    L.total = lattice ? align16(end + D * k * k * k * 4) : end;
+    L.total = lattice ? align16(off + D * k * k * k * 4) : off;
     return L;
 }
 
@@ -1590,10 +1658,10 @@ static PoolLayout level_layout(int D, int k, int budget, bool lattice) {
     const int want = 5 * budget + 257 < kPoolMax ? 5 * budget + 257 : kPoolMax;
     for (int in_lds = lattice ? 1 : 0; in_lds >= 0; --in_lds)
         for (int cap = want; cap >= 2 * budget + 257; cap -= 64) {
-            const PoolLayout L = pool_layout_cap(D, k, N, true, in_lds != 0, cap);
+            const PoolLayout L = pool_layout_cap(D, k, N, in_lds != 0, cap);
             if (L.total <= kTreeLdsBudget) return L;
         }
-    return pool_layout_cap(D, k, N, true, false, 2 * budget + 257);
+    return pool_layout_cap(D, k, N, false, 2 * budget + 257);
 }
 
 // static LDS of the beam kernel, taken off the dynamic budget
@@ -1601,9 +1669,9 @@ static constexpr int kBeamStatic = 4096;
 
 static PoolLayout beam_layout(int D, int k, int budget, int width, bool lattice) {
     const int cap = budget + width * k + 1;  // root, T below the budget, one more depth
-    const PoolLayout L = pool_layout_cap(D, k, budget + 1, false, lattice, cap);
+    const PoolLayout L = pool_layout_cap(D, k, budget + 1, lattice, cap);
     if (!lattice || L.total <= kTreeLdsBudget - kBeamStatic) return L;
-    return pool_layout_cap(D, k, budget + 1, false, false, cap);
+    return pool_layout_cap(D, k, budget + 1, false, cap);
 }
 
 bool tree_build_fits(int D, int k, int branch, int N, int beam_width, bool alg2) {
@@ -1617,7 +1685,7 @@ presto_status launch_build_tree(const presto_tree_desc* desc, const int32_t* ids
                                 const int32_t* root_token, int32_t* n_nodes, int32_t* parent,
                                 int32_t* token, int32_t* depth, int32_t* rank, float* score,
                                 uint64_t* anc, hipStream_t stream) {
-    TreeArgs a;
+    TreeArgs a{};
     a.D = desc->depth;
     a.k = desc->k;
     a.branch = desc->branch;
@@ -1669,19 +1737,38 @@ presto_status launch_build_tree(const presto_tree_desc* desc, const int32_t* ids
     const bool beam = desc->mode == PRESTO_TREE_BEAM;
     const bool lattice = log_rho != nullptr;
     a.beam_width = beam ? desc->beam_width : 0;
+    if (!beam && pops_first(a.D, a.k, a.branch, a.budget, lattice)) {
+        // candidate table, lambda, then per node its children, record and path key
+        int lds = 0;
+        auto take = [&](int& at, int bytes) { at = lds; lds = align16(lds + bytes); };
+        take(a.o_lp, a.D * a.k * 4);
+        take(a.o_ids, a.D * a.k * 4);
+        take(a.o_lam, a.D * 4);
+        take(a.o_kord, a.N * a.k * 4);
+        take(a.o_krank, a.N * a.k);
+        take(a.o_rec, a.N * 8);
+        take(a.o_pkey, a.N * 16);
+        auto go = [&](auto kernel) { kernel<<<desc->batch, kWave, lds, stream>>>(a); };
+        if (a.k <= 4) {
+            if (lattice) go(tree_pop_kernel<2, true>);
+            else go(tree_pop_kernel<0, true>);
+        } else {
+            if (lattice) go(tree_pop_kernel<2, false>);
+            else go(tree_pop_kernel<0, false>);
+        }
+        return check_launch("tree_pop_kernel");
+    }
     const PoolLayout L = beam ? beam_layout(a.D, a.k, a.budget, a.beam_width, lattice)
                               : level_layout(a.D, a.k, a.budget, lattice);
     a.o_lp = L.o_lp; a.o_ids = L.o_ids; a.o_lam = L.o_lam; a.o_rho = L.o_rho;
     a.o_pool = L.o_pool; a.o_key = L.o_key; a.o_hist = L.o_hist; a.o_fine = L.o_fine; a.o_list = L.o_list;
     a.o_place = L.o_place; a.o_row = L.o_row; a.o_par = L.o_par; a.o_misc = L.o_misc;
-    a.o_kord = L.o_kord; a.o_krank = L.o_krank; a.o_rec = L.o_rec; a.o_pkey = L.o_pkey;
     a.cap = L.cap;
     const uint64_t k3 = (uint64_t)a.k * a.k * a.k;
     a.mag_k = (uint32_t)(((1ull << 32) + a.k - 1) / a.k);  // k > 1 only
     a.mag_k3 = (uint32_t)(((1ull << 32) + k3 - 1) / k3);
     const int rho_mode = !lattice ? 0 : (L.rho_in_lds ? 1 : 2);
-    const bool pops = !beam && pops_first(a.D, a.k, a.branch, a.budget, lattice);
-    const int threads = beam ? kBeamThreads : (pops ? kWave : level_threads(a.budget));
+    const int threads = beam ? kBeamThreads : level_threads(a.budget);
     auto go = [&](auto kernel) {
         st = allow_lds(kernel, L.total);
         if (st == PRESTO_OK) kernel<<<desc->batch, threads, L.total, stream>>>(a);
@@ -1696,30 +1783,15 @@ presto_status launch_build_tree(const presto_tree_desc* desc, const int32_t* ids
         if (st != PRESTO_OK) return st;
         return check_launch("tree_beam_kernel");
     }
-    if (pops) {
-        if (a.k <= 4) {
-            if (lattice) go(tree_pop_kernel<2, true>);
-            else go(tree_pop_kernel<0, true>);
-        } else {
-            if (lattice) go(tree_pop_kernel<2, false>);
-            else go(tree_pop_kernel<0, false>);
-        }
-        if (st != PRESTO_OK) return st;
-        return check_launch("tree_pop_kernel");
-    }
-#define PRESTO_LEVEL3(T, S, K)                                   \
-    if (rho_mode == 0) go(tree_level_kernel<T, S, 0, K>);        \
-    else if (rho_mode == 1) go(tree_level_kernel<T, S, 1, K>);   \
-    else go(tree_level_kernel<T, S, 2, K>)
-#define PRESTO_LEVEL(T, S) \
-    if (L.kw == 2) { PRESTO_LEVEL3(T, S, 2); } else { PRESTO_LEVEL3(T, S, 4); }
-    // the second parameter: frontier slots per lane of the one-node-at-a-time
-    // search, ceil(N / 64)
-    if (a.budget <= 64) { PRESTO_LEVEL(256, 2) }
-    else if (a.budget <= 128) { PRESTO_LEVEL(256, 3) }
-    else if (a.budget <= 256) { PRESTO_LEVEL(512, 5) }
-    else if (a.budget <= 512) { PRESTO_LEVEL(1024, 9) }
-    else { PRESTO_LEVEL(1024, 16) }
+#define PRESTO_LEVEL3(T, K)                                   \
+    if (rho_mode == 0) go(tree_level_kernel<T, 0, K>);        \
+    else if (rho_mode == 1) go(tree_level_kernel<T, 1, K>);   \
+    else go(tree_level_kernel<T, 2, K>)
+#define PRESTO_LEVEL(T) \
+    if (L.kw == 2) { PRESTO_LEVEL3(T, 2); } else { PRESTO_LEVEL3(T, 4); }
+    if (threads == 256) { PRESTO_LEVEL(256) }
+    else if (threads == 512) { PRESTO_LEVEL(512) }
+    else { PRESTO_LEVEL(1024) }
 #undef PRESTO_LEVEL
 #undef PRESTO_LEVEL3
     if (st != PRESTO_OK) return st;

@@ -253,9 +253,9 @@ def _shape_table(kind, rng, b, D, k):
 def test_tree_level_search_routes(kind, D, k, branch, B):
     """Budgets at the edges of the level kernel's sizes, two- and four-word
     rank-path keys (D = 16 | 17 at k = 10), levels that are counted before
-    they are entered, pools that overflow and are closed up, the way into the
-    one-node-at-a-time search (more ties than the pool holds) and trees that
-    candidates of S = -inf fill; beam search on the same tables.  Bit-exact."""
+    they are entered, pools that overflow and are closed up, more ties than the
+    pool holds, and trees that candidates of S = -inf fill; beam search on the
+    same tables.  Bit-exact."""
     rng = np.random.default_rng([D, k, B, len(kind)])
     b = 3
     lp = _shape_table(kind, rng, b, D, k)
@@ -271,15 +271,16 @@ def test_tree_level_search_routes(kind, D, k, branch, B):
 
 
 @pytest.mark.parametrize("D,k,branch,B", [(6, 16, 16, 300), (6, 16, 16, 512), (6, 16, 16, 800), (6, 15, 15, 400),
-                                          (6, 14, 14, 400), (12, 12, 12, 1023), (16, 10, 10, 1023), (14, 16, 12, 600)])
+                                          (6, 14, 14, 400), (12, 12, 12, 1023), (16, 10, 10, 1023), (14, 16, 12, 600),
+                                          (32, 4, 4, 128), (32, 4, 3, 129), (16, 4, 4, 64), (24, 2, 2, 11),
+                                          (16, 8, 8, 257)])
 @pytest.mark.parametrize("lattice", [False, True])
 def test_tree_more_ties_than_the_pool(D, k, branch, B, lattice):
     """Equal scores past the level search's pool: all scores alike (k >= 14:
-    a level of k^3 ties outgrows the pool) and candidates of probability 1
-    beside each other (every prefix of them ties).  The one-node-at-a-time
-    search then takes over the memory in which the workgroup's waves have just
-    read that the pool overflowed, so the shapes are those where its records
-    reach the histogram and the level counts.  Many sequences, bit-exact."""
+    a level of k^3 ties outgrows the pool), candidates of probability 1 beside
+    each other (every prefix of them ties, at every level anew) and scores of
+    few values.  The budget-th best is then found exactly, path and all, over
+    the pool and the level.  Many sequences, bit-exact."""
     b = 24
     ids = np.stack([[np.random.default_rng([s, d]).choice(5000, k, replace=False) for d in range(D)]
                     for s in range(b)]).astype(np.int32)
@@ -288,7 +289,8 @@ def test_tree_more_ties_than_the_pool(D, k, branch, B, lattice):
     sure = np.full((b, D, k), -3.0, np.float32)
     sure[:, :, :3] = 0.0
     rho = np.full((b, D, k, k, k), -0.5, np.float32) if lattice else None
-    for name, lp, lam_v in (("flat", flat, 0.25), ("sure", sure, 0.0)):
+    few = -np.sort(np.random.default_rng([D, k, B]).integers(0, 4, (b, D, k)) * 0.5, axis=2).astype(np.float32)
+    for name, lp, lam_v in (("flat", flat, 0.25), ("sure", sure, 0.0), ("few", few, 0.0)):
         lam = np.full(D, lam_v, np.float32)
         print(f"pool ties {name} D={D} k={k} branch={branch} B={B} lattice={lattice}", flush=True)
         g, o = _gpu_and_oracle(ids, lp, rho, lam, root, D, k, B, branch=branch)
