@@ -303,10 +303,11 @@ typedef struct {
     presto_dtype dt;
     int32_t ctx_layout; /* presto_ctx_layout */
     /* Sum of ctx_b over the batch, or 0 when the caller does not know it.
-     * A scheduling hint only: the result is the same for any value.  With
-     * ragged contexts it lets the context be split by the actual total, and
-     * the workgroups be dealt over the splits each sequence really has,
-     * instead of assuming batch x max_ctx. */
+     * A scheduling hint only: any value gives the same result up to the
+     * rounding of the split partials.  With ragged contexts it lets the
+     * contexts be split by the actual total, and the workgroups be dealt over
+     * the splits each sequence really has or over equal shares of all keys,
+     * instead of assuming batch x max_ctx.  The workspace size depends on it. */
     int64_t total_ctx;
 } presto_attn_desc;
 

@@ -32,17 +32,10 @@ __device__ __forceinline__ uint64_t vocab_key(float x, uint32_t id) {
 __device__ __forceinline__ uint32_t key_id(uint64_t k) { return 0xffffffffu - (uint32_t)k; }
 __device__ __forceinline__ float key_value(uint64_t k) { return unord32((uint32_t)(k >> 32)); }
 
-// bf16 <-> fp32 on raw bit patterns.
+// bf16 -> fp32 on raw bit patterns.
 __device__ __forceinline__ float bf16lo(uint32_t packed) { return __uint_as_float(packed << 16); }
 __device__ __forceinline__ float bf16hi(uint32_t packed) { return __uint_as_float(packed & 0xffff0000u); }
 __device__ __forceinline__ float bf16_to_f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
-__device__ __forceinline__ uint16_t f_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
 
 // 16-byte streaming load (read once: do not keep in the caches).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -52,43 +45,7 @@ __device__ __forceinline__ uint4 load_stream16(const void* p) {
 }
 
 // ---------------------------------------------------------------------------
-// Wave-wide reductions (butterfly: every lane ends with the result).
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        uint32_t w = __shfl_xor(v, o, kWave);
-        v = w > v ? w : v;
-    }
-    return v;
-}
-
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int o) {
-    uint32_t lo = __shfl_xor((uint32_t)v, o, kWave);
-    uint32_t hi = __shfl_xor((uint32_t)(v >> 32), o, kWave);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        uint64_t w = shfl_xor_u64(v, o);
-        v = w > v ? w : v;
-    }
-    return v;
-}
+// Wave-wide sum (butterfly: every lane ends with the result).
 
 __device__ __forceinline__ int wave_sum_i32(int v) {
 #pragma unroll
@@ -167,41 +124,24 @@ __device__ __forceinline__ uint32_t wave_min_u32_dpp(uint32_t v) {
 }
 
 // Inclusive prefix sum over the lanes of a wave.
-__device__ __forceinline__ int wave_prefix_sum_i32(int v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int t = __shfl_up(v, d);
-        if (lane >= d) v += t;
-    }
+__device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t v) {
+    v += dpp_u32<0x111>(0u, v);        // row_shr:1
+    v += dpp_u32<0x112>(0u, v);        // row_shr:2
+    v += dpp_u32<0x114>(0u, v);        // row_shr:4
+    v += dpp_u32<0x118>(0u, v);        // row_shr:8
+    v += dpp_u32<0x142, 0xa>(0u, v);   // row_bcast:15
+    v += dpp_u32<0x143, 0xc>(0u, v);   // row_bcast:31
     return v;
 }
 
-// Unsigned 64-bit max / min over the whole wave, as two 32-bit reductions:
-// the high words first, then the low words of the lanes holding that high
-// word (each stage is one fused DPP max/min per step).
+// Unsigned 64-bit max over the whole wave, as two 32-bit reductions: the high
+// words first, then the low words of the lanes holding that high word (each
+// stage is one fused DPP max per step).
 __device__ __forceinline__ uint64_t wave_max_u64_dpp(uint64_t v) {
     const uint32_t hi = (uint32_t)(v >> 32);
     const uint32_t H = wave_max_u32_dpp(hi);
     const uint32_t L = wave_max_u32_dpp(hi == H ? (uint32_t)v : 0u);
     return ((uint64_t)H << 32) | L;
-}
-
-__device__ __forceinline__ uint64_t wave_min_u64_dpp(uint64_t v) {
-    const uint32_t hi = (uint32_t)(v >> 32);
-    const uint32_t H = wave_min_u32_dpp(hi);
-    const uint32_t L = wave_min_u32_dpp(hi == H ? (uint32_t)v : ~0u);
-    return ((uint64_t)H << 32) | L;
-}
-
-// Unsigned 64-bit max over lanes 0..15 (row 0), returned to every lane.
-__device__ __forceinline__ uint64_t row0_max_u64_dpp(uint64_t v) {
-    uint64_t t;
-    t = dpp_u64<0xb1>(0ull, v); v = t > v ? t : v;
-    t = dpp_u64<0x4e>(0ull, v); v = t > v ? t : v;
-    t = dpp_u64<0x114>(0ull, v); v = t > v ? t : v;
-    t = dpp_u64<0x118>(0ull, v); v = t > v ? t : v;
-    return readlane_u64(v, 15);
 }
 
 // Flags word: OR a bit from one lane (vector atomic).

@@ -13,18 +13,19 @@
 // transposed, S^T = K Q^T: a lane then holds one query row and 16 of the 32
 // keys of a block, the row max needs one cross-half swap, and the bf16
 // probabilities are already in the B-operand layout of O^T = V^T P^T.  K and
-// V sit in LDS row-major (rows padded so that the b128 K reads and the
-// transposed ds_read_b64_tr_b16 V reads are free of bank conflicts).  Three
-// 64-key LDS buffers rotate: tile t is consumed, tile t+1 is resident (the
-// last block of a tile already scores the first block of the next), tile t+2
-// waits in registers; one barrier per tile.  Inside a wave the scores of
-// block i+1 are issued ahead of the softmax and P V of block i, so the matrix
-// cores can run while the vector ALUs work.  The running reference maximum
-// only moves when a block exceeds it by a margin, which keeps the 64-register
-// accumulator rescale off the common path.  The context is split across
-// workgroups when the batch alone cannot fill the chip; each split leaves,
-// per query row, its (reference, sum) pair and its output divided by its own
-// sum (bf16), which a second kernel merges.
+// V sit in LDS row-major (the chunks of a row permuted so that the b128 K reads
+// and the transposed ds_read_b64_tr_b16 V reads are free of bank conflicts).
+// Four 64-key LDS buffers rotate, filled straight from global memory: tile t is
+// consumed, tile t+1 is resident (the blocks of a tile already score those of
+// the next), tiles t+2 and t+3 are in flight; one barrier per tile.  Inside a
+// wave the P V of block i, the scores of block i+2 and the exponentials of
+// block i+1 are issued interleaved, so the matrix cores can run while the
+// vector ALUs work.  The running reference maximum only moves when a block
+// exceeds it by a margin, which keeps the 64-register accumulator rescale off
+// the common path.  The context is split across workgroups when the batch alone
+// cannot fill the chip; each split leaves, per query row, its (reference, sum)
+// pair and its output divided by its own sum (bf16), which a second kernel
+// merges.
 #include <math.h>
 
 #include <type_traits>
@@ -123,21 +124,11 @@ __device__ __forceinline__ int live_splits(const AttnArgs& a, int bb) {
     const int keys = ctx_span(a.ctx_off, bb, a.ctx_slots).ctx + clamp_nodes(a.n_nodes[bb], a.n_max);
     return (keys + a.split_len - 1) / a.split_len;
 }
-__device__ __forceinline__ int wave_prefix_dpp(int v) {
-    uint32_t x = (uint32_t)v;
-    x += dpp_u32<0x111>(0u, x);        // row_shr:1
-    x += dpp_u32<0x112>(0u, x);        // row_shr:2
-    x += dpp_u32<0x114>(0u, x);        // row_shr:4
-    x += dpp_u32<0x118>(0u, x);        // row_shr:8
-    x += dpp_u32<0x142, 0xa>(0u, x);   // row_bcast:15
-    x += dpp_u32<0x143, 0xc>(0u, x);   // row_bcast:31
-    return (int)x;
-}
 // All tiles of the batch (every wave computes it for itself).
 __device__ __forceinline__ int share_total(const AttnArgs& a) {
     int total = 0;
     for (int b0 = 0; b0 < a.batch; b0 += kWave)
-        total += __builtin_amdgcn_readlane(wave_prefix_dpp(share_tiles(a, b0 + lane_id())), kWave - 1);
+        total += __builtin_amdgcn_readlane((int)wave_scan_dpp(share_tiles(a, b0 + lane_id())), kWave - 1);
     return total;
 }
 
@@ -195,12 +186,12 @@ struct AttnLds {
 // TAIL: a tree of 2^i draft nodes has 2^i + 1 rows per query head, so that the
 // query rows often end 1 .. 16 past a multiple of 256.  A row tile of its own
 // for them streams all keys again through a workgroup that computes next to
-// nothing (4 sequences of 32768 keys: 560 us at 256 nodes, 663 at 257); here
-// the last full tile's workgroup takes them along on 16 x 16 MFMAs: of every
-// tile in LDS, waves 0 - 3 (one per SIMD) take sixteen keys each (scores
-// 16x16x32, P V 16x16x16, the query from LDS), about a tenth of a tile's matrix
-// work, and their states are combined at the end: 611 us; 129 nodes 383 -> 333,
-// 32 sequences of 2048 keys and 129 nodes 246 -> 218.
+// nothing; here the last full tile's workgroup takes them along on 16 x 16
+// MFMAs: of every tile in LDS, waves 0 - 3 (one per SIMD) take sixteen keys each
+// (scores 16x16x32, P V 16x16x16, the query from LDS), about a tenth of a
+// tile's matrix work, and their states are combined at the end.  us per call:
+// 4 sequences of 32768 keys, 257 nodes 618 -> 596, 129 nodes 374 -> 319;
+// 8 of 2048, 257 nodes 136 -> 92.
 template <int D, bool SHARES, bool TAIL>
 __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(AttnArgs a) {
     constexpr int KS = D / 16;                 // S^T contraction steps over the head dimension
@@ -226,7 +217,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
             // every wave counts the pairs itself
             int pairs = 0;
             for (int b0 = 0; b0 < a.batch; b0 += kWave)
-                pairs += __builtin_amdgcn_readlane(wave_prefix_dpp(live_splits(a, b0 + lane_id())), kWave - 1);
+                pairs += __builtin_amdgcn_readlane((int)wave_scan_dpp(live_splits(a, b0 + lane_id())), kWave - 1);
             n_tasks = pairs * a.hkv * a.row_tiles;
             n_blocks = (n_tasks + 7) / 8 * 8;
             if ((int)blockIdx.x >= n_blocks) return;
@@ -867,7 +858,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
                 // item = the pair's index in sequence order, splits in reverse as well
                 b = -1;
                 for (int b0 = 0, base = 0; b0 < a.batch && b < 0; b0 += kWave) {
-                    const int n = live_splits(a, b0 + lane_id()), incl = wave_prefix_dpp(n);
+                    const int n = live_splits(a, b0 + lane_id()), incl = (int)wave_scan_dpp(n);
                     const uint64_t hit = __ballot(base + incl > item);
                     if (hit) {
                         const int l = __ffsll((unsigned long long)hit) - 1;
@@ -892,7 +883,7 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
     if (from >= to) return;
     int b = -1, base = 0;  // the sequence and its first tile
     for (int b0 = 0; b0 < a.batch && b < 0; b0 += kWave) {
-        const int n = share_tiles(a, b0 + lane_id()), incl = wave_prefix_dpp(n);
+        const int n = share_tiles(a, b0 + lane_id()), incl = (int)wave_scan_dpp(n);
         const uint64_t hit = __ballot(base + incl > from);
         if (hit) {
             const int l = __ffsll((unsigned long long)hit) - 1;

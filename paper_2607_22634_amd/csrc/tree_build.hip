@@ -491,17 +491,6 @@ __device__ __forceinline__ uint32_t score_bin(float S) {
     return min(u - (127u << kBinBits), (uint32_t)(kBins - 1));
 }
 
-// Inclusive prefix sum over the wave (DPP, no LDS traffic).
-__device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t v) {
-    v += dpp_u32<0x111>(0u, v);        // row_shr:1
-    v += dpp_u32<0x112>(0u, v);        // row_shr:2
-    v += dpp_u32<0x114>(0u, v);        // row_shr:4
-    v += dpp_u32<0x118>(0u, v);        // row_shr:8
-    v += dpp_u32<0x142, 0xa>(0u, v);   // row_bcast:15
-    v += dpp_u32<0x143, 0xc>(0u, v);   // row_bcast:31
-    return v;
-}
-
 __device__ __forceinline__ int lanes_below(uint64_t m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
