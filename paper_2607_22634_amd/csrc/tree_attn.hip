@@ -924,8 +924,9 @@ __global__ __launch_bounds__(kAttnWaves * kWave) void tree_attn_bf16_kernel(Attn
 // small grid has one wave per SIMD, which spends its time on the weights and
 // sums (about 25 vector instructions per split and lane), so two dims per lane
 // spread it over four times the waves: whole calls of 1 x 4096 keys, 33 nodes
-// 22.3 -> 21.8 us, 9 nodes at 2048 keys 17.3 -> 16.4; at 264 workgroups of
-// eight dims (129 nodes) 30.2 -> 30.7, at 136 (65 nodes) 25.1 -> 24.8.
+// 22.3 -> 21.8 us, 9 nodes at 2048 keys 17.3 -> 16.4 (72 and 24 workgroups of
+// eight dims); at 136 (65 nodes) the merge takes 4.45 us with eight and 4.85
+// with two in a round, at 264 (129 nodes) the call 30.2 and 30.7.
 constexpr int kMergeUnroll = 8;
 template <int E>
 struct Bf16Chunk {
@@ -1719,9 +1720,9 @@ presto_status launch_tree_attention(const presto_attn_desc* d, const void* q, co
         else
             tree_attn_merge_kernel<128, E><<<mgrid, 256, 0, stream>>>(a);
     };
-    // eight dims per lane where that makes most of a workgroup per CU
+    // eight dims per lane where that makes a workgroup for every other CU or so
     const int64_t wide = (int64_t)pairs * ((p.rows * d->head_dim + 2047) / 2048);
-    if (wide >= 200) merge(std::integral_constant<int, 8>{});
+    if (wide >= 100) merge(std::integral_constant<int, 8>{});
     else merge(std::integral_constant<int, 2>{});
     return check_launch("tree_attn_merge_kernel");
 }

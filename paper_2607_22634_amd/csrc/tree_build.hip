@@ -865,7 +865,7 @@ __device__ __forceinline__ bool place_tree(const TreeArgs& a, char* lds, const P
         if (tid == NT - 1) P.fine[NF] = off;
     }
     __syncthreads();
-    if (!CUT && (int)M >= budget + kCrowd / 2 && P.misc[61] != 0u) return false;
+    if (!CUT && __builtin_expect((int)M >= budget + kCrowd / 2 && P.misc[61] != 0u, 0)) return false;
     for (int e = 1 + tid; e < n; e += NT) {
         const float S = P.S(e);
         if (takes(e, S)) P.list[P.fine[fine_bin(S)] + P.place[e]] = (uint16_t)e;
@@ -900,7 +900,7 @@ __device__ __forceinline__ bool place_tree(const TreeArgs& a, char* lds, const P
     }
     if (tid == 0) P.place[0] = 0;
     __syncthreads();
-    if (fill) {
+    if (__builtin_expect(fill, 0)) {
         uint16_t* child = reinterpret_cast<uint16_t*>(P.key);  // the keys have done their part
         for (int i = tid; i < n * k; i += NT) child[i] = 0;
         __syncthreads();
@@ -962,7 +962,7 @@ __device__ __forceinline__ bool place_tree(const TreeArgs& a, char* lds, const P
 template <int NT, int NF, int KW, typename Scores>
 __device__ __forceinline__ void finish_tree(const TreeArgs& a, char* lds, const Pool<KW>& P, int n,
                                             const Scores& scores, bool fill) {
-    if (place_tree<NT, NF, KW, false>(a, lds, P, n, scores, fill, Bound<KW>())) return;
+    if (__builtin_expect(place_tree<NT, NF, KW, false>(a, lds, P, n, scores, fill, Bound<KW>()), 1)) return;
     // without the entries past the budget-th best
     for (int i = threadIdx.x; i < NF; i += NT) P.fine[i] = 0u;
     __syncthreads();
@@ -1120,7 +1120,7 @@ __device__ __forceinline__ bool search_levels(const TreeArgs& a, const Pool<KW>&
         }
         __syncthreads();
         const int entered = (int)P.misc[d];
-        if (hi + entered > a.cap) {
+        if (__builtin_expect(hi + entered > a.cap, 0)) {
             // the histogram holds every candidate of the level, entered or not
             J = threshold_bin(P.hist, a.budget, known);
             __syncthreads();  // every wave has read the level's count
@@ -1155,7 +1155,7 @@ __global__ __launch_bounds__(NT) void tree_level_kernel(TreeArgs a) {
     int d = 1, lo = 0, hi = 1;  // next level, entries of the one above
     uint32_t J = kBins - 1;     // candidates in later bins are dropped
     bool below = false;         // a candidate of S = -inf was left out
-    if (!search_levels<NT, RHO, KW, false>(a, P, scores, d, lo, hi, J, below))
+    if (__builtin_expect(!search_levels<NT, RHO, KW, false>(a, P, scores, d, lo, hi, J, below), 0))
         search_levels<NT, RHO, KW, true>(a, P, scores, d, lo, hi, J, below);
     // the counts are shared, so the whole workgroup agrees on the outcome (a
     // wave's J may differ, finish_tree takes it anew)
