@@ -1239,14 +1239,15 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void tree_attn_f32_kernel(Att
     // holds, but the MFMAs have added 0 times that, NaN where V is not finite.
     // Where a live row's sums are not all finite, the workgroup starts over key
     // by key (looked for here: a test of V within the key loop cost it 8%).
-    uint32_t big = 0u;  // the largest |sum|, as bits
+    float odd[4] = {0.f, 0.f, 0.f, 0.f};  // NaN once a sum is not finite
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) big = max(big, __float_as_uint(o[db][e]) & 0x7fffffffu);
-    if (__ballot(is_live && big >= 0x7f800000u)) s_odd = 1;
+        for (int e = 0; e < 16; ++e) odd[e & 3] = fmaf(o[db][e], 0.f, odd[e & 3]);
+    const float any = (odd[0] + odd[1]) + (odd[2] + odd[3]);
+    if (__ballot(is_live && any != any)) s_odd = 1;
     __syncthreads();
-    if (s_odd) {
+    if (__builtin_expect(s_odd, 0)) {
         // one row per wave at a time, 64 keys per step, a key per lane for the
         // score and D / 64 dimensions per lane for the output
         constexpr int PER = D / kWave;
