@@ -1032,10 +1032,11 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
 // Q sits in LDS to leave the registers to the loads in flight.
 // 2 sequences x 2048 keys, 33 nodes, 32/8 heads of 128: 701 us with one wave
 // per query row and a key per lane (uncoalesced reads, each row reading all
-// of K and V), 46 now (43% of the cycles with the matrix cores busy; the rest is
+// of K and V), 45 now (the matrix cores busy 37% of the cycles; the rest is
 // the first blocks' arrival, which all workgroups wait for at once, the
 // exponentials of two waves per SIMD and the combination).  8 x 16384 keys, 32
-// nodes: 102 TFLOP/s (a large fp32 matrix product reaches 148 on this card).
+// nodes: 67% of the cycles, 86 TFLOP/s (a large fp32 matrix product reaches 148
+// on this card).
 struct AttnF32Args {
     const float* q;
     const float* kc;
