@@ -439,13 +439,14 @@ def test_attention_ragged_schedules(hq, hkv, d, N, b, max_ctx, total):
             parent[s, n] = rng.integers(max(0, n - 7), n)
     att, anc = _edge_inputs(rng, b, N, hq, hkv, d, ctx, dtype, parent, n_nodes)
     print(f"attn schedules hq={hq} hkv={hkv} d={d} N={N} b={b} max_ctx={max_ctx} total={total}", flush=True)
-    out = torch.full((b, N, hq, d), 7.0, dtype=torch.bfloat16, device="cuda")
-    for _ in range(2):  # the second call finds the first one's partials and notes in the workspace
+    outs = [torch.full((b, N, hq, d), x, dtype=torch.bfloat16, device="cuda") for x in (7.0, -3.0)]
+    for out in outs:
         P.presto_tree_attention(
             to_dev(att["q"], dtype), to_dev(att["k_cache"], dtype), to_dev(att["v_cache"], dtype),
             to_dev(att["ctx_offsets"]), to_dev(att["k_tree"], dtype), to_dev(att["v_tree"], dtype),
             to_dev(anc), to_dev(n_nodes), max_ctx, d ** -0.5, total_ctx=total, out=out)
     torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))  # bit for bit
     ref = oracle.tree_attention(dtype, att["q"], att["k_cache"], att["v_cache"], att["ctx_offsets"],
                                 att["k_tree"], att["v_tree"], anc, n_nodes, d ** -0.5)
     got = sy.as_f32(to_host(out), dtype).astype(np.float64)
@@ -493,12 +494,14 @@ def test_attention_rows_that_ride_along(hq, hkv, d, N, b, max_ctx, split_len):
             att["q"][s, n_nodes[s]:] = _not_numbers(dtype, att["q"][s, n_nodes[s]:].shape)
         print(f"attn along hq={hq} hkv={hkv} d={d} N={N} b={b} ctx={ctx[:3].tolist()} live={n_nodes[:3].tolist()}",
               flush=True)
-        out = torch.full((b, N, hq, d), 7.0, dtype=torch.bfloat16, device="cuda")
-        P.presto_tree_attention(
-            to_dev(att["q"], dtype), to_dev(att["k_cache"], dtype), to_dev(att["v_cache"], dtype),
-            to_dev(att["ctx_offsets"]), to_dev(att["k_tree"], dtype), to_dev(att["v_tree"], dtype),
-            to_dev(anc), to_dev(n_nodes), max_ctx, d ** -0.5, out=out)
+        outs = [torch.full((b, N, hq, d), x, dtype=torch.bfloat16, device="cuda") for x in (7.0, -3.0)]
+        for out in outs:
+            P.presto_tree_attention(
+                to_dev(att["q"], dtype), to_dev(att["k_cache"], dtype), to_dev(att["v_cache"], dtype),
+                to_dev(att["ctx_offsets"]), to_dev(att["k_tree"], dtype), to_dev(att["v_tree"], dtype),
+                to_dev(anc), to_dev(n_nodes), max_ctx, d ** -0.5, out=out)
         torch.cuda.synchronize()
+        assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))  # bit for bit
         ref = oracle.tree_attention(dtype, att["q"], att["k_cache"], att["v_cache"], att["ctx_offsets"],
                                     att["k_tree"], att["v_tree"], anc, n_nodes, d ** -0.5)
         got = sy.as_f32(to_host(out), dtype).astype(np.float64)
