@@ -559,7 +559,7 @@ def measure_at_scale(P, sy, dev):
                 "frac": round(gbs / HBM_PEAK_GBS, 4)}
 
     def tree_latency(us, tree):
-        # one wave per sequence, all sequences at once: the launch takes as
+        # one workgroup per sequence, all sequences at once: the launch takes as
         # long as the longest sequence's search
         nodes = int(tree["n_nodes"].max().item())
         return {"us": round(us, 2), "bound": "latency", "nodes_per_seq": nodes,

@@ -122,7 +122,7 @@ __device__ __forceinline__ int share_tiles(const AttnArgs& a, int bb) {
 __device__ __forceinline__ int live_splits(const AttnArgs& a, int bb) {
     if (bb >= a.batch) return 0;
     const int keys = ctx_span(a.ctx_off, bb, a.ctx_slots).ctx + clamp_nodes(a.n_nodes[bb], a.n_max);
-    return (keys + a.split_len - 1) / a.split_len;
+    return min((keys + a.split_len - 1) / a.split_len, a.splits);
 }
 // All tiles of the batch (every wave computes it for itself).
 __device__ __forceinline__ int share_total(const AttnArgs& a) {
@@ -1467,7 +1467,7 @@ static AttnPlan attn_plan_shares(const presto_attn_desc* d) {
     AttnPlan p = attn_plan_split(d, false, false, 1);
     p.cost = 1e30;
     const int64_t per_pair = (int64_t)d->hkv * p.row_tiles;
-    if (per_pair > 128 || (int64_t)d->batch * d->hkv > 65535) return p;
+    if (per_pair > 128) return p;
     const double row_bytes = 2.0 * d->head_dim + 8.0;
     const double tiles = ((double)d->total_ctx + (double)d->batch * d->n_max) / kKeyTile +
                          (kLeadTiles + 0.5) * d->batch;
@@ -1582,7 +1582,9 @@ static AttnPlan attn_plan_tail(const presto_attn_desc* d, const AttnPlan& p, int
 // a row's first key to its last, no bf16 partials and no merge (32 x 400 keys
 // 24.0 / 23.0 / 36.6, 32 x 1600 47.2 / 45.8 / 53.6).
 static AttnPlan attn_plan(const presto_attn_desc* d) {
-    if (!attn_ragged(d)) return attn_plan_tail(d, attn_plan_split(d, false, false, kMaxSplits), kMaxSplits);
+    // (65536 and more merges fit no schedule with partials: the grid that such batches fill unsplit)
+    if (!attn_ragged(d) || (int64_t)d->batch * d->hkv > 65535)
+        return attn_plan_tail(d, attn_plan_split(d, false, false, kMaxSplits), kMaxSplits);
     const AttnPlan pr = attn_plan_split(d, false, true, kMaxSplits);
     if (pr.splits == 1) return attn_plan_tail(d, attn_plan_split(d, false, false, 1), 1);
     const AttnPlan de = attn_plan_split(d, false, false, kMaxSplits);

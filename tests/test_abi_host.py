@@ -66,6 +66,14 @@ def test_attention_tail_rows_do_not_split_a_batch(b, max_ctx):
     assert P.lib().presto_tree_attention_workspace(ctypes.byref(d)) == 0
 
 
+def test_attention_ragged_batches_too_large_to_merge_are_not_split():
+    """batch x KV heads above the merge's grid: a hinted ragged batch is served
+    without partials, however uneven its contexts are."""
+    for b, hkv in ((70000, 1), (9000, 8)):
+        d = P.AttnDesc(b, 9, hkv, hkv, 64, 4000, 0.1, P.PRESTO_DT_BF16, P.PRESTO_CTX_PACKED, 100 * b)
+        assert P.lib().presto_tree_attention_workspace(ctypes.byref(d)) == 0
+
+
 def _err(status):
     return status, P.lib().presto_last_error().decode()
 
